@@ -225,6 +225,16 @@ PairShape pair_default_shape(int prec, int N);
 // k-point build (kpoint.hip): complex fields as interleaved (re, im) doubles.
 hipError_t kpair_round(int N, const void* u, void* spec, const KPair* slots, int nslots, void* W, const void* tw,
                        const KernelParams& kp, double c, hipStream_t s);
+// Owner-computes form of the k-point pair stage (grids kpair_owner_fits):
+// forward and z pass over nslots pairs, whose spectra are all resident in spec
+// (nslots * N^3 complex values), then every orbital's row of W from its
+// entries (slot, partner) adj_ptr[k] .. adj_ptr[k + 1] of adj; operm (nullable)
+// is the order the owners are dispatched in.  add: W already holds earlier
+// pairs (else every row is written).  nslots * N / 8 < 2^31.
+bool kpair_owner_fits(int N);
+hipError_t kpair_owner(int N, const void* u, void* spec, const KPair* slots, int64_t nslots, const int32_t* adj_ptr,
+                       const int32_t* adj, const int32_t* operm, int ntot, void* W, const void* tw,
+                       const KernelParams& kp, double c, bool add, hipStream_t s);
 void launch_times_minus_i(const void* W, void* Wm, int64_t n, hipStream_t s);
 void launch_hermitize(const double* Re, const double* Im, int n, int nk, void* Mout, void* negM, hipStream_t s);
 void launch_trace_avg(const double* Re, int n, int nk, double* ex, hipStream_t s);

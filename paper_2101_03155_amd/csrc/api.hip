@@ -1285,6 +1285,42 @@ int ace_apply_energy_noalloc(ace_ctx* c, const ace_grid* g, int norb, const doub
 
 
 // ------------------------------------------------------------------ complex orbitals, k-points
+// Pairs whose spectra the owner-computes form of the k-point build keeps
+// resident at a time, or 0 where it does not apply (the plane exceeds LDS, or
+// ACE_WORKSPACE_MAX leaves less than the split passes need): all of them
+// within the budget of the owner paths (ACE_OWNER_SPECTRA_MAX bytes, and 60%
+// of the free device memory), else as many as fit.  The other workspaces of
+// the call are already held.
+static int64_t kowner_chunk(ace_ctx* c, int N, int64_t npairs, int ntot, size_t slot_bytes) {
+  if (!kpair_owner_fits(N)) return 0;
+  const int64_t few = std::min<int64_t>(npairs, 32);  // the slots of one launch of the split passes
+  auto held = [c](const char* name) {
+    auto it = c->bufs.find(name);
+    return it == c->bufs.end() ? size_t(0) : it->second.bytes;
+  };
+  const size_t have = held("kspec");
+  size_t room = c->owner_max;
+  size_t freeb = 0, totb = 0;
+  if (std::min(room, size_t(npairs) * slot_bytes) > have && hipMemGetInfo(&freeb, &totb) == hipSuccess)
+    room = std::min(room, size_t(0.6 * double(freeb + have)));
+  int64_t chunk = std::max<int64_t>(few, int64_t(room / slot_bytes));
+  if (c->ws_cap) {
+    // under a workspace cap the tables come out of it first
+    const size_t others = c->ws_total - have - held("kslots") - held("kadj");
+    const size_t fixed = others + size_t(npairs) * sizeof(KPair);
+    for (;;) {
+      chunk = std::min(chunk, npairs);
+      const int64_t nchunk = (npairs + chunk - 1) / chunk;
+      const size_t tab = (size_t(nchunk) * (size_t(ntot) + 1) + 4 * size_t(npairs) + size_t(ntot)) * sizeof(int32_t);
+      if (fixed + tab + size_t(chunk) * slot_bytes <= c->ws_cap) break;
+      if (chunk <= few) return 0;
+      chunk = std::max(few, chunk / 2);
+    }
+  }
+  // the launch grids are 32-bit
+  return std::min<int64_t>(std::min(chunk, npairs), int64_t(1) << 22);
+}
+
 int ace_build_kpoints(ace_ctx* c, const ace_grid* g, int norb, int nk, const double* kvec, const double* u,
                       const int32_t* pairs, int64_t npairs, int kernel, double omega, double* xi, double* Mout,
                       double* Wout, double* ex) {
@@ -1312,18 +1348,6 @@ int ace_build_kpoints(ace_ctx* c, const ace_grid* g, int norb, int nk, const dou
   rc = schedule_for(c, pr, npairs, ntot, 16, &Sp);
   if (rc) return rc;
   const Schedule& S = *Sp;
-  // one slot per pair of every pack, launches in the schedule's order
-  std::vector<KPair> slots(2 * S.packs.size());
-  for (size_t p = 0; p < S.packs.size(); ++p) {
-    const Pack& pk = S.packs[p];
-    for (int h = 0; h < 2; ++h) {
-      KPair& kq = slots[2 * p + h];
-      kq.a = h ? pk.ib : pk.ia;
-      kq.b = h ? pk.jb : pk.ja;
-      for (int d = 0; d < 3; ++d)
-        kq.d[d] = kq.b < 0 ? 0.0 : kvec[3 * (kq.b / norb) + d] - kvec[3 * (kq.a / norb) + d];
-    }
-  }
   const void* tw;
   rc = twiddles(c, N, 0, &tw);
   if (rc) return rc;
@@ -1333,8 +1357,6 @@ int ace_build_kpoints(ace_ctx* c, const ace_grid* g, int norb, int nk, const dou
   int* info;
   int64_t kchunk;
   const int64_t nsplit = gemm_nt_nsplit(norb, norb, 2 * ng, &kchunk);
-  WS(c, "kslots", slots.size() * sizeof(KPair), dslots);
-  WS(c, "kspec", size_t(2 * S.max_launch) * ng * 2 * sizeof(double), spec);
   if (Wout) W = Wout; else WS(c, "kW", cbytes, W);
   WS(c, "kWm", cbytes, Wm);
   WS(c, "kMre", size_t(nk) * norb * norb * sizeof(double), Mre);
@@ -1345,16 +1367,73 @@ int ace_build_kpoints(ace_ctx* c, const ace_grid* g, int norb, int nk, const dou
   WS(c, "kLi", size_t(nk) * norb * norb * sizeof(double), Li);
   WS(c, "kX2", size_t(norb) * ng * 2 * sizeof(double), X2);
   WS(c, "kinfo", size_t(nk) * sizeof(int) + 64, info);
-  HIPCHK(c, hipMemcpyAsync(dslots, slots.data(), slots.size() * sizeof(KPair), hipMemcpyHostToDevice, s));
-  launch_zero(W, cbytes, s);
   KernelParams kp;
   kp.kind = kernel;
   kp.omega = omega;
   kp.inv_ng = 1.0 / double(ng);
   for (int d = 0; d < 3; ++d) kp.g[d] = 2.0 * 3.141592653589793238462643383279502884 / g->L[d];
-  // (c) pair potentials and W, launch by launch (each conflict-free)
-  for (const Schedule::Launch& l : S.launches)
-    HIPCHK(c, kpair_round(N, u, spec, dslots + 2 * size_t(l.first), 2 * l.second, W, tw, kp, 1.0 / nk, s));
+  // (c) pair potentials and W
+  auto slot_of = [&](int a, int b) {
+    KPair kq;
+    kq.a = a;
+    kq.b = b;
+    for (int d = 0; d < 3; ++d) kq.d[d] = b < 0 ? 0.0 : kvec[3 * (b / norb) + d] - kvec[3 * (a / norb) + d];
+    return kq;
+  };
+  const size_t slot_bytes = size_t(ng) * 2 * sizeof(double);
+  const int64_t chunk = kowner_chunk(c, N, npairs, ntot, slot_bytes);
+  if (chunk > 0) {
+    // owner-computes, the spectra of `chunk` pairs resident at a time; the
+    // entries of a chunk are the schedule's, in its order, by chunk-local slot
+    std::vector<KPair> slots(static_cast<size_t>(npairs));
+    for (int64_t p = 0; p < npairs; ++p) slots[size_t(p)] = slot_of(pr[size_t(2 * p)], pr[size_t(2 * p + 1)]);
+    const int64_t nchunk = (npairs + chunk - 1) / chunk;
+    const size_t np1 = size_t(ntot) + 1;
+    std::vector<int32_t> tab;  // per chunk its offsets (ntot + 1), then every chunk's entries, then the order
+    std::vector<int32_t> ent;
+    tab.reserve(size_t(nchunk) * np1 + S.adj.size() + size_t(ntot));
+    for (int64_t q = 0; q < nchunk; ++q) {
+      for (int k = 0; k < ntot; ++k) {
+        tab.push_back(int32_t(ent.size() / 2));
+        for (int a = S.adj_ptr[size_t(k)]; a < S.adj_ptr[size_t(k) + 1]; ++a) {
+          const int64_t p = S.adj[size_t(2 * a)] - q * chunk;
+          if (p < 0 || p >= chunk) continue;
+          ent.push_back(int32_t(p));
+          ent.push_back(S.adj[size_t(2 * a + 1)]);
+        }
+      }
+      tab.push_back(int32_t(ent.size() / 2));
+    }
+    const size_t ent_off = tab.size();
+    tab.insert(tab.end(), ent.begin(), ent.end());
+    const size_t perm_off = tab.size();
+    tab.insert(tab.end(), S.operm.begin(), S.operm.end());
+    int32_t* dtab;
+    WS(c, "kslots", slots.size() * sizeof(KPair), dslots);
+    WS(c, "kadj", tab.size() * sizeof(int32_t), dtab);
+    WS(c, "kspec", size_t(chunk) * slot_bytes, spec);
+    HIPCHK(c, hipMemcpyAsync(dslots, slots.data(), slots.size() * sizeof(KPair), hipMemcpyHostToDevice, s));
+    HIPCHK(c, hipMemcpyAsync(dtab, tab.data(), tab.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
+    for (int64_t q = 0; q < nchunk; ++q)
+      HIPCHK(c, kpair_owner(N, u, spec, dslots + q * chunk, std::min(chunk, npairs - q * chunk),
+                            dtab + size_t(q) * np1, dtab + ent_off, c->owner_order ? dtab + perm_off : nullptr, ntot,
+                            W, tw, kp, 1.0 / nk, q > 0, s));
+    // (pageable copies return once the host arrays are staged: no wait here)
+  } else {
+    // conflict-free launches of the split passes, one slot per pair of every
+    // pack, in the schedule's order
+    std::vector<KPair> slots(2 * S.packs.size());
+    for (size_t p = 0; p < S.packs.size(); ++p) {
+      slots[2 * p] = slot_of(S.packs[p].ia, S.packs[p].ja);
+      slots[2 * p + 1] = slot_of(S.packs[p].ib, S.packs[p].jb);
+    }
+    WS(c, "kslots", slots.size() * sizeof(KPair), dslots);
+    WS(c, "kspec", size_t(2 * S.max_launch) * slot_bytes, spec);
+    HIPCHK(c, hipMemcpyAsync(dslots, slots.data(), slots.size() * sizeof(KPair), hipMemcpyHostToDevice, s));
+    launch_zero(W, cbytes, s);
+    for (const Schedule::Launch& l : S.launches)
+      HIPCHK(c, kpair_round(N, u, spec, dslots + 2 * size_t(l.first), 2 * l.second, W, tw, kp, 1.0 / nk, s));
+  }
   // (d) per k-point M = dV U^H W from real products over the interleaved rows
   launch_times_minus_i(W, Wm, int64_t(ntot) * ng, s);
   for (int q = 0; q < nk; ++q) {

@@ -14,36 +14,22 @@
 // conj(V)).  Every pair is one full complex N^3 field: there is no Hermitian
 // symmetry to halve it and no second pair to pack into its imaginary part.
 //
-// The passes are the split ones of the real build (x rows in LDS, y and z
-// lines over x-tiles), with W updated by read-modify-write in conflict-free
-// rounds: within one launch no orbital appears in two pairs.
+// Where a complex plane fits in LDS (N <= 96) the stage is owner-computes, as
+// the real build's: a forward pass over (pair, z-plane), the z pass, and one
+// workgroup per (orbital, z-plane) that transforms the planes of its orbital's
+// pairs back and writes its row of W once; the spectra of all pairs (of a chunk
+// of them, where they exceed the budget) stay resident.  Larger planes take
+// the split passes (x rows in LDS, y and z lines over x-tiles), with W updated
+// by read-modify-write in conflict-free rounds: within one launch no orbital
+// appears in two pairs.
 #include <hip/hip_runtime.h>
 
 #include "ace_internal.h"
 #include "fft.h"
+#include "kpoint_phases.h"
 #include "pair_phases.h"
 
 namespace ace {
-
-// v(|G + d|) / N^3 at integer frequencies (kx, ky, kz) in FFT order.
-template <int N>
-__device__ __forceinline__ double kernel_value_shift(const KernelParams& kp, const double* d, int kx, int ky, int kz) {
-  const int sx = kx < (N + 1) / 2 ? kx : kx - N;
-  const int sy = ky < (N + 1) / 2 ? ky : ky - N;
-  const int sz = kz < (N + 1) / 2 ? kz : kz - N;
-  const double gx = kp.g[0] * sx + d[0], gy = kp.g[1] * sy + d[1], gz = kp.g[2] * sz + d[2];
-  const double g2 = gx * gx + gy * gy + gz * gz;
-  const double four_pi = 12.566370614359172953850573533118011537;
-  double v;
-  if (g2 == 0.0) {
-    v = (kp.kind == 0) ? 0.0 : 3.14159265358979323846264338327950288 / (kp.omega * kp.omega);
-  } else if (kp.kind == 0) {
-    v = four_pi / g2;
-  } else {
-    v = -four_pi / g2 * expm1(-g2 / (4.0 * kp.omega * kp.omega));
-  }
-  return v * kp.inv_ng;
-}
 
 // Forward x pass: f = conj(u_a) u_b over ROWS rows, row FFTs, store.
 template <int N, int ROWS, int NT>
@@ -179,6 +165,129 @@ hipError_t kpair_round(int N, const void* u, void* spec, const KPair* slots, int
   switch (N) {
 #define X(n) case n: return kpair_round_t<n>(u, spec, slots, nslots, W, tw, kp, c, s);
     X(8) X(12) X(16) X(24) X(32) X(48) X(64) X(80) X(96) X(100) X(108) X(120) X(160)
+#undef X
+    default: return hipErrorInvalidValue;
+  }
+}
+
+// ------------------------------------------------------------ owner-computes W
+// Bytes per pair in units of the complex field (N^3 x 16): the spectrum
+// written once, read and written by the z pass and read by each of the two
+// owners, and the orbitals' planes, most of which the caches serve; the split
+// passes move 16 units (five passes over the spectrum, four over W).  All
+// three kernels are bound by HBM: at 256 Bloch orbitals on 48^3 (about 17200
+// pairs, 30 GB of spectra) the forward takes 8.4 ms (3.6 TB/s of spectrum
+// writes), the z pass 11.8 ms (5.2 TB/s, the rate of a large copy) and the
+// owner pass 12.6 ms (4.8 TB/s of spectrum reads); the build went from 91.8 to
+// 36.0 ms.  Running forward and z pass in chunks that the memory-side cache
+// could hold (32 to 512 pairs) was slower (36.8 to 51 ms): the launches' tails
+// cost more than the shorter trips give.
+
+template <int N, int NT>
+__global__ __launch_bounds__(NT) void k_kfwd_xy(const double2* __restrict__ u, double2* __restrict__ spec,
+                                                const KPair* __restrict__ slots, const double2* __restrict__ twg) {
+  constexpr size_t PL = size_t(N) * N, NG = PL * N;
+  __shared__ double2 buf[N * (N + 1)];
+  __shared__ double2 tw[N];
+  const int tid = threadIdx.x;
+  // slots fastest: the workgroups in flight share a few z-planes of u
+  const size_t slot = blockIdx.x, zo = size_t(blockIdx.y) * PL;
+  for (int i = tid; i < N; i += NT) tw[i] = twg[i];
+  // one-pass plans have no barrier between this and the table's first use,
+  // and never use it
+  body_kfwd_xy<N, NT>(u + size_t(slots[slot].a) * NG + zo, u + size_t(slots[slot].b) * NG + zo, spec + slot * NG + zo,
+                      buf, tw, tid);
+}
+
+// SPW consecutive slots per workgroup: their kernel values are evaluated once
+// for each run of equal shifts (lists sorted by (a, b) hold one run per
+// k-point of b).
+template <int N, int TX, int NT, int SPW>
+__global__ __launch_bounds__(NT, N >= 80 ? 3 : 4) void k_kconv_own(double2* __restrict__ spec, const KPair* __restrict__ slots,
+                                                  int64_t nslots, const double2* __restrict__ twg, KernelParams kp) {
+  constexpr size_t NG = size_t(N) * N * N;
+  constexpr int NTILE = N * N / TX;
+  __shared__ double2 buf[N * TX];
+  __shared__ double2 tw[N];
+  const int tid = threadIdx.x;
+  for (int i = tid; i < N; i += NT) tw[i] = twg[i];
+  const int f0 = int(blockIdx.x % NTILE) * TX;
+  const int64_t s0 = int64_t(blockIdx.x / NTILE) * SPW;
+  double vv[kconv_lv<N, TX, NT>()], d[3];
+  for (int q = 0; q < SPW && s0 + q < nslots; ++q) {
+    const KPair& kq = slots[s0 + q];
+    if (q == 0 || kq.d[0] != d[0] || kq.d[1] != d[1] || kq.d[2] != d[2]) {
+      for (int x = 0; x < 3; ++x) d[x] = kq.d[x];
+      load_kvtile<N, TX, NT>(kp, d, f0, tid, vv);
+    }
+    int t = tid;  // opaque: keeps the transform's index arithmetic inside the loop
+    asm volatile("" : "+v"(t));
+    body_kconv_z<N, TX, NT>(spec + size_t(s0 + q) * NG + f0, buf, tw, t, vv);
+  }
+}
+
+// One workgroup per (orbital, z-plane); with N a multiple of 8 XCD x is given
+// the planes z = x mod 8 with the orbital fastest (as the real owner pass).
+template <int N, int NT>
+__global__ __launch_bounds__(NT) void k_kowner(const double2* __restrict__ u, const double2* __restrict__ spec,
+                                               const int32_t* __restrict__ adj_ptr, const int32_t* __restrict__ adj,
+                                               const int32_t* __restrict__ operm, int ntot, double2* __restrict__ W,
+                                               const double2* __restrict__ twg, double c, int add) {
+  constexpr size_t NG = size_t(N) * N * N;
+  __shared__ double2 buf[N * (N + 1)];
+  __shared__ double2 tw[N];
+  int z, k;
+  if (N % 8 == 0) {
+    const int l = int(blockIdx.x) >> 3;
+    z = (l / ntot) * 8 + (int(blockIdx.x) & 7);
+    k = l % ntot;
+  } else {
+    z = int(blockIdx.x) / ntot;
+    k = int(blockIdx.x) % ntot;
+  }
+  if (operm) k = operm[k];
+  const int a0 = adj_ptr[k], a1 = adj_ptr[k + 1];
+  if (add && a0 == a1) return;
+  for (int i = threadIdx.x; i < N; i += NT) tw[i] = twg[i];
+  body_kowner<N, NT>(u, spec, adj, a0, a1, k, z, W + size_t(k) * NG, c, add != 0, buf, tw, threadIdx.x);
+}
+
+template <int N>
+static hipError_t kpair_owner_t(const void* u_, void* spec_, const KPair* slots, int64_t nslots,
+                                const int32_t* adj_ptr, const int32_t* adj, const int32_t* operm, int ntot, void* W_,
+                                const void* tw_, const KernelParams& kp, double c, bool add, hipStream_t s) {
+  if constexpr (!kplane_fits<N>()) {
+    return hipErrorInvalidValue;
+  } else {
+    const double2* u = static_cast<const double2*>(u_);
+    double2* spec = static_cast<double2*>(spec_);
+    const double2* tw = static_cast<const double2*>(tw_);
+    constexpr int NTP = kplane_nt<N>(), TX = kconv_tx<N>(), NTZ = kconv_nt<N>(), SPW = 8, NTILE = N * N / TX;
+    hipLaunchKernelGGL((k_kfwd_xy<N, NTP>), dim3(unsigned(nslots), N), dim3(NTP), 0, s, u, spec, slots, tw);
+    hipLaunchKernelGGL((k_kconv_own<N, TX, NTZ, SPW>), dim3(unsigned((nslots + SPW - 1) / SPW * NTILE)), dim3(NTZ), 0,
+                       s, spec, slots, nslots, tw, kp);
+    hipLaunchKernelGGL((k_kowner<N, NTP>), dim3(unsigned(N) * unsigned(ntot)), dim3(NTP), 0, s, u, spec, adj_ptr, adj,
+                       operm, ntot, static_cast<double2*>(W_), tw, c, add ? 1 : 0);
+    return hipGetLastError();
+  }
+}
+
+bool kpair_owner_fits(int N) {
+  switch (N) {
+#define X(n) case n: return kplane_fits<n>();
+    X(8) X(12) X(16) X(24) X(32) X(48) X(64) X(80) X(96)
+#undef X
+    default: return false;
+  }
+}
+
+hipError_t kpair_owner(int N, const void* u, void* spec, const KPair* slots, int64_t nslots, const int32_t* adj_ptr,
+                       const int32_t* adj, const int32_t* operm, int ntot, void* W, const void* tw,
+                       const KernelParams& kp, double c, bool add, hipStream_t s) {
+  switch (N) {
+#define X(n) \
+  case n: return kpair_owner_t<n>(u, spec, slots, nslots, adj_ptr, adj, operm, ntot, W, tw, kp, c, add, s);
+    X(8) X(12) X(16) X(24) X(32) X(48) X(64) X(80) X(96)
 #undef X
     default: return hipErrorInvalidValue;
   }
