@@ -99,6 +99,7 @@ int pair_energy_blocks(int N, const PairShape& sh);
 bool pair_supported(int N);
 bool pair_r2c_fits(int prec, int N);
 int pair_owner_ntile(int prec, int N);  // z-pass tiles per pair slot of the owner path
+size_t pair_owner_slot_elems(int prec, int N);  // complex values per pair slot of the owner path
 // Owner-computes W over all pairs (spectra of every pair resident); operm
 // (nullable) is the order the owners are dispatched in; W may be
 // null (energies only); epart: per (pack, tile) partial energies or null; vt:
@@ -221,6 +222,10 @@ void launch_select(const float* pred, const float* feats, int64_t np, int norb, 
                    const double* O, double rho_cut, float ood_tol, int* ood, double* tau, uint8_t* keep, int64_t cap,
                    int32_t* pairs, int64_t* count, float* q, double* w, hipStream_t s);
 PairShape pair_default_shape(int prec, int N);
+// The shape the conflict-free rounds run in: sh, or where that is the owner
+// path (its spectra over budget) or does not fit, the real-to-complex or split
+// passes.
+PairShape pair_rounds_shape(int prec, int N, const PairShape& sh);
 
 // k-point build (kpoint.hip): complex fields as interleaved (re, im) doubles.
 hipError_t kpair_round(int N, const void* u, void* spec, const KPair* slots, int nslots, void* W, const void* tw,

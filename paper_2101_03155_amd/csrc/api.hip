@@ -546,7 +546,7 @@ int ace_set_pair_shape(ace_ctx* c, int prec, int n, int fused, int max_packs) {
   if (!c || (prec != 0 && prec != 1) || !pair_supported(n) || max_packs < 1 || fused < 0 || fused > 3)
     return fail(c, ACE_E_ARG, "bad pair shape");
   PairShape sh = pair_default_shape(prec, n);
-  sh.fused_xy = (fused >= 2 && fused <= 3 && pair_r2c_fits(prec, n)) ? fused
+  sh.fused_xy = fused == 3 || (fused == 2 && pair_r2c_fits(prec, n)) ? fused
                 : (fused == 1 && pair_fused_fits(prec, n)) ? 1 : 0;
   c->shapes[n * 2 + prec] = sh;
   c->max_packs[n * 2 + prec] = max_packs;
@@ -1029,13 +1029,13 @@ static int build_impl(ace_ctx* c, const ace_grid* g, int norb, const double* phi
   rec_begin(R, ST_BUILD, s);
 
   const size_t es = prec == 0 ? sizeof(double) : sizeof(float);
-  const PairShape sh = shape_for(c, prec, N);
+  PairShape sh = shape_for(c, prec, N);
   // owner-computes W when every pair's half spectrum fits the budget
   const int64_t onpk = int64_t(S.opacks.size());
-  const size_t slot_bytes = size_t(N) * N * (N / 2 + 1) * 2 * es;
+  const size_t slot_bytes = pair_owner_slot_elems(prec, N) * 2 * es;
   // ... and when the spectra, beyond what the workspace already holds, take
   // at most 60% of the free device memory (a fuller device slows down)
-  bool owner = sh.fused_xy == 3 && pair_r2c_fits(prec, N) && size_t(2 * onpk) * slot_bytes <= c->owner_max;
+  bool owner = sh.fused_xy == 3 && size_t(2 * onpk) * slot_bytes <= c->owner_max;
   if (owner) {
     const size_t need = size_t(2 * onpk) * slot_bytes;
     auto it = c->bufs.find("spec");
@@ -1044,6 +1044,7 @@ static int build_impl(ace_ctx* c, const ace_grid* g, int norb, const double* phi
     if (need > have && hipMemGetInfo(&freeb, &totb) == hipSuccess)
       owner = double(need) <= 0.6 * double(freeb + have);
   }
+  if (!owner) sh = pair_rounds_shape(prec, N, sh);
   const int nblk = owner ? pair_owner_ntile(prec, N) : pair_energy_blocks(N, sh);
   void *W, *spec, *phiw;
   Pack* dpk;

@@ -51,13 +51,16 @@ constexpr bool smooth235(int n) {
   return n == 1;
 }
 // The grid sizes of the pair stage whose factors do not pair up into radix-8
-// passes take composite radices 9, 10, 12 and 16 instead (two passes, so two
+// passes take composite radices 6, 9, 10, 12 and 16 instead (two passes, so two
 // LDS round trips per line rather than three or four).
 constexpr int plan_fill(int n, int* r) {
   switch (n) {
     case 12: r[0] = 12; return 1;
     case 16: r[0] = 16; return 1;
     case 48: r[0] = 4; r[1] = 12; return 2;
+    case 50: r[0] = 10; r[1] = 5; return 2;
+    case 54: r[0] = 9; r[1] = 6; return 2;
+    case 60: r[0] = 12; r[1] = 5; return 2;
     case 80: r[0] = 8; r[1] = 10; return 2;
     case 96: r[0] = 8; r[1] = 12; return 2;
     case 100: r[0] = 10; r[1] = 10; return 2;
@@ -255,6 +258,9 @@ __device__ __forceinline__ void dft_ct(C* v) {
   }
 }
 
+template <int S, typename C> struct Dft<6, S, C> {
+  static __device__ __forceinline__ void run(C* v) { dft_ct<2, 3, S, C>(v); }
+};
 template <int S, typename C> struct Dft<9, S, C> {
   static __device__ __forceinline__ void run(C* v) { dft_ct<3, 3, S, C>(v); }
 };
@@ -282,26 +288,33 @@ template <int S, typename C> struct Dft<16, S, C> {
 // WROT: threads whose butterfly index j has bit 2 set store their R outputs
 // in an order rotated by WROT (same values, same places, other instructions),
 // which moves their writes to other banks than those of threads j - 4.
+// The twiddles tw[m] = exp(-2 pi i m / N) come from an LDS table, or through
+// TwStride from the table of a multiple of N.
+template <typename T, int ST> struct TwStride {
+  const cplx<T>* p;
+  __device__ __forceinline__ cplx<T> operator[](int m) const { return p[m * ST]; }
+};
+
 template <typename T, int N, int P, int LINES, int LS, int PS, int NT, int S, bool JFAST, int V, bool END_SYNC,
-          int WROT = 0, typename L, typename St>
-__device__ __forceinline__ void fft_pass_ls(cplx<T>* buf, const cplx<T>* tw, int tid, L load, St store);
+          int WROT = 0, typename TW, typename L, typename St>
+__device__ __forceinline__ void fft_pass_ls(cplx<T>* buf, TW tw, int tid, L load, St store);
 
 template <typename T, int N, int P, int LINES, int LS, int PS, int NT, int S, bool JFAST, int V, int WROT = 0,
-          typename L>
-__device__ __forceinline__ void fft_pass_l(cplx<T>* buf, const cplx<T>* tw, int tid, L load) {
+          typename TW, typename L>
+__device__ __forceinline__ void fft_pass_l(cplx<T>* buf, TW tw, int tid, L load) {
   fft_pass_ls<T, N, P, LINES, LS, PS, NT, S, JFAST, V, true, WROT>(
       buf, tw, tid, load, [buf](int l, int p, cplx<T> x) { buf[l * LS + p * PS] = x; });
 }
 
-template <typename T, int N, int P, int LINES, int LS, int PS, int NT, int S, bool JFAST, int V>
-__device__ __forceinline__ void fft_pass(cplx<T>* buf, const cplx<T>* tw, int tid) {
+template <typename T, int N, int P, int LINES, int LS, int PS, int NT, int S, bool JFAST, int V, typename TW>
+__device__ __forceinline__ void fft_pass(cplx<T>* buf, TW tw, int tid) {
   fft_pass_l<T, N, P, LINES, LS, PS, NT, S, JFAST, V>(buf, tw, tid,
                                                       [buf](int l, int p) { return buf[l * LS + p * PS]; });
 }
 
 template <typename T, int N, int P, int LINES, int LS, int PS, int NT, int S, bool JFAST, int V, bool END_SYNC,
-          int WROT, typename L, typename St>
-__device__ __forceinline__ void fft_pass_ls(cplx<T>* buf, const cplx<T>* tw, int tid, L load, St store) {
+          int WROT, typename TW, typename L, typename St>
+__device__ __forceinline__ void fft_pass_ls(cplx<T>* buf, TW tw, int tid, L load, St store) {
   using C = cplx<T>;
   constexpr int R = plan_radix_v(N, P, V);
   constexpr int NS = plan_ns(N, P, V);
@@ -360,8 +373,8 @@ __device__ __forceinline__ void fft_pass_ls(cplx<T>* buf, const cplx<T>* tw, int
   if (END_SYNC) __syncthreads();
 }
 
-template <typename T, int N, int P, int LINES, int LS, int PS, int NT, int S, bool JFAST, int V>
-__device__ __forceinline__ void fft_lines_from(cplx<T>* buf, const cplx<T>* tw, int tid) {
+template <typename T, int N, int P, int LINES, int LS, int PS, int NT, int S, bool JFAST, int V, typename TW>
+__device__ __forceinline__ void fft_lines_from(cplx<T>* buf, TW tw, int tid) {
   if constexpr (P < plan_len(N)) {
     fft_pass<T, N, P, LINES, LS, PS, NT, S, JFAST, V>(buf, tw, tid);
     fft_lines_from<T, N, P + 1, LINES, LS, PS, NT, S, JFAST, V>(buf, tw, tid);
@@ -370,8 +383,8 @@ __device__ __forceinline__ void fft_lines_from(cplx<T>* buf, const cplx<T>* tw, 
 
 // Full length-N transform of LINES lines held in LDS.  tw[m] = exp(-2 pi i m/N).
 // Expects the caller to have synchronized after filling buf; ends synchronized.
-template <typename T, int N, int LINES, int LS, int PS, int NT, int S, bool JFAST, int V = 0>
-__device__ __forceinline__ void fft_lines(cplx<T>* buf, const cplx<T>* tw, int tid) {
+template <typename T, int N, int LINES, int LS, int PS, int NT, int S, bool JFAST, int V = 0, typename TW>
+__device__ __forceinline__ void fft_lines(cplx<T>* buf, TW tw, int tid) {
   static_assert(smooth235(N), "FFT length must be 2^a 3^b 5^c");
   fft_lines_from<T, N, 0, LINES, LS, PS, NT, S, JFAST, V>(buf, tw, tid);
 }
@@ -379,8 +392,8 @@ __device__ __forceinline__ void fft_lines(cplx<T>* buf, const cplx<T>* tw, int t
 // Passes P .. plan_len(N) - 2 in place, then the last pass through the storer
 // (followed by a barrier if ES, for a storer that writes LDS).
 template <typename T, int N, int P, int LINES, int LS, int PS, int NT, int S, bool JFAST, int V, bool ES = false,
-          typename St>
-__device__ __forceinline__ void fft_lines_to(cplx<T>* buf, const cplx<T>* tw, int tid, St store) {
+          typename TW, typename St>
+__device__ __forceinline__ void fft_lines_to(cplx<T>* buf, TW tw, int tid, St store) {
   if constexpr (P + 1 < plan_len(N)) {
     fft_pass<T, N, P, LINES, LS, PS, NT, S, JFAST, V>(buf, tw, tid);
     fft_lines_to<T, N, P + 1, LINES, LS, PS, NT, S, JFAST, V, ES>(buf, tw, tid, store);
@@ -395,8 +408,8 @@ __device__ __forceinline__ void fft_lines_to(cplx<T>* buf, const cplx<T>* tw, in
 // unless ES).  Expects nothing of buf (the first pass fills it after a
 // barrier); ends unsynchronized unless ES.
 template <typename T, int N, int LINES, int LS, int PS, int NT, int S, bool JFAST, int V, bool ES = false,
-          typename L, typename St>
-__device__ __forceinline__ void fft_lines_ls(cplx<T>* buf, const cplx<T>* tw, int tid, L load, St store) {
+          typename TW, typename L, typename St>
+__device__ __forceinline__ void fft_lines_ls(cplx<T>* buf, TW tw, int tid, L load, St store) {
   static_assert(smooth235(N), "FFT length must be 2^a 3^b 5^c");
   if constexpr (plan_len(N) == 1) {
     fft_pass_ls<T, N, 0, LINES, LS, PS, NT, S, JFAST, V, ES>(buf, tw, tid, load, store);
@@ -408,8 +421,8 @@ __device__ __forceinline__ void fft_lines_ls(cplx<T>* buf, const cplx<T>* tw, in
 
 // The same, with the first pass reading its inputs through load(l, p) (an
 // element-wise step fused into the transform's first LDS read).
-template <typename T, int N, int LINES, int LS, int PS, int NT, int S, bool JFAST, int V, typename L>
-__device__ __forceinline__ void fft_lines_load(cplx<T>* buf, const cplx<T>* tw, int tid, L load) {
+template <typename T, int N, int LINES, int LS, int PS, int NT, int S, bool JFAST, int V, typename TW, typename L>
+__device__ __forceinline__ void fft_lines_load(cplx<T>* buf, TW tw, int tid, L load) {
   static_assert(smooth235(N), "FFT length must be 2^a 3^b 5^c");
   fft_pass_l<T, N, 0, LINES, LS, PS, NT, S, JFAST, V>(buf, tw, tid, load);
   fft_lines_from<T, N, 1, LINES, LS, PS, NT, S, JFAST, V>(buf, tw, tid);

@@ -157,19 +157,46 @@ constexpr bool r2c_fits_t() {
   return (size_t(N) * r2c_xs<N>() + N) * sizeof(cplx<T>) + 1024 <= 163840;
 }
 
+// LDS values of one row class: its spectrum rows, or its packed x lines.
+template <int N, int YC> constexpr int cls_elems() {
+  constexpr int a = N / YC * r2c_xs<N>(), b = N / YC / 2 * xls<N>();
+  return a > b ? a : b;
+}
+// Launch shape of the owner path: row classes (YC), threads of the forward and
+// the owner pass, and columns per class, threads and slots per workgroup of
+// the z pass.  One class where two planes fit in a CU's LDS; where only one
+// does, or none, classes bring back two or three workgroups per CU, whose
+// transforms and memory phases then overlap.  Sums of the three FP64 passes,
+// before and after: 100^3 24.3 -> 17.6 ms, 108^3 26.5 -> 22.0, 120^3 33.8 ->
+// 29.3 (96 orbitals each), 160^3 62.3 (split passes) -> 28.8 (64 orbitals, 4
+// classes; 2 classes of one 1024-thread workgroup per CU: 32.7).  Smaller
+// planes gain nothing (96^3: 18.9 and 18.7 ms).  FP32 keeps whole planes: the
+// classes round differently, and FP32 results are kept to the bit; a plane
+// that fits once per CU (160^3) takes 1024 threads, four waves per SIMD.
+// z pass: the four slots of a workgroup share the tile's kernel values (FP64
+// 5% faster at 96^3; FP32, half the table, faster with one).
+template <typename T, int N> struct OwnCfg {
+  static constexpr bool D = sizeof(T) == 8;
+  static constexpr int YC = !D || N < 100 ? 1 : N == 160 ? 4 : 2;
+  static constexpr int NTF = N == 160 ? (D ? 320 : 1024) : 512;
+  static constexpr int NTO = N == 160 && !D ? 1024 : 512;
+  static constexpr int TX = YC == 1 ? 32 : YC == 2 ? 16 : 8, NTZ = YC == 4 ? 512 : 256;
+  static constexpr int SPW = D ? 4 : 1;
+};
+
 // ZFAST: blockIdx.x = z-plane, blockIdx.y = pair slot; otherwise the slot
 // runs fastest, so the workgroups in flight share a few z-planes and the
 // phi rows of those planes stay in the caches (dealing the planes to the
 // XCDs, as the owner pass does, measured no faster here: the pass is bound
 // by its spectrum writes).
-template <typename T, int N, int NT, bool ZFAST = true>
+// YC > 1: the z index runs over (plane, row class); PP: pitch of a class.
+template <typename T, int N, int NT, bool ZFAST = true, int YC = 1, int PP = N / YC * r2c_xs<N>()>
 __global__ __launch_bounds__(NT) void k_fwd_xy_r(const T* __restrict__ phi, cplx<T>* __restrict__ spec,
                                                  const Pack* __restrict__ packs,
                                                  const cplx<T>* __restrict__ twg) {
   using C = cplx<T>;
-  constexpr int XS = r2c_xs<N>();
-  constexpr size_t NG = size_t(N) * N * N, PL = size_t(N) * XS;
-  __shared__ C buf[N * XS];
+  constexpr size_t NG = size_t(N) * N * N;
+  __shared__ C buf[cls_elems<N, YC>()];
   __shared__ C tw[N];
   const int tid = threadIdx.x;
   const int z = ZFAST ? blockIdx.x : blockIdx.y, slot = ZFAST ? blockIdx.y : blockIdx.x;
@@ -177,20 +204,19 @@ __global__ __launch_bounds__(NT) void k_fwd_xy_r(const T* __restrict__ phi, cplx
   const int i = (slot & 1) ? pk.ib : pk.ia, j = (slot & 1) ? pk.jb : pk.ja;
   if (j < 0) return;
   for (int t = tid; t < N; t += NT) tw[t] = twg[t];
-  const size_t zo = size_t(z) * N * N;
-  body_fwd_xy_r<T, N, NT>(phi + size_t(i) * NG + zo, phi + size_t(j) * NG + zo,
-                          spec + size_t(slot) * N * PL + size_t(z) * PL, buf, tw, tid);
+  const size_t zo = size_t(z / YC) * N * N + size_t(z % YC) * N;
+  body_fwd_xy_r<T, N, NT, 0, YC>(phi + size_t(i) * NG + zo, phi + size_t(j) * NG + zo,
+                                 spec + (size_t(slot) * (N * YC) + z) * PP, buf, tw, tid);
 }
 
 // epart != nullptr: per-tile partial sums of sum_r rho v for the pair
 // energies, epart[2 * (pack * ntile + tile) + (slot & 1)].  SPW slots per
 // workgroup (blockIdx.y = slot group): the tile's slice of the v(G) table is
 // then fetched from memory once and re-read from L2 for the other slots.
-template <typename T, int N, int TX, int NT, int SPW = 1>
+template <typename T, int N, int TX, int NT, int SPW = 1, int PP = N * r2c_xs<N>()>
 __global__ __launch_bounds__(NT) void k_conv_z_r(cplx<T>* __restrict__ spec, const Pack* __restrict__ packs,
                                                  int nslots, const cplx<T>* __restrict__ twg, KernelParams kp,
                                                  double* __restrict__ epart, const T* __restrict__ vt) {
-  constexpr size_t PL = size_t(N) * r2c_xs<N>();
   __shared__ cplx<T> buf[N * TX];
   __shared__ cplx<T> tw[N];
   __shared__ double red[NT / 64];
@@ -205,8 +231,31 @@ __global__ __launch_bounds__(NT) void k_conv_z_r(cplx<T>* __restrict__ spec, con
     double* es = epart ? epart + 2 * (size_t(slot >> 1) * gridDim.x + blockIdx.x) + (slot & 1) : nullptr;
     // (each body's first barrier orders the previous body's reads of buf,
     // tw and red before its writes)
-    body_conv_z_r_v<T, N, TX, NT>(spec + size_t(slot) * N * PL, blockIdx.x * TX, kp, buf, tw, threadIdx.x, true, es,
+    body_conv_z_r_v<T, N, TX, NT, 0, PP>(spec + size_t(slot) * N * PP, blockIdx.x * TX, kp, buf, tw, threadIdx.x, true, es,
                                   red, vt != nullptr, vv);
+  }
+}
+
+// The z pass over row classes.
+template <typename T, int N, int TX, int YC, int NT, int SPW>
+__global__ __launch_bounds__(NT) void k_conv_z_c(cplx<T>* __restrict__ spec, const Pack* __restrict__ packs,
+                                                 int nslots, const cplx<T>* __restrict__ twg,
+                                                 double* __restrict__ epart, const T* __restrict__ vt) {
+  constexpr size_t PL = size_t(YC) * cls_pitch<T, N, YC>();
+  __shared__ cplx<T> buf[N * TX * YC];
+  __shared__ cplx<T> tw[N];
+  __shared__ double red[NT / 64];
+  for (int t = threadIdx.x; t < N; t += NT) tw[t] = twg[t];
+  T vv[conv_lv_c<T, N, TX, YC, NT>()];
+  load_vtile_c<T, N, TX, YC, NT>(vt, blockIdx.x * TX, threadIdx.x, vv);
+  for (int q = 0; q < SPW; ++q) {
+    const int slot = blockIdx.y * SPW + q;
+    if (slot >= nslots) break;
+    if ((slot & 1) && packs[slot >> 1].jb < 0) continue;
+    double* es = epart ? epart + 2 * (size_t(slot >> 1) * gridDim.x + blockIdx.x) + (slot & 1) : nullptr;
+    int t = threadIdx.x;  // opaque: keeps the transform's index arithmetic inside the loop
+    asm volatile("" : "+v"(t));
+    body_conv_z_c<T, N, TX, YC, NT>(spec + size_t(slot) * N * PL, blockIdx.x * TX, buf, tw, t, es, red, vv);
   }
 }
 
@@ -218,14 +267,15 @@ __global__ __launch_bounds__(NT) void k_conv_z_r(cplx<T>* __restrict__ spec, con
 // the eight XCDs in turn, so XCD x is given the planes z = x mod 8 with the
 // orbital fastest; the owners in flight on an XCD then share the partner
 // planes and spectra they read in that XCD's L2 (3-6% faster at 32 waters).
-template <typename T, int N, int NT, bool XCD = false>
+// YC > 1: the z index runs over (plane, row class).
+template <typename T, int N, int NT, bool XCD = false, int YC = 1>
 __global__ __launch_bounds__(NT, 4) void k_inv_owner_r(const T* __restrict__ phi, const cplx<T>* __restrict__ spec,
                                                     const int32_t* __restrict__ adj_ptr,
                                                     const int32_t* __restrict__ adj,
                                                     const int32_t* __restrict__ operm, T* __restrict__ W,
                                                     const cplx<T>* __restrict__ twg) {
   constexpr size_t NG = size_t(N) * N * N;
-  __shared__ cplx<T> buf[N * r2c_xs<N>()];
+  __shared__ cplx<T> buf[cls_elems<N, YC>()];
   __shared__ cplx<T> tw[N];
   int z, k;
   if (!XCD) {
@@ -233,15 +283,16 @@ __global__ __launch_bounds__(NT, 4) void k_inv_owner_r(const T* __restrict__ phi
     k = blockIdx.y;
   } else {
     const int i = blockIdx.x, l = i >> 3;
-    const int norb = int(gridDim.x) / N;
+    const int norb = int(gridDim.x) / (N * YC);
     z = (l / norb) * 8 + (i & 7);
     k = l % norb;
   }
   if (operm) k = operm[k];
   for (int t = threadIdx.x; t < N; t += NT) tw[t] = twg[t];
-  const size_t zo = size_t(z) * N * N;
-  body_inv_owner_r<T, N, NT>(phi, spec, adj, adj_ptr[k], adj_ptr[k + 1], zo,
-                                                W + size_t(k) * NG + zo, buf, tw, threadIdx.x);
+  const int cls = z % YC;
+  const size_t zo = size_t(z / YC) * N * N;
+  body_inv_owner_r<T, N, NT, 0, YC, cls_pitch<T, N, YC>()>(phi, spec, adj, adj_ptr[k], adj_ptr[k + 1], zo,
+                                    W + size_t(k) * NG + zo + size_t(cls) * N, buf, tw, threadIdx.x, cls);
 }
 
 template <typename T, int N, int NT, bool EN>
@@ -349,6 +400,12 @@ static hipError_t pair_round_t(const PairShape& sh, const void* phi_, void* spec
   return hipGetLastError();
 }
 
+// z-pass tiles per pair slot.
+template <typename T, int N> constexpr int own_tiles() {
+  constexpr int TX = OwnCfg<T, N>::TX, CP = N / OwnCfg<T, N>::YC * r2c_xs<N>();
+  return (CP + TX - 1) / TX;
+}
+
 // ------------------------------------------------------------ owner-computes W
 // All pairs are transformed forward (packs of consecutive pairs, no conflict
 // constraints: only phi is read) and convolved, with every pair's half
@@ -363,20 +420,16 @@ static hipError_t pair_owner_t(const void* phi_, void* spec_, const Pack* packs,
                                int64_t nadj, void* W_,
                                double* epart, const void* tw_, const KernelParams& kp, const void* vt_, int chunk,
                                hipStream_t s, EventRecorder* rec) {
-  if constexpr (!r2c_fits_t<T, N>()) {
-    return hipErrorInvalidValue;
-  } else {
+  {
     using C = cplx<T>;
     const T* phi = static_cast<const T*>(phi_);
     T* W = static_cast<T*>(W_);
     C* spec = static_cast<C*>(spec_);
     const C* tw = static_cast<const C*>(tw_);
-    // planes too large for two workgroups per CU take 1024 threads, so that
-    // one workgroup still runs four waves per SIMD
-    constexpr int NTR = size_t(N) * r2c_xs<N>() * sizeof(C) > 81920 ? 1024 : 512;
-    constexpr int NTL = 256, TXR = own_tx<T, N>();
-    constexpr int NTILE = own_ntile<T, N>();
-    constexpr size_t SLOT = size_t(N) * N * r2c_xs<N>();  // complex values per pair slot
+    using Cfg = OwnCfg<T, N>;
+    constexpr int YC = Cfg::YC, NTR = Cfg::NTO, NTZ = Cfg::NTZ, SPW = Cfg::SPW, NTILE = own_tiles<T, N>();
+    constexpr int PP = cls_pitch<T, N, YC>();
+    constexpr size_t SLOT = size_t(N) * YC * PP;  // complex values per pair slot
     const double u3 = double(N) * N * N * sizeof(T);
     // forward and z pass in launches of at most `chunk` packs (grid y = 2 *
     // packs <= 65534); one launch each over all pairs measured fastest
@@ -385,29 +438,28 @@ static hipError_t pair_owner_t(const void* phi_, void* spec_, const Pack* packs,
       const int nc = (npacks - c0 < CH) ? npacks - c0 : CH;
       const int pc = (2 * c0 + 2 * nc <= npairs) ? 2 * nc : npairs - 2 * c0;  // pairs in this chunk
       rec_begin(rec, KC_FWD_XY, s);
-      hipLaunchKernelGGL((k_fwd_xy_r<T, N, NTR, false>), dim3(2 * nc, N), dim3(NTR), 0, s, phi,
+      hipLaunchKernelGGL((k_fwd_xy_r<T, N, Cfg::NTF, false, YC, PP>), dim3(2 * nc, N * YC), dim3(Cfg::NTF), 0, s, phi,
                          spec + 2 * size_t(c0) * SLOT, packs + c0, tw);
       rec_end(rec, KC_FWD_XY, s, 3 * u3 * pc);
       rec_begin(rec, KC_CONV_Z, s);
-      // FP64: four slots per workgroup share the table slice (z pass 5% faster
-      // at 32 waters); FP32 (half the table) measured faster with one
-      if (sizeof(T) == 8)
-        hipLaunchKernelGGL((k_conv_z_r<T, N, TXR, NTL, 4>), dim3(NTILE, (2 * nc + 3) / 4), dim3(NTL), 0, s,
-                           spec + 2 * size_t(c0) * SLOT, packs + c0, 2 * nc, tw, kp,
-                           epart ? epart + 2 * size_t(c0) * NTILE : nullptr, static_cast<const T*>(vt_));
+      const dim3 gz(NTILE, (2 * nc + SPW - 1) / SPW);
+      C* spz = spec + 2 * size_t(c0) * SLOT;
+      double* ep = epart ? epart + 2 * size_t(c0) * NTILE : nullptr;
+      if constexpr (YC > 1)
+        hipLaunchKernelGGL((k_conv_z_c<T, N, Cfg::TX, YC, NTZ, SPW>), gz, dim3(NTZ), 0, s, spz, packs + c0, 2 * nc, tw,
+                           ep, static_cast<const T*>(vt_));
       else
-        hipLaunchKernelGGL((k_conv_z_r<T, N, TXR, NTL>), dim3(NTILE, 2 * nc), dim3(NTL), 0, s,
-                           spec + 2 * size_t(c0) * SLOT, packs + c0, 2 * nc, tw, kp,
-                           epart ? epart + 2 * size_t(c0) * NTILE : nullptr, static_cast<const T*>(vt_));
+        hipLaunchKernelGGL((k_conv_z_r<T, N, Cfg::TX, NTZ, SPW, PP>), gz, dim3(NTZ), 0, s, spz, packs + c0, 2 * nc, tw, kp,
+                           ep, static_cast<const T*>(vt_));
       rec_end(rec, KC_CONV_Z, s, 2 * u3 * pc);
     }
     if (W) {
       rec_begin(rec, KC_INV_XY, s);
-      if (N % 8 == 0)
-        hipLaunchKernelGGL((k_inv_owner_r<T, N, NTR, true>), dim3(N * norb), dim3(NTR), 0, s, phi, spec, adj_ptr, adj,
+      if (N * YC % 8 == 0)
+        hipLaunchKernelGGL((k_inv_owner_r<T, N, NTR, true, YC>), dim3(N * YC * norb), dim3(NTR), 0, s, phi, spec, adj_ptr, adj,
                            operm, W, tw);
       else
-        hipLaunchKernelGGL((k_inv_owner_r<T, N, NTR>), dim3(N, norb), dim3(NTR), 0, s, phi, spec, adj_ptr, adj, operm,
+        hipLaunchKernelGGL((k_inv_owner_r<T, N, NTR, false, YC>), dim3(N * YC, norb), dim3(NTR), 0, s, phi, spec, adj_ptr, adj, operm,
                            W, tw);
       rec_end(rec, KC_INV_XY, s, double(nadj) * (2.0 * SLOT * sizeof(T) + u3) + double(norb) * u3);
     }
@@ -476,7 +528,20 @@ hipError_t launch_vtable(int prec, int N, const KernelParams& kp, void* vt, hipS
 
 int pair_owner_ntile(int prec, int N) {
   switch (N) {
-#define X(n) case n: return prec == 0 ? own_ntile<double, n>() : own_ntile<float, n>();
+#define X(n) case n: return prec == 0 ? own_tiles<double, n>() : own_tiles<float, n>();
+    ACE_PAIR_SIZES(X)
+#undef X
+    default:
+      return 0;
+  }
+}
+
+size_t pair_owner_slot_elems(int prec, int N) {
+  switch (N) {
+#define X(n)                                                                       \
+  case n:                                                                          \
+    return prec == 0 ? n * OwnCfg<double, n>::YC * size_t(cls_pitch<double, n, OwnCfg<double, n>::YC>()) \
+                     : n * OwnCfg<float, n>::YC * size_t(cls_pitch<float, n, OwnCfg<float, n>::YC>());
     ACE_PAIR_SIZES(X)
 #undef X
     default:
@@ -491,6 +556,14 @@ bool pair_r2c_fits(int prec, int N) {
 #undef X
     default: return false;
   }
+}
+
+PairShape pair_rounds_shape(int prec, int N, const PairShape& sh) {
+  PairShape use = sh;
+  if (use.fused_xy == 3) use.fused_xy = 2;
+  if ((use.fused_xy == 1 && !pair_fused_fits(prec, N)) || (use.fused_xy == 2 && !pair_r2c_fits(prec, N)))
+    use.fused_xy = 0;
+  return use;
 }
 
 // Complex spectrum elements per pack (two pairs) for a launch shape.
@@ -513,7 +586,7 @@ bool pair_fused_fits(int prec, int N) {
 // even at one workgroup per CU (120^3 FP64, 160^3 FP32).
 PairShape pair_default_shape(int prec, int N) {
   PairShape sh;
-  sh.fused_xy = pair_r2c_fits(prec, N) ? 3 : 0;
+  sh.fused_xy = 3;
   sh.nt_xy = 512;
   sh.tx = pick_tx(N);
   return sh;
@@ -527,10 +600,7 @@ int pair_energy_blocks(int N, const PairShape& sh) {
 hipError_t pair_round(int prec, int N, const PairShape& sh, const void* phi, void* spec,
                       const Pack* packs, int npacks, int npairs, void* W, double* epart, const void* tw,
                       const KernelParams& kp, hipStream_t s, EventRecorder* rec) {
-  PairShape use = sh;
-  if (use.fused_xy == 3) use.fused_xy = 2;  // owner path over budget: real-to-complex rounds
-  if ((use.fused_xy == 1 && !pair_fused_fits(prec, N)) || (use.fused_xy == 2 && !pair_r2c_fits(prec, N)))
-    use.fused_xy = 0;
+  const PairShape use = pair_rounds_shape(prec, N, sh);
   switch (N) {
 #define X(n)                                                                                          \
   case n:                                                                                             \

@@ -226,10 +226,10 @@ template <int N> __device__ __forceinline__ int xpos(int e) { return e + e / N *
 // an order rotated by 2 (WROT), which puts them on the other half of the
 // bank groups.  (Padding the x lines instead made the FP64 owner kernel
 // spill registers.)  FP32 writes are conflict-free without the rotation.
-template <typename T, int N, int V> struct InvLayout {
+template <typename T, int N, int V, int YC = 1> struct InvLayout {
   static constexpr int XS = r2c_xs<N>();
   static constexpr int R0 = plan_radix_v(N, 0, V ^ 1);
-  static constexpr bool SIG = N % 32 == 0 && N / R0 == 8;
+  static constexpr bool SIG = N / YC % 32 == 0 && N / R0 == 8;
   static constexpr int WROT = sizeof(T) == 8 && SIG && R0 == 12 ? 2 : 0;
   static constexpr int XL = xls<N>();
   static __host__ __device__ __forceinline__ int ysig(int y) {
@@ -237,6 +237,15 @@ template <typename T, int N, int V> struct InvLayout {
   }
   static __host__ __device__ __forceinline__ int xq(int l, int p) { return l * XL + p; }
 };
+// Pitch of the resident spectra of the owner path, in complex values per row
+// class (YC of them per plane): whole 128-byte lines, so that the z pass's
+// tiles start on one.  Where N * XS values are not (120 in FP32, 100 and 108),
+// every second plane's tiles had straddled lines that two workgroups on
+// different XCDs then both fetched and wrote.
+template <typename T, int N, int YC> __host__ __device__ constexpr int cls_pitch() {
+  constexpr int LINE = 128 / int(2 * sizeof(T));
+  return (N / YC * r2c_xs<N>() + LINE - 1) / LINE * LINE;
+}
 template <int N> __host__ __device__ constexpr int r2c_tx() {
   return (N * r2c_xs<N>()) % 16 == 0 ? 16 : (N * r2c_xs<N>()) % 8 == 0 ? 8 : (N * r2c_xs<N>()) % 4 == 0 ? 4 : 2;
 }
@@ -249,13 +258,25 @@ template <typename T, int N> __host__ __device__ constexpr int own_ntile() {
   return (N * r2c_xs<N>() + own_tx<T, N>() - 1) / own_tx<T, N>();
 }
 
-// Pair density of plane z (phi_i, phi_j point at the plane) -> its half
-// spectrum after the x and y transforms, stored to out (N * XS values).
-template <typename T, int N, int NT, int V = 0>
+// Row classes (YC > 1): a plane whose half spectrum leaves room for one
+// workgroup per CU, or none, is taken as YC classes of rows y = c mod YC, each
+// of NY = N / YC rows in a workgroup of its own.  Class c transforms
+// y' = (y - c) / YC with length NY, and the z pass, which reads the same
+// columns of every class, joins them:
+//   X[ky' + NY q] = sum_c w_N^(c ky') w_YC^(c q) Y_c[ky'],
+// and splits them again after the multiplication, so the in-plane kernels
+// need 1 / YC of the LDS for the same bytes moved.  The spectrum of a plane is
+// then [c][ky'][kx] before and after the z pass.
+
+// Pair density of plane z (phi_i, phi_j point at the plane's first row of the
+// class) -> its half spectrum after the x and y transforms, stored to out
+// (NY * XS values).
+template <typename T, int N, int NT, int V = 0, int YC = 1>
 __device__ __forceinline__ void body_fwd_xy_r(const T* __restrict__ pi_, const T* __restrict__ pj_, cplx<T>* out,
                                               cplx<T>* buf, const cplx<T>* tw, int tid) {
   using C = cplx<T>;
-  constexpr int H = N / 2, XS = r2c_xs<N>();
+  constexpr int NY = N / YC, H = NY / 2, XS = r2c_xs<N>(), RP = N * YC;  // RP: pitch of the class's rows
+  const TwStride<T, YC> twy{tw};
   // The x transforms of the packed lines (line l: row l in .x, row l + H in
   // .y).  When the first pass has a butterfly for every thread it forms the
   // products from global memory itself (all of a thread's loads are issued
@@ -264,8 +285,8 @@ __device__ __forceinline__ void body_fwd_xy_r(const T* __restrict__ pi_, const T
   // loads in flight (measured).
   auto prod = [pi_, pj_](int l, int p) {
     C v;
-    v.x = pi_[l * N + p] * pj_[l * N + p];
-    v.y = pi_[(l + H) * N + p] * pj_[(l + H) * N + p];
+    v.x = pi_[l * RP + p] * pj_[l * RP + p];
+    v.y = pi_[(l + H) * RP + p] * pj_[(l + H) * RP + p];
     return v;
   };
   // The lines sit at stride xls<N>() in LDS; the passes that read LDS give
@@ -314,8 +335,8 @@ __device__ __forceinline__ void body_fwd_xy_r(const T* __restrict__ pi_, const T
     }
     return x;
   };
-  fft_lines_ls<T, N, XS, 1, XS, NT, -1, false, V>(buf, tw, tid, sep,
-                                                  [out](int l, int p, C x) { out[p * XS + l] = x; });
+  fft_lines_ls<T, NY, XS, 1, XS, NT, -1, false, V>(buf, twy, tid, sep,
+                                                   [out](int l, int p, C x) { out[p * XS + l] = x; });
 }
 
 // z lines of the TX consecutive flattened columns starting at f0 of one
@@ -348,8 +369,8 @@ __device__ __forceinline__ void load_vtile(const T* __restrict__ vt, int f0, int
 }
 
 // body_conv_z_r with the tile's kernel values already in registers (usev) or
-// evaluated per element (kp).
-template <typename T, int N, int TX, int NT, int V = 0>
+// evaluated per element (kp); PP: pitch of the planes.
+template <typename T, int N, int TX, int NT, int V = 0, int PP = N * r2c_xs<N>()>
 __device__ __forceinline__ void body_conv_z_r_v(cplx<T>* spec_p, int f0, const KernelParams& kp, cplx<T>* buf,
                                                 const cplx<T>* tw, int tid, bool active, double* eslot,
                                                 double* red, bool usev, const T (&vv)[conv_lv<T, N, TX, NT>()]) {
@@ -361,7 +382,7 @@ __device__ __forceinline__ void body_conv_z_r_v(cplx<T>* spec_p, int f0, const K
   const int ncol = PL - f0 < TX ? PL - f0 : TX;
   // forward z transforms, the first pass reading the tile from global memory
   fft_lines_load<T, N, TX, 1, TX, NT, -1, false, V>(buf, tw, tid, [=](int l, int p) {
-    if (active && (PL % TX == 0 || l < ncol)) return base[size_t(p) * PL + l];
+    if (active && (PL % TX == 0 || l < ncol)) return base[size_t(p) * PP + l];
     C zr;
     zr.x = T(0);
     zr.y = T(0);
@@ -394,7 +415,7 @@ __device__ __forceinline__ void body_conv_z_r_v(cplx<T>* spec_p, int f0, const K
   }
   // inverse z transforms, the last pass storing the tile to global memory
   fft_lines_to<T, N, 0, TX, 1, TX, NT, +1, false, V>(buf, tw, tid, [=](int l, int p, C x) {
-    if (active && (PL % TX == 0 || l < ncol)) base[size_t(p) * PL + l] = x;
+    if (active && (PL % TX == 0 || l < ncol)) base[size_t(p) * PP + l] = x;
   });
 }
 
@@ -407,6 +428,91 @@ __device__ __forceinline__ void body_conv_z_r(cplx<T>* spec_p, int f0, const Ker
   // the table loads are issued before the forward transform, so they overlap it
   if (vt) load_vtile<T, N, TX, NT>(vt, f0, tid, vv);
   body_conv_z_r_v<T, N, TX, NT, V>(spec_p, f0, kp, buf, tw, tid, active, eslot, red, vt != nullptr, vv);
+}
+
+// z pass over row classes: the TX flattened (ky', kx) columns starting at f0
+// of each of the YC classes of one pair's half spectrum; buf holds YC * TX
+// lines, line c * TX + l being column l of class c.  The z transforms act on
+// the classes one by one; the multiplication, which holds the same column and
+// kz of every class in one thread, joins them to the frequencies ky' + NY q,
+// multiplies, and splits them again.  Arguments as body_conv_z_r_v; vt is
+// required (load_vtile_c; a thread's values are those of its columns, q
+// fastest).
+template <typename T, int N, int TX, int YC, int NT> __host__ __device__ constexpr int conv_lv_c() {
+  return (N * TX + NT - 1) / NT * YC;
+}
+template <typename T, int N, int TX, int YC, int NT>
+__device__ __forceinline__ void load_vtile_c(const T* __restrict__ vt, int f0, int tid,
+                                             T (&vv)[conv_lv_c<T, N, TX, YC, NT>()]) {
+  constexpr int XS = r2c_xs<N>(), NY = N / YC, E = N * TX;
+#pragma unroll
+  for (int s = 0; s < (E + NT - 1) / NT; ++s) {
+    const int e = tid + s * NT, f = f0 + e % TX;
+    if ((E % NT == 0 || e < E) && (NY * XS % TX == 0 || f < NY * XS)) {
+#pragma unroll
+      for (int q = 0; q < YC; ++q)
+        vv[s * YC + q] =
+            vt[(size_t(vt_fold<N>(e / TX)) * vt_half<N>() + vt_fold<N>(f / XS + NY * q)) * XS + f % XS];
+    }
+  }
+}
+
+template <typename T, int N, int TX, int YC, int NT>
+__device__ __forceinline__ void body_conv_z_c(cplx<T>* spec_p, int f0, cplx<T>* buf, const cplx<T>* tw, int tid,
+                                              double* eslot, double* red,
+                                              const T (&vv)[conv_lv_c<T, N, TX, YC, NT>()]) {
+  using C = cplx<T>;
+  constexpr int XS = r2c_xs<N>(), NY = N / YC, CP = NY * XS, LN = TX * YC, E = N * TX;
+  constexpr int PP = cls_pitch<T, N, YC>(), PL = YC * PP;
+  C* base = spec_p + f0;
+  const int ncol = CP - f0 < TX ? CP - f0 : TX;
+  fft_lines_load<T, N, LN, 1, LN, NT, -1, false, 0>(buf, tw, tid, [=](int l, int p) {
+    if (CP % TX == 0 || l % TX < ncol) return base[size_t(p) * PL + l / TX * PP + l % TX];
+    C zr;
+    zr.x = T(0);
+    zr.y = T(0);
+    return zr;
+  });
+  double es = 0.0;
+#pragma unroll
+  for (int s = 0; s < (E + NT - 1) / NT; ++s) {
+    const int e = tid + s * NT, l = e % TX;
+    if (E % NT != 0 && e >= E) continue;
+    if (CP % TX != 0 && l >= ncol) continue;
+    const int kx = (f0 + l) % XS, ky = (f0 + l) / XS;
+    C* col = buf + e / TX * LN + l;
+    C t[YC];
+#pragma unroll
+    for (int c = 0; c < YC; ++c) {
+      t[c] = col[c * TX];
+      if (c > 0) t[c] = cmul(t[c], tw[c * ky]);
+    }
+    Dft<YC, -1, C>::run(t);
+#pragma unroll
+    for (int q = 0; q < YC; ++q) {
+      const T v = vv[s * YC + q];
+      if (eslot)
+        es += double((kx == 0 || kx == N / 2) ? 1 : 2) * double(v) * (double(t[q].x) * t[q].x + double(t[q].y) * t[q].y);
+      t[q].x *= v;
+      t[q].y *= v;
+    }
+    Dft<YC, +1, C>::run(t);
+#pragma unroll
+    for (int c = 0; c < YC; ++c) col[c * TX] = c > 0 ? cmulc(t[c], tw[c * ky]) : t[c];
+  }
+  if (eslot) {
+    for (int off = 32; off > 0; off >>= 1) es += __shfl_down(es, off, 64);
+    if ((tid & 63) == 0) red[tid >> 6] = es;
+  }
+  __syncthreads();
+  if (eslot && tid == 0) {
+    double sx = 0.0;
+    for (int w = 0; w < NT / 64; ++w) sx += red[w];
+    eslot[0] = sx;
+  }
+  fft_lines_to<T, N, 0, LN, 1, LN, NT, +1, false, 0>(buf, tw, tid, [=](int l, int p, C x) {
+    if (CP % TX == 0 || l % TX < ncol) base[size_t(p) * PL + l / TX * PP + l % TX] = x;
+  });
 }
 
 // Half spectrum of plane z -> the real potential of the plane, left in buf as
@@ -424,7 +530,7 @@ __device__ __forceinline__ void body_inv_xy_r(const cplx<T>* in, cplx<T>* buf, c
 }
 
 // The x transforms of body_inv_xy_t (buf holds the y-transformed plane).
-template <typename T, int N, int NT, int V>
+template <typename T, int N, int NT, int V, int YC = 1>
 __device__ __forceinline__ void inv_x_repacked(cplx<T>* buf, const cplx<T>* tw, int tid);
 
 template <typename T, int N, int NT, int V>
@@ -440,35 +546,35 @@ __device__ __forceinline__ void body_inv_xy_t(cplx<T>* buf, const cplx<T>* tw, i
 // The same from the half-spectrum plane in global memory: the first pass of
 // the y transforms reads it directly (no staging copy).  Needs no barrier
 // before it: the first pass reads before its barrier and writes after.
-template <typename T, int N, int NT, int V = 0>
+template <typename T, int N, int NT, int V = 0, int YC = 1>
 __device__ __forceinline__ void body_inv_xy_g(const cplx<T>* __restrict__ in, cplx<T>* buf, const cplx<T>* tw,
                                               int tid) {
-  using Lay = InvLayout<T, N, V>;
+  using Lay = InvLayout<T, N, V, YC>;
   constexpr int XS = r2c_xs<N>();
-  fft_lines_ls<T, N, XS, 1, XS, NT, +1, false, V, true>(
-      buf, tw, tid, [in](int l, int p) { return in[p * XS + l]; },
+  fft_lines_ls<T, N / YC, XS, 1, XS, NT, +1, false, V, true>(
+      buf, TwStride<T, YC>{tw}, tid, [in](int l, int p) { return in[p * XS + l]; },
       [buf](int l, int p, cplx<T> x) { buf[l + Lay::ysig(p) * XS] = x; });
-  inv_x_repacked<T, N, NT, V>(buf, tw, tid);
+  inv_x_repacked<T, N, NT, V, YC>(buf, tw, tid);
 }
 
-template <typename T, int N, int NT, int V>
+template <typename T, int N, int NT, int V, int YC>
 __device__ __forceinline__ void inv_x_repacked(cplx<T>* buf, const cplx<T>* tw, int tid) {
   using C = cplx<T>;
-  constexpr int H = N / 2, XS = r2c_xs<N>();
+  constexpr int H = N / YC / 2, NH = N / 2, XS = r2c_xs<N>();
   // The x transforms, whose first pass re-packs rows l and l + H into line
   // l on the way in: Z[k] = X1[k] + i X2[k] and Z[N-k] = conj X1[k] +
-  // i conj X2[k] for k <= H (X1, X2 = rows l, l + H of the [y][kx] layout);
+  // i conj X2[k] for k <= N/2 (X1, X2 = rows l, l + H of the [y][kx] layout);
   // the zero and Nyquist bins of a real row are real, as a c2r transform
   // takes them.  This pass keeps consecutive butterflies of one line on
   // consecutive threads (with consecutive lines its re-pack spills registers
   // in FP64), with the radix order reversed: the larger first radix spreads
   // its writes over more banks.  The later passes take consecutive lines.
-  using Lay = InvLayout<T, N, V>;
+  using Lay = InvLayout<T, N, V, YC>;
   fft_pass_l<T, N, 0, H, Lay::XL, 1, NT, +1, true, V ^ 1, Lay::WROT>(buf, tw, tid, [buf](int l, int p) {
-    const bool lowk = p <= H;
+    const bool lowk = p <= NH;
     const int k = lowk ? p : N - p;
     C x1 = buf[Lay::ysig(l) * XS + k], x2 = buf[Lay::ysig(l + H) * XS + k];
-    if (k == 0 || k == H) {
+    if (k == 0 || k == NH) {
       x1.y = T(0);
       x2.y = T(0);
     }
@@ -548,17 +654,23 @@ __device__ __forceinline__ void accumulate_w_r(const T* __restrict__ pi_, const 
 // W_k = -sum_j v_kj phi_j.  For each adjacency entry (pair slot p, partner j)
 // the pair's half-spectrum plane is transformed back and v_kj phi_j is added
 // to an accumulator in registers; the row is written once, never read.
-template <typename T, int N, int NT, int V = 0>
+// PP: pitch of a class (a plane where YC is 1) of the spectra.
+template <typename T, int N, int NT, int V = 0, int YC = 1, int PP = N / YC * r2c_xs<N>()>
 __device__ __forceinline__ void body_inv_owner_r(const T* __restrict__ phi, const cplx<T>* __restrict__ spec,
                                                  const int32_t* __restrict__ adj, int a0, int a1, size_t zo,
-                                                 T* __restrict__ wk, cplx<T>* buf, const cplx<T>* tw, int tid) {
-  constexpr int XS = r2c_xs<N>(), HN = (N / 2) * N;
-  constexpr size_t NG = size_t(N) * N * N, PL = size_t(N) * XS;
+                                                 T* __restrict__ wk, cplx<T>* buf, const cplx<T>* tw, int tid,
+                                                 int cls = 0) {
+  constexpr int HN = (N / YC / 2) * N;  // elements of the packed lines
+  constexpr size_t NG = size_t(N) * N * N, PL = size_t(YC) * PP;
+  // offset in the class's rows (row pitch N * YC) of packed element e
+  auto at = [](int e) { return YC == 1 ? e : e + e / N * (N * (YC - 1)); };
   constexpr int LP = (HN + NT - 1) / NT;
   T acc0[LP], acc1[LP];
 #pragma unroll
   for (int q = 0; q < LP; ++q) { acc0[q] = T(0); acc1[q] = T(0); }
-  const size_t zp = zo / (size_t(N) * N) * PL;  // plane offset in a pair's half spectrum
+  // offset of the plane's class in a pair's half spectrum
+  const size_t zp = zo / (size_t(N) * N) * PL + size_t(cls) * PP;
+  zo += size_t(cls) * N;  // (wk points at the class's first row)
   for (int a = a0; a < a1; ++a) {
     // an opaque copy of the thread index keeps the transform's index
     // arithmetic inside the loop (hoisted, it would all stay live)
@@ -567,7 +679,7 @@ __device__ __forceinline__ void body_inv_owner_r(const T* __restrict__ phi, cons
     const int p = adj[2 * a], j = adj[2 * a + 1];
     // (the first pass's barrier also orders the previous entry's reads of buf
     // before this entry's writes)
-    body_inv_xy_g<T, N, NT, V>(spec + size_t(p) * N * PL + zp, buf, tw, t);
+    body_inv_xy_g<T, N, NT, V, YC>(spec + size_t(p) * N * PL + zp, buf, tw, t);
     const T* fj = phi + size_t(j) * NG + zo;
     // partner row in batches of U elements per thread, loads first
     constexpr int U = 3;
@@ -577,7 +689,7 @@ __device__ __forceinline__ void body_inv_owner_r(const T* __restrict__ phi, cons
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int e = t + (q0 + u) * NT;
-        if (q0 + u < LP && (HN % NT == 0 || e < HN)) { f0[u] = fj[e]; f1[u] = fj[e + HN]; }
+        if (q0 + u < LP && (HN % NT == 0 || e < HN)) { f0[u] = fj[at(e)]; f1[u] = fj[at(e) + HN * YC]; }
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
@@ -593,7 +705,7 @@ __device__ __forceinline__ void body_inv_owner_r(const T* __restrict__ phi, cons
 #pragma unroll
   for (int q = 0; q < LP; ++q) {
     const int e = tid + q * NT;
-    if (HN % NT == 0 || e < HN) { wk[e] = -acc0[q]; wk[e + HN] = -acc1[q]; }
+    if (HN % NT == 0 || e < HN) { wk[at(e)] = -acc0[q]; wk[at(e) + HN * YC] = -acc1[q]; }
   }
 }
 
