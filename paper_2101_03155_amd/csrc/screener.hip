@@ -285,150 +285,237 @@ __global__ __launch_bounds__(256) void k_mlp_forward(const float* __restrict__ m
 
 // Minibatch gradient, per-block partial sums.  Sample k of the batch is
 // idx = (off + (b0 + k) * stride) mod n; the batch holds bsz samples (the
-// loss is their mean).  Each block takes whole chunks of 64 samples; thread t
-// owns gradient entries t, t + 256, ... (18 of them).
+// loss is their mean).  Each block takes whole chunks of 64 samples with 512
+// threads, everything in LDS: the three 64 x 64 x 64 products of a chunk
+// (hidden layer, its backward, and the gradient of W2) run on the FP32 matrix
+// cores, wave w owning the 16 x 16 tiles 2w and 2w + 1, the gradient tiles in
+// registers from chunk to chunk; the thin gradients (W1, b1, b2, w3, b3) are
+// one entry per thread.  At 4096 samples the launch is 64 blocks of one chunk,
+// so a step is a chain of LDS trips and barriers and is bound by their latency
+// (12 us, and 5 us for the Adam step; scalar loops over LDS took 114 and 18 us:
+// an epoch of 131072 samples went from 4.18 to 0.52 ms).
+// Rows have a pitch of 68 floats: the MFMA operand reads of 16 rows x 4 columns
+// then fall in 64 distinct banks, as 4 * row + column.
 constexpr int GCH = 64;
-constexpr int GPT = (NPAR + 255) / 256;
+constexpr int GNT = 512;
+constexpr int GP = 68;
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-__global__ __launch_bounds__(256) void k_mlp_grad_partial(const float* __restrict__ model, const float* __restrict__ x,
+// rows [16 tm, +16) x columns [16 tn, +16) of sum_k A(m, k) B(k, n) over 64 k;
+// a and b read A[m][k] and B[k][n] from LDS.
+template <typename FA, typename FB>
+__device__ __forceinline__ f32x4 tile64(int lane, FA a, FB b, f32x4 acc) {
+  const int i = lane & 15, q = lane >> 4;
+#pragma unroll
+  for (int k = 0; k < NH; k += 4) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a(i, k + q), b(k + q, i), acc, 0, 0, 0);
+  return acc;
+}
+
+__global__ __launch_bounds__(GNT) void k_mlp_grad_partial(const float* __restrict__ model, const float* __restrict__ x,
                                                           const float* __restrict__ t, int64_t n, int64_t off,
                                                           int64_t stride, int64_t b0, int bsz,
                                                           float* __restrict__ gpart, float* __restrict__ lpart) {
-  __shared__ float w[NMODEL];
-  __shared__ float xs[GCH][NIN];
-  __shared__ float H1[GCH][NH], H2[GCH][NH], D2[GCH][NH], D1[GCH][NH];
-  __shared__ float dout[GCH];
-  __shared__ float lsum[GCH];
-  const int tid = threadIdx.x;
-  for (int e = tid; e < NMODEL; e += 256) w[e] = model[e];
-  float acc[GPT];
+  __shared__ float W2[NH * GP], W2T[NH * GP], H1[GCH * GP], H2[GCH * GP], D2[GCH * GP], D1[GCH * GP];
+  __shared__ float xs[GCH][8];  // standardized features, [5] the standardized target
+  __shared__ float dout[GCH], lsum[GCH];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  for (int e = tid; e < NH * NH; e += GNT) {
+    const int j = e / NH, k = e % NH;
+    const float v = model[OW2 + e];
+    W2[j * GP + k] = v;
+    W2T[k * GP + j] = v;
+  }
+  // this thread's hidden unit in the first layer, and in the head its samples' part
+  const int hj = tid & 63, hs = tid >> 6;  // unit hj of samples hs, hs + 8, ...
+  float w1[NIN];
 #pragma unroll
-  for (int q = 0; q < GPT; ++q) acc[q] = 0.f;
-  float loss = 0.f;
-  __syncthreads();
+  for (int k = 0; k < NIN; ++k) w1[k] = model[OW1 + hj * NIN + k];
+  const float b1 = model[OB1 + hj];
+  const int ps = tid >> 3, pp = tid & 7;  // sample ps, hidden units 8 pp .. 8 pp + 7
+  float w3[8];
+#pragma unroll
+  for (int q = 0; q < 8; ++q) w3[q] = model[OW3 + 8 * pp + q];
+  const float b3 = model[OB3], tm = model[OTM], ts = model[OTS];
+  const float mu = pp < NIN ? model[OXM + pp] : 0.f, sd = pp < NIN ? model[OXS + pp] : 1.f;
+  const int ti = 2 * wv, tj = 2 * wv + 1;  // this wave's tiles (row ti / 4, column ti % 4)
+  const float b2i = model[OB2 + (ti & 3) * 16 + (lane & 15)], b2j = model[OB2 + (tj & 3) * 16 + (lane & 15)];
+  f32x4 g2i = {0.f, 0.f, 0.f, 0.f}, g2j = {0.f, 0.f, 0.f, 0.f};
+  // thin gradient entries: thread t < 320 owns W1 entry t, the next 64 b1, then b2, w3; thread 0 also b3
+  float gthin = 0.f, gb3 = 0.f, loss = 0.f;
   const int nch = (bsz + GCH - 1) / GCH;
   for (int ch = blockIdx.x; ch < nch; ch += gridDim.x) {
     const int s0 = ch * GCH;
     const int cnt = (bsz - s0 < GCH) ? bsz - s0 : GCH;
     // inputs and standardized targets
-    for (int e = tid; e < GCH * NIN; e += 256) {
-      const int sl = e / NIN, k = e % NIN;
+    {
       float v = 0.f;
-      if (sl < cnt) {
-        const int64_t idx = (off + (b0 + s0 + sl) * stride) % n;
-        v = (x[idx * NIN + k] - w[OXM + k]) / w[OXS + k];
+      if (ps < cnt && pp <= NIN) {
+        const int64_t idx = (off + (b0 + s0 + ps) * stride) % n;
+        v = pp < NIN ? (x[idx * NIN + pp] - mu) / sd : (t[idx] - tm) / ts;
       }
-      xs[sl][k] = v;
+      xs[ps][pp] = v;
     }
     __syncthreads();
-    for (int e = tid; e < GCH * NH; e += 256) {
-      const int sl = e / NH, j = e % NH;
-      float a = w[OB1 + j];
-      for (int k = 0; k < NIN; ++k) a += w[OW1 + j * NIN + k] * xs[sl][k];
-      H1[sl][j] = tanhf(a);
-    }
-    __syncthreads();
-    for (int e = tid; e < GCH * NH; e += 256) {
-      const int sl = e / NH, j = e % NH;
-      float a = w[OB2 + j];
-      for (int k = 0; k < NH; ++k) a += w[OW2 + j * NH + k] * H1[sl][k];
-      H2[sl][j] = tanhf(a);
-    }
-    __syncthreads();
-    if (tid < GCH) {
-      float o = w[OB3];
-      for (int j = 0; j < NH; ++j) o += w[OW3 + j] * H2[tid][j];
-      float r = 0.f;
-      if (tid < cnt) {
-        const int64_t idx = (off + (b0 + s0 + tid) * stride) % n;
-        r = o - (t[idx] - w[OTM]) / w[OTS];
-      }
-      dout[tid] = 2.f * r / float(bsz);
-      lsum[tid] = r * r / float(bsz);
-    }
-    __syncthreads();
-    for (int e = tid; e < GCH * NH; e += 256) {
-      const int sl = e / NH, j = e % NH;
-      D2[sl][j] = dout[sl] * w[OW3 + j] * (1.f - H2[sl][j] * H2[sl][j]);
-    }
-    __syncthreads();
-    for (int e = tid; e < GCH * NH; e += 256) {
-      const int sl = e / NH, k = e % NH;
-      float a = 0.f;
-      for (int j = 0; j < NH; ++j) a += D2[sl][j] * w[OW2 + j * NH + k];
-      D1[sl][k] = a * (1.f - H1[sl][k] * H1[sl][k]);
-    }
-    __syncthreads();
-    if (tid == 0)
-      for (int sl = 0; sl < GCH; ++sl) loss += lsum[sl];
 #pragma unroll
-    for (int q = 0; q < GPT; ++q) {
-      const int e = tid + q * 256;
-      if (e >= NPAR) continue;
+    for (int q = 0; q < GCH / 8; ++q) {
+      const int sl = hs + 8 * q;
+      float a = b1;
+#pragma unroll
+      for (int k = 0; k < NIN; ++k) a += w1[k] * xs[sl][k];
+      H1[sl * GP + hj] = tanhf(a);
+    }
+    __syncthreads();
+    {
+      const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+      auto fwd = [&](int tl, float b2) {
+        const int m0 = (tl >> 2) * 16, n0 = (tl & 3) * 16;
+        const f32x4 z = tile64(lane, [&](int i, int k) { return H1[(m0 + i) * GP + k]; },
+                               [&](int k, int i) { return W2[(n0 + i) * GP + k]; }, zero);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) H2[(m0 + 4 * (lane >> 4) + r) * GP + n0 + (lane & 15)] = tanhf(z[r] + b2);
+      };
+      fwd(ti, b2i);
+      fwd(tj, b2j);
+    }
+    __syncthreads();
+    {
+      float h[8], o = 0.f;
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        h[q] = H2[ps * GP + 8 * pp + q];
+        o += w3[q] * h[q];
+      }
+      for (int m = 1; m < 8; m <<= 1) o += __shfl_xor(o, m, 64);
+      const float r = ps < cnt ? o + b3 - xs[ps][NIN] : 0.f;
+      const float d = 2.f * r / float(bsz);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) D2[ps * GP + 8 * pp + q] = d * w3[q] * (1.f - h[q] * h[q]);
+      if (pp == 0) {
+        dout[ps] = d;
+        lsum[ps] = r * r / float(bsz);
+      }
+    }
+    __syncthreads();
+    {
+      const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+      auto bwd = [&](int tl) {
+        const int m0 = (tl >> 2) * 16, n0 = (tl & 3) * 16;
+        const f32x4 z = tile64(lane, [&](int i, int k) { return D2[(m0 + i) * GP + k]; },
+                               [&](int k, int i) { return W2T[(n0 + i) * GP + k]; }, zero);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int e = (m0 + 4 * (lane >> 4) + r) * GP + n0 + (lane & 15);
+          D1[e] = z[r] * (1.f - H1[e] * H1[e]);
+        }
+      };
+      bwd(ti);
+      bwd(tj);
+      auto grad = [&](int tl, f32x4 acc) {
+        const int m0 = (tl >> 2) * 16, n0 = (tl & 3) * 16;
+        return tile64(lane, [&](int i, int s) { return D2[s * GP + m0 + i]; },
+                      [&](int s, int i) { return H1[s * GP + n0 + i]; }, acc);
+      };
+      g2i = grad(ti, g2i);
+      g2j = grad(tj, g2j);
+    }
+    __syncthreads();
+    {
       float g = 0.f;
-      if (e < OB1) {
-        const int j = (e - OW1) / NIN, k = (e - OW1) % NIN;
-        for (int sl = 0; sl < GCH; ++sl) g += D1[sl][j] * xs[sl][k];
-      } else if (e < OW2) {
-        const int j = e - OB1;
-        for (int sl = 0; sl < GCH; ++sl) g += D1[sl][j];
-      } else if (e < OB2) {
-        const int j = (e - OW2) / NH, k = (e - OW2) % NH;
-        for (int sl = 0; sl < GCH; ++sl) g += D2[sl][j] * H1[sl][k];
-      } else if (e < OW3) {
-        const int j = e - OB2;
-        for (int sl = 0; sl < GCH; ++sl) g += D2[sl][j];
-      } else if (e < OB3) {
-        const int j = e - OW3;
-        for (int sl = 0; sl < GCH; ++sl) g += dout[sl] * H2[sl][j];
+      if (tid < OB1) {
+        const int j = tid / NIN, k = tid % NIN;
+        for (int sl = 0; sl < GCH; ++sl) g += D1[sl * GP + j] * xs[sl][k];
+      } else if (tid < OB1 + NH) {
+        for (int sl = 0; sl < GCH; ++sl) g += D1[sl * GP + tid - OB1];
+      } else if (tid < OB1 + 2 * NH) {
+        for (int sl = 0; sl < GCH; ++sl) g += D2[sl * GP + tid - OB1 - NH];
       } else {
-        for (int sl = 0; sl < GCH; ++sl) g += dout[sl];
+        for (int sl = 0; sl < GCH; ++sl) g += dout[sl] * H2[sl * GP + tid - OB1 - 2 * NH];
       }
-      acc[q] += g;
+      gthin += g;
+      if (wv == 0) {  // (every lane of the wave ends with the sums)
+        float a = dout[lane], l = lsum[lane];
+        for (int m = 1; m < 64; m <<= 1) {
+          a += __shfl_xor(a, m, 64);
+          l += __shfl_xor(l, m, 64);
+        }
+        gb3 += a;
+        loss += l;
+      }
     }
     __syncthreads();
   }
+  float* out = gpart + int64_t(blockIdx.x) * NPAR;
 #pragma unroll
-  for (int q = 0; q < GPT; ++q) {
-    const int e = tid + q * 256;
-    if (e < NPAR) gpart[int64_t(blockIdx.x) * NPAR + e] = acc[q];
+  for (int r = 0; r < 4; ++r) {
+    out[OW2 + ((ti >> 2) * 16 + 4 * (lane >> 4) + r) * NH + (ti & 3) * 16 + (lane & 15)] = g2i[r];
+    out[OW2 + ((tj >> 2) * 16 + 4 * (lane >> 4) + r) * NH + (tj & 3) * 16 + (lane & 15)] = g2j[r];
   }
-  if (tid == 0) lpart[blockIdx.x] = loss;
+  out[tid < OW2 ? tid : OB2 - OW2 + tid] = gthin;  // W1 and b1, then b2 and w3
+  if (tid == 0) {
+    out[OB3] = gb3;
+    lpart[blockIdx.x] = loss;
+  }
+}
+static_assert(OB1 + 3 * NH == GNT && OW2 == OB1 + NH, "one thin gradient entry per thread");
+
+// Sum over the block partials of one parameter per group of 8 threads (thread
+// g takes blocks g, g + 8, ..., the groups' sums are added in order), 32
+// parameters per workgroup; returned to the group's first thread.
+constexpr int RG = 8, RPB = 32;
+__device__ __forceinline__ float partial_sum(const float* __restrict__ gpart, int nb, int e, float (&red)[RG][RPB]) {
+  const int p = threadIdx.x % RPB, g = threadIdx.x / RPB;
+  float a = 0.f;
+  if (e < NPAR)
+    for (int b = g; b < nb; b += RG) a += gpart[int64_t(b) * NPAR + e];
+  red[g][p] = a;
+  __syncthreads();
+  float s = 0.f;
+  if (g == 0)
+    for (int q = 0; q < RG; ++q) s += red[q][p];
+  return s;
+}
+// The block losses, summed by the first wave of workgroup 0.
+__device__ __forceinline__ float loss_sum(const float* __restrict__ lpart, int nb) {
+  float l = 0.f;
+  for (int b = threadIdx.x; b < nb; b += 64) l += lpart[b];
+  for (int m = 1; m < 64; m <<= 1) l += __shfl_xor(l, m, 64);
+  return l;
 }
 
-// Sum of the block partials in block order: gradient and loss.
-__global__ void k_mlp_reduce(const float* __restrict__ gpart, const float* __restrict__ lpart, int nb,
-                             float* __restrict__ grad, float* __restrict__ loss) {
-  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < NPAR; e += gridDim.x * blockDim.x) {
-    float g = 0.f;
-    for (int b = 0; b < nb; ++b) g += gpart[int64_t(b) * NPAR + e];
-    grad[e] = g;
-  }
-  if (blockIdx.x == 0 && threadIdx.x == 0 && loss) {
-    float l = 0.f;
-    for (int b = 0; b < nb; ++b) l += lpart[b];
-    loss[0] = l;
+// Sum of the block partials in a fixed order: gradient and loss.
+__global__ __launch_bounds__(RG * RPB) void k_mlp_reduce(const float* __restrict__ gpart,
+                                                         const float* __restrict__ lpart, int nb,
+                                                         float* __restrict__ grad, float* __restrict__ loss) {
+  __shared__ float red[RG][RPB];
+  const int e = blockIdx.x * RPB + threadIdx.x % RPB;
+  const float g = partial_sum(gpart, nb, e, red);
+  if (threadIdx.x < RPB && e < NPAR) grad[e] = g;
+  if (blockIdx.x == 0 && threadIdx.x < 64 && loss) {
+    const float l = loss_sum(lpart, nb);
+    if (threadIdx.x == 0) loss[0] = l;
   }
 }
 
 // Adam on the summed partials; loss_acc[0] += batch loss.
-__global__ void k_mlp_adam(const float* __restrict__ gpart, const float* __restrict__ lpart, int nb,
-                           float* __restrict__ model, float* __restrict__ mom, float* __restrict__ vel, int step,
-                           float lr, float b1, float b2, float eps, float* __restrict__ loss_acc) {
-  const float c1 = 1.f - powf(b1, float(step)), c2 = 1.f - powf(b2, float(step));
-  for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < NPAR; e += gridDim.x * blockDim.x) {
-    float g = 0.f;
-    for (int b = 0; b < nb; ++b) g += gpart[int64_t(b) * NPAR + e];
+__global__ __launch_bounds__(RG * RPB) void k_mlp_adam(const float* __restrict__ gpart,
+                                                       const float* __restrict__ lpart, int nb,
+                                                       float* __restrict__ model, float* __restrict__ mom,
+                                                       float* __restrict__ vel, int step, float lr, float b1, float b2,
+                                                       float eps, float* __restrict__ loss_acc) {
+  __shared__ float red[RG][RPB];
+  const int e = blockIdx.x * RPB + threadIdx.x % RPB;
+  const float g = partial_sum(gpart, nb, e, red);
+  if (threadIdx.x < RPB && e < NPAR) {
+    const float c1 = 1.f - powf(b1, float(step)), c2 = 1.f - powf(b2, float(step));
     const float m = b1 * mom[e] + (1.f - b1) * g;
     const float v = b2 * vel[e] + (1.f - b2) * g * g;
     mom[e] = m;
     vel[e] = v;
     model[e] -= lr * (m / c1) / (sqrtf(v / c2) + eps);
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0 && loss_acc) {
-    float l = 0.f;
-    for (int b = 0; b < nb; ++b) l += lpart[b];
-    loss_acc[0] += l;
+  if (blockIdx.x == 0 && threadIdx.x < 64 && loss_acc) {
+    const float l = loss_sum(lpart, nb);
+    if (threadIdx.x == 0) loss_acc[0] += l;
   }
 }
 
@@ -611,15 +698,15 @@ void launch_mlp_forward(const float* m, const float* x, int64_t n, int clamp, fl
 int mlp_grad_blocks(int bsz) { return int(gridn(bsz, GCH, 1024)); }
 void launch_mlp_grad_partial(const float* m, const float* x, const float* t, int64_t n, int64_t off, int64_t stride,
                              int64_t b0, int bsz, float* gpart, float* lpart, hipStream_t s) {
-  hipLaunchKernelGGL(k_mlp_grad_partial, dim3(mlp_grad_blocks(bsz)), dim3(256), 0, s, m, x, t, n, off, stride, b0,
+  hipLaunchKernelGGL(k_mlp_grad_partial, dim3(mlp_grad_blocks(bsz)), dim3(GNT), 0, s, m, x, t, n, off, stride, b0,
                      bsz, gpart, lpart);
 }
 void launch_mlp_reduce(const float* gpart, const float* lpart, int nb, float* grad, float* loss, hipStream_t s) {
-  hipLaunchKernelGGL(k_mlp_reduce, dim3(gridn(NPAR, 256)), dim3(256), 0, s, gpart, lpart, nb, grad, loss);
+  hipLaunchKernelGGL(k_mlp_reduce, dim3(gridn(NPAR, RPB)), dim3(RG * RPB), 0, s, gpart, lpart, nb, grad, loss);
 }
 void launch_mlp_adam(const float* gpart, const float* lpart, int nb, float* m, float* mom, float* vel, int step,
                      float lr, float b1, float b2, float eps, float* loss_acc, hipStream_t s) {
-  hipLaunchKernelGGL(k_mlp_adam, dim3(gridn(NPAR, 256)), dim3(256), 0, s, gpart, lpart, nb, m, mom, vel, step, lr, b1,
+  hipLaunchKernelGGL(k_mlp_adam, dim3(gridn(NPAR, RPB)), dim3(RG * RPB), 0, s, gpart, lpart, nb, m, mom, vel, step, lr, b1,
                      b2, eps, loss_acc);
 }
 void launch_select(const float* pred, const float* feats, int64_t np, int norb, const float* model, double budget,
