@@ -142,7 +142,7 @@ void launch_trinv(const double* L, int n, double* X, hipStream_t s);
 // -A = L L^T and X = L^-1 (zeros above the diagonal); info zero on entry, set
 // as by launch_cholesky.  A holds L afterwards only where n > 128.
 void launch_chol_inv(double* A, int n, int* info, double* X, double* tinv, hipStream_t s);
-void launch_colnorm(const double* A, int n, int64_t ng, double* res, hipStream_t s);
+void launch_colnorm(const double* A, int n, int64_t ld, int64_t ng, double* res, hipStream_t s);
 int qrcp_blocks(int64_t ng);
 void launch_qrcp_update(const double* A, int n, int64_t ng, const double* q, double* res, double* pv, int64_t* pi,
                         const int* stop, hipStream_t s);
@@ -151,12 +151,12 @@ void launch_qrcp_update_r(double* R, int n, int P, const double* q, double* res,
                           const int* stop, hipStream_t s);
 void launch_qrcp_select_r(const double* R, int n, int P, int* kdev, const double* pv, const int64_t* pi,
                           double* Q, double* res, int32_t* piv, double* qout, const int32_t* pool,
-                          const double* t_out, int* stop, hipStream_t s);
+                          const double* t_out, int* stop, double* t_next, hipStream_t s);
 // Selection and update of one pool step in one launch (candidates read from
 // pv_in/pi_in, written to pv_out/pi_out; n <= 1024).
 void launch_qrcp_step_r(double* R, int n, int P, int* kdev, const double* pv_in, const int64_t* pi_in, double* Q,
                         double* res, int32_t* piv, const int32_t* pool, const double* t_out, int* stop,
-                        double* pv_out, int64_t* pi_out, hipStream_t s);
+                        double* pv_out, int64_t* pi_out, double* t_next, hipStream_t s);
 void launch_add_inplace(double* a, const double* b, int64_t cnt, hipStream_t s);
 void launch_qrcp_select(const double* A, int n, int64_t ng, int* kdev, const double* pv, const int64_t* pi,
                         int nblk, double* Q, double* res, int32_t* piv, double* qout, const int32_t* pool,
@@ -168,7 +168,11 @@ void launch_pool_write(const double* res, int64_t ng, const double* t, const int
                        double* pres, hipStream_t s);
 void launch_pool_gather(const double* A, int n, int64_t ng, const int32_t* pool, int np, double* Apool,
                         hipStream_t s);
-void launch_refresh_res(const double* L, int k, int64_t rc, const double* norm0, double* res, hipStream_t s);
+// Columns with res >= *t: their number (*total) and the offsets launch_pool_write
+// lists them by (pres may then be null).
+void launch_count_above(const double* res, int64_t ng, const double* t, int64_t* cnt, double* tmax, int* total,
+                        double* below, hipStream_t s);
+void launch_scatter_res(const int32_t* list, int64_t cnt, const double* v, double* res, hipStream_t s);
 void launch_retire(const int32_t* piv, int k, double* res, hipStream_t s);
 void launch_gather_cols(const double* A, int n, int64_t ng, const int32_t* piv, double* AC, hipStream_t s);
 void launch_scale_inf(double* X, const double* G, int n, hipStream_t s);

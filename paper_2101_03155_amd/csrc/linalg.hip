@@ -397,12 +397,13 @@ __global__ __launch_bounds__(64) void k_trinv_lower(const double* __restrict__ L
 }
 
 // ---------------------------------------------------------------- SCDM pivot search
-// Residual column norms res[r] = sum_i A[i][r]^2, A = psi [n][ng].
-__global__ void k_colnorm(const double* __restrict__ A, int n, int64_t ng, double* __restrict__ res) {
+// Residual column norms res[r] = sum_i A[i][r]^2 of ng columns, A = psi [n]
+// with pitch ld.
+__global__ void k_colnorm(const double* __restrict__ A, int n, int64_t ld, int64_t ng, double* __restrict__ res) {
   for (int64_t r = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; r < ng; r += int64_t(gridDim.x) * blockDim.x) {
     double s = 0.0;
     for (int i = 0; i < n; ++i) {
-      const double a = A[int64_t(i) * ng + r];
+      const double a = A[int64_t(i) * ld + r];
       s += a * a;
     }
     res[r] = s;
@@ -771,7 +772,10 @@ __global__ __launch_bounds__(NT) void k_qrcp_update_r(double* __restrict__ R, in
 // best live column; its norm is recomputed, certified against t_out (an upper
 // bound of every residual outside the pool), and q_k = R[:,b] / |R[:,b]| is
 // appended to Q.  A failed certification or an exhausted pool raises the
-// stop flag, after which the queued steps are no-ops.
+// stop flag, after which the queued steps are no-ops, and leaves in *t_next the
+// residual down to which the bounds are refreshed for the next pool: half the
+// best one of this pool (0 when it is exhausted).
+constexpr double REFRESH_BELOW = 0.5;
 template <int NT>
 __global__ __launch_bounds__(NT) void k_qrcp_select_r(const double* __restrict__ R, int n, int P,
                                                       int* __restrict__ kdev, const double* __restrict__ pv,
@@ -779,7 +783,8 @@ __global__ __launch_bounds__(NT) void k_qrcp_select_r(const double* __restrict__
                                                       double* __restrict__ Q, double* __restrict__ res,
                                                       int32_t* __restrict__ piv, double* __restrict__ qout,
                                                       const int32_t* __restrict__ pool,
-                                                      const double* __restrict__ t_out, int* __restrict__ stop) {
+                                                      const double* __restrict__ t_out, int* __restrict__ stop,
+                                                      double* __restrict__ t_next) {
   if (*stop) return;
   __shared__ double bv;
   __shared__ int64_t bi;
@@ -795,7 +800,10 @@ __global__ __launch_bounds__(NT) void k_qrcp_select_r(const double* __restrict__
   }
   const int64_t b = bi;
   if (b < 0 || b >= P) {
-    if (threadIdx.x == 0) *stop = 1;
+    if (threadIdx.x == 0) {
+      *stop = 1;
+      *t_next = 0.0;
+    }
     return;
   }
   double v = 0.0;
@@ -817,6 +825,7 @@ __global__ __launch_bounds__(NT) void k_qrcp_select_r(const double* __restrict__
       res[b] = -1.0;
     } else {
       *stop = 1;
+      *t_next = r2 > 0.0 ? REFRESH_BELOW * r2 : 0.0;
     }
   }
   __syncthreads();
@@ -849,7 +858,8 @@ __global__ __launch_bounds__(NT) void k_qrcp_step_r(double* __restrict__ R, int 
                                                     double* __restrict__ Q, double* __restrict__ res,
                                                     int32_t* __restrict__ piv, const int32_t* __restrict__ pool,
                                                     const double* __restrict__ t_out, int* __restrict__ stop,
-                                                    double* __restrict__ pv_out, int64_t* __restrict__ pi_out) {
+                                                    double* __restrict__ pv_out, int64_t* __restrict__ pi_out,
+                                                    double* __restrict__ t_next) {
   constexpr int RG = NT / CW;
   __shared__ double qs[1024];
   __shared__ double red[RG][CW];
@@ -879,7 +889,10 @@ __global__ __launch_bounds__(NT) void k_qrcp_step_r(double* __restrict__ R, int 
   }
   const int64_t b = bi;
   if (b < 0 || b >= P) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) *stop = 1;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      *stop = 1;
+      *t_next = 0.0;
+    }
     return;
   }
   {
@@ -896,7 +909,10 @@ __global__ __launch_bounds__(NT) void k_qrcp_step_r(double* __restrict__ R, int 
   for (int w = 0; w < NT / 64; ++w) r2 += r2s[w];
   const bool ok = r2 > 0.0 && (t_out == nullptr || r2 >= *t_out);
   if (!ok) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) *stop = 1;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      *stop = 1;
+      *t_next = r2 > 0.0 ? REFRESH_BELOW * r2 : 0.0;
+    }
     return;
   }
   const double inv = 1.0 / sqrt(r2);
@@ -1141,7 +1157,7 @@ __global__ __launch_bounds__(256) void k_pool_write(const double* __restrict__ r
     for (int w = 0; w < wv; ++w) o += wsum[w];
     if (keep) {
       pool[o + before] = int32_t(r);
-      pres[o + before] = v;
+      if (pres) pres[o + before] = v;
     }
     __syncthreads();
     if (threadIdx.x == 0) base += wsum[0] + wsum[1] + wsum[2] + wsum[3];
@@ -1159,18 +1175,11 @@ __global__ void k_pool_gather(const double* __restrict__ A, int n, int64_t ng, c
   }
 }
 
-// Residual bounds: res[r] = base[r] - sum_m L[m][r]^2 over the projections
-// L = Q A of a chunk of columns onto k directions (L is [k][rc]).  base may
-// be res itself (each element is read before it is written).
-__global__ void k_refresh_res(const double* __restrict__ L, int k, int64_t rc, const double* norm0, double* res) {
-  for (int64_t r = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; r < rc; r += int64_t(gridDim.x) * blockDim.x) {
-    double s = norm0[r];
-    for (int m = 0; m < k; ++m) {
-      const double l = L[int64_t(m) * rc + r];
-      s -= l * l;
-    }
-    res[r] = s;
-  }
+// res[list[p]] = v[p]
+__global__ void k_scatter_res(const int32_t* __restrict__ list, int64_t cnt, const double* __restrict__ v,
+                              double* __restrict__ res) {
+  for (int64_t p = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; p < cnt; p += int64_t(gridDim.x) * blockDim.x)
+    res[list[p]] = v[p];
 }
 
 __global__ void k_retire(const int32_t* __restrict__ piv, int k, double* __restrict__ res) {
@@ -1366,8 +1375,8 @@ void launch_chol_inv(double* A, int n, int* info, double* X, double* tinv, hipSt
     launch_trinv(A, n, X, s);
   }
 }
-void launch_colnorm(const double* A, int n, int64_t ng, double* res, hipStream_t s) {
-  hipLaunchKernelGGL(k_colnorm, dim3(grid_for(ng, 256)), dim3(256), 0, s, A, n, ng, res);
+void launch_colnorm(const double* A, int n, int64_t ld, int64_t ng, double* res, hipStream_t s) {
+  hipLaunchKernelGGL(k_colnorm, dim3(grid_for(ng, 256)), dim3(256), 0, s, A, n, ld, ng, res);
 }
 int qrcp_blocks(int64_t ng) { return grid_for(ng, 256, 2048); }
 void launch_qrcp_update(const double* A, int n, int64_t ng, const double* q, double* res, double* pv, int64_t* pi,
@@ -1388,17 +1397,18 @@ void launch_qrcp_update_r(double* R, int n, int P, const double* q, double* res,
 }
 void launch_qrcp_select_r(const double* R, int n, int P, int* kdev, const double* pv, const int64_t* pi,
                           double* Q, double* res, int32_t* piv, double* qout, const int32_t* pool,
-                          const double* t_out, int* stop, hipStream_t s) {
+                          const double* t_out, int* stop, double* t_next, hipStream_t s) {
   hipLaunchKernelGGL(k_qrcp_select_r<256>, dim3(1), dim3(256), 0, s, R, n, P, kdev, pv, pi, qrcp_pool_blocks(P), Q,
-                     res, piv, qout, pool, t_out, stop);
+                     res, piv, qout, pool, t_out, stop, t_next);
 }
 void launch_qrcp_step_r(double* R, int n, int P, int* kdev, const double* pv_in, const int64_t* pi_in, double* Q,
                         double* res, int32_t* piv, const int32_t* pool, const double* t_out, int* stop,
-                        double* pv_out, int64_t* pi_out, hipStream_t s) {
+                        double* pv_out, int64_t* pi_out, double* t_next, hipStream_t s) {
   // rows per thread of the block's tile: n / (256 / QCW), held in registers
 #define QSTEP(MPV)                                                                                                 \
   hipLaunchKernelGGL((k_qrcp_step_r<256, QCW, MPV>), dim3(qrcp_pool_blocks(P)), dim3(256), 0, s, R, n, P, kdev,   \
-                     pv_in, pi_in, qrcp_pool_blocks(P), Q, res, piv, pool, t_out, stop, pv_out, pi_out)
+                     pv_in, pi_in, qrcp_pool_blocks(P), Q, res, piv, pool, t_out, stop, pv_out, pi_out, \
+                     t_next)
   constexpr int RG = 256 / QCW;
   if (n <= 8 * RG) QSTEP(8);
   else if (n <= 16 * RG) QSTEP(16);
@@ -1414,10 +1424,7 @@ void launch_pool_build(const double* res, int64_t ng, int pmax, unsigned* hist, 
                        double* tmax, int* total, double* t_out, hipStream_t s) {
   hipLaunchKernelGGL(k_res_hist, dim3(grid_for(ng, 256, 1024)), dim3(256), 0, s, res, ng, hist);
   hipLaunchKernelGGL(k_pool_threshold, dim3(1), dim3(1024), 0, s, hist, pmax, t);
-  const int nb = pool_blocks(ng);
-  const int64_t chunk = (ng + nb - 1) / nb;
-  hipLaunchKernelGGL(k_pool_count, dim3(nb), dim3(256), 0, s, res, ng, chunk, t, cnt, tmax);
-  hipLaunchKernelGGL(k_pool_scan, dim3(1), dim3(1024), 0, s, cnt, tmax, nb, total, t_out);
+  launch_count_above(res, ng, t, cnt, tmax, total, t_out, s);
 }
 void launch_pool_write(const double* res, int64_t ng, const double* t, const int64_t* off, int32_t* pool,
                        double* pres, hipStream_t s) {
@@ -1430,8 +1437,15 @@ void launch_pool_gather(const double* A, int n, int64_t ng, const int32_t* pool,
   hipLaunchKernelGGL(k_pool_gather, dim3(grid_for(int64_t(n) * np, 256)), dim3(256), 0, s, A, n, ng, pool, np,
                      Apool);
 }
-void launch_refresh_res(const double* L, int k, int64_t rc, const double* norm0, double* res, hipStream_t s) {
-  hipLaunchKernelGGL(k_refresh_res, dim3(grid_for(rc, 256)), dim3(256), 0, s, L, k, rc, norm0, res);
+void launch_count_above(const double* res, int64_t ng, const double* t, int64_t* cnt, double* tmax, int* total,
+                        double* below, hipStream_t s) {
+  const int nb = pool_blocks(ng);
+  const int64_t chunk = (ng + nb - 1) / nb;
+  hipLaunchKernelGGL(k_pool_count, dim3(nb), dim3(256), 0, s, res, ng, chunk, t, cnt, tmax);
+  hipLaunchKernelGGL(k_pool_scan, dim3(1), dim3(1024), 0, s, cnt, tmax, nb, total, below);
+}
+void launch_scatter_res(const int32_t* list, int64_t cnt, const double* v, double* res, hipStream_t s) {
+  hipLaunchKernelGGL(k_scatter_res, dim3(grid_for(cnt, 256)), dim3(256), 0, s, list, cnt, v, res);
 }
 void launch_retire(const int32_t* piv, int k, double* res, hipStream_t s) {
   if (k > 0) hipLaunchKernelGGL(k_retire, dim3((k + 255) / 256), dim3(256), 0, s, piv, k, res);
