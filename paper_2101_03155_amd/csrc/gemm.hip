@@ -16,6 +16,7 @@
 // element r of lane l is D[l/16 + 4r][l%16] for the FP64 instruction and
 // D[4(l/16) + r][l%16] for the FP32 one (checked on gfx950 by a lane probe).
 #include <hip/hip_runtime.h>
+#include <algorithm>
 #include <cstdint>
 #include <type_traits>
 #include "ace_internal.h"
@@ -768,12 +769,199 @@ hipError_t gemm_nt(int prec, int op, const void* A, int64_t lda, const void* B, 
   return hipGetLastError();
 }
 
+// ---------------------------------------------------------------- streaming left-small product
+// C[m][r] = alpha * sum_k S(m, k) B[k][r] for small K.  S stays in registers:
+// wave w of a workgroup holds the MFMA operands of its RW 16-row blocks over
+// all of K, loaded once, and the workgroup runs through column tiles of NC,
+// every ns-th one.  A tile of B (K x NC) sits in LDS, double buffered; the
+// next one is loaded to registers while the current one is multiplied, and a
+// tile ends with one barrier.  (Tiles of 64 x 64 or 128 x 128 with both
+// operands staged per step of K start and end every tile with an idle memory
+// pipe.)  Bound by memory up to 64 rows, by the MFMAs and the waits of its
+// loads and stores beyond (at 128 x 128 a wave spends 60% of a tile in its
+// MFMAs, 30% in the issue of the tile's 16 loads and 16 stores; dealing these
+// out between the MFMAs spilled registers and was slower).  Before and after:
+// 64 x 64 on 160^3 1.84 -> 0.87 ms (4.8 TB/s), 40 x 40 on 64^3 67 -> 43 us,
+// 128 x 128 on 96^3 0.75 -> 0.69 ms, triangular 0.545 -> 0.414 ms, the same
+// with FP32 B 0.658 -> 0.402 ms, 256 x 256 on 120^3 4.44 -> 4.16 ms.
+// The two rows of k that a half-wave reads are moved to opposite halves of the
+// banks by swapping 16-column blocks on every second row (pair of rows in FP32).
+// LOWER: S(m, k) = 0 for k > m.  The row blocks are dealt so that the waves
+// of a SIMD share the work, and a row block's MFMAs stop at its last row.
+struct LsSplit {
+  int rows;      // rows per row block of workgroups
+  int first[5];  // workgroups first[b] .. first[b + 1] - 1 take row block b
+};
+
+template <int RW, int NWV>
+__device__ __forceinline__ int ls_rowblk(int w, int i) {
+  return RW == 2 ? (i == 0 ? w : 2 * NWV - 1 - w) : w < NWV / 2 ? w : NWV + NWV / 2 - 1 - w;
+}
+
+template <typename TB, int RW, int NWV, int KMAX, int NC, bool TRANS, bool LOWER>
+__global__ __launch_bounds__(64 * NWV, 2) void k_ls_stream(const double* __restrict__ S, int lds,
+                                                           const TB* __restrict__ B, int64_t ldb,
+                                                           double* __restrict__ C, int64_t ldc, int M, int K,
+                                                           int64_t R, double alpha, LsSplit sp) {
+  constexpr int NT = 64 * NWV, PER = KMAX * NC / NT, JB = NC / 16, KSTEPS = KMAX / 4, KR = NT / NC;
+  static_assert(NT % NC == 0 && KMAX % KR == 0 && NC % 16 == 0, "tile shape");
+  __shared__ TB Bs[2][KMAX * NC];
+  const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, q = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int rb = 0;
+  while (int(blockIdx.x) >= sp.first[rb + 1]) ++rb;
+  const int m0 = rb * sp.rows;
+  const int64_t ns = sp.first[rb + 1] - sp.first[rb], ntile = (R + NC - 1) / NC;
+  const int kt = LOWER && m0 + sp.rows < K ? m0 + sp.rows : K;  // rows of B this row block reads
+  double a[RW][KSTEPS];
+  int kend[RW];
+#pragma unroll
+  for (int i = 0; i < RW; ++i) {
+    const int b0 = m0 + 16 * ls_rowblk<RW, NWV>(w, i), m = b0 + li;
+    kend[i] = b0 >= M ? 0 : LOWER && b0 + 16 < K ? b0 + 16 : K;
+#pragma unroll
+    for (int t = 0; t < KSTEPS; ++t) {
+      const int k = 4 * t + q;
+      a[i][t] = 0.0;
+      if (m < M && k < kt && (!LOWER || k <= m)) a[i][t] = TRANS ? S[int64_t(k) * lds + m] : S[int64_t(m) * lds + k];
+    }
+  }
+  const int kmax = RW == 2 && kend[RW - 1] > kend[0] ? kend[RW - 1] : kend[0];
+  // this thread's column of a tile and its first row of k (rows kr + KR u)
+  const int kr = tid / NC, nc = tid % NC;
+  TB vb[PER];
+  auto load = [&](int64_t tile) {
+    const int64_t c = tile * NC + nc;
+    const TB* p = B + c + int64_t(kr) * ldb;
+    if (kt == KMAX && tile * NC + NC <= R) {
+#pragma unroll
+      for (int u = 0; u < PER; ++u, p += int64_t(KR) * ldb) vb[u] = *p;
+    } else {
+      int k = kr;  // opaque: the bounds are not kept in registers from tile to tile
+      asm volatile("" : "+v"(k));
+#pragma unroll
+      for (int u = 0; u < PER; ++u) {
+        vb[u] = TB(0);
+        if (c < R && k + KR * u < kt) vb[u] = p[int64_t(KR * u) * ldb];
+      }
+    }
+  };
+  auto swap16 = [](int k) { return NC == 16 ? 0 : (sizeof(TB) == 8 ? k & 1 : (k >> 1) & 1) << 4; };
+  auto store = [&](TB* dst) {
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+      const int k = kr + KR * u;
+      dst[k * NC + (nc ^ swap16(k))] = vb[u];
+    }
+  };
+  int64_t tile = int(blockIdx.x) - sp.first[rb];
+  if (tile >= ntile) return;
+  load(tile);
+  store(Bs[0]);
+  __syncthreads();
+  int buf = 0;
+  for (;;) {
+    const int64_t next = tile + ns;
+    if (next < ntile) load(next);
+    // column 16 j + li of row 4 t + q, its bit 4 flipped where the row is swapped
+    const TB* bl = Bs[buf] + q * NC + li;
+    const int sw = swap16(q);
+    d4 acc[RW][JB];
+#pragma unroll
+    for (int i = 0; i < RW; ++i)
+#pragma unroll
+      for (int j = 0; j < JB; ++j) acc[i][j] = d4{0, 0, 0, 0};
+#pragma unroll
+    for (int g = 0; g < KSTEPS; g += 4) {
+      if (4 * g < kmax) {  // (uniform over the wave)
+#pragma unroll
+        for (int t = g; t < g + 4; ++t) {
+          double b[JB];
+#pragma unroll
+          for (int j = 0; j < JB; ++j) b[j] = double(bl[4 * t * NC + ((16 * j) ^ sw)]);
+#pragma unroll
+          for (int i = 0; i < RW; ++i)
+            if (!LOWER || RW == 1 || 4 * g < kend[i]) {
+#pragma unroll
+              for (int j = 0; j < JB; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i][t], b[j], acc[i][j], 0, 0, 0);
+            }
+        }
+      }
+    }
+    // the next tile goes to LDS before the stores of C are issued: a wait for
+    // its loads after them would wait for the stores too
+    buf ^= 1;
+    if (next < ntile) store(Bs[buf]);
+    const int64_t c0 = tile * NC;
+#pragma unroll
+    for (int i = 0; i < RW; ++i) {
+      const int b0 = m0 + 16 * ls_rowblk<RW, NWV>(w, i);
+      double* cp = C + int64_t(b0 + q) * ldc + c0 + li;
+      if (b0 + 16 <= M && c0 + NC <= R) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int j = 0; j < JB; ++j) cp[int64_t(4 * r) * ldc + 16 * j] = alpha * acc[i][j][r];
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int j = 0; j < JB; ++j)
+            if (b0 + q + 4 * r < M && c0 + 16 * j + li < R) cp[int64_t(4 * r) * ldc + 16 * j] = alpha * acc[i][j][r];
+      }
+    }
+    if (next >= ntile) break;
+    __syncthreads();
+    tile = next;
+  }
+}
+
+// Row blocks and the workgroups of each, two per CU in all: shares follow the
+// work (with LOWER the later row blocks have more).
+template <typename TB, int RW, int NWV, int KMAX, int NC, bool TRANS, bool LOWER>
+static void launch_stream(const double* S, int lds, const TB* B, int64_t ldb, double* C, int64_t ldc, int M, int K,
+                          int64_t R, double alpha, hipStream_t s) {
+  LsSplit sp;
+  sp.rows = 16 * RW * NWV;
+  const int nrb = (M + sp.rows - 1) / sp.rows;
+  const int64_t ntile = (R + NC - 1) / NC;
+  const int total = int(std::min<int64_t>(512, ntile * nrb));
+  double w[4], sum = 0.0;
+  for (int b = 0; b < nrb; ++b) {
+    const int lo = b * sp.rows, hi = std::min(M, lo + sp.rows);
+    w[b] = LOWER ? 0.5 * (double(hi) * hi - double(lo) * lo) : double(hi - lo);
+    sum += w[b];
+  }
+  sp.first[0] = 0;
+  double acc = 0.0;
+  for (int b = 0; b < nrb; ++b) {
+    acc += w[b];
+    const int end = b + 1 == nrb ? total : int(total * acc / sum + 0.5);
+    sp.first[b + 1] = std::max(end, sp.first[b] + 1);
+  }
+  for (int b = nrb; b < 4; ++b) sp.first[b + 1] = sp.first[b];
+  hipLaunchKernelGGL((k_ls_stream<TB, RW, NWV, KMAX, NC, TRANS, LOWER>), dim3(unsigned(sp.first[nrb])), dim3(64 * NWV),
+                     0, s, S, lds, B, ldb, C, ldc, M, K, R, alpha, sp);
+}
+
 template <typename TB, bool TRANS, bool LOWER>
 static void launch_ls(const double* S, int lds, const TB* B, int64_t ldb, double* C, int64_t ldc, int M, int K,
                       int64_t R, double alpha, hipStream_t s) {
   if (R <= 1024) {
     dim3 grid(unsigned((R + 15) / 16), unsigned((M + 15) / 16));
     hipLaunchKernelGGL((k_gemm_tiny<TB, TRANS, LOWER>), grid, dim3(64), 0, s, S, lds, B, ldb, C, ldc, M, K, R, alpha);
+  } else if (K <= 64 && M <= 64) {
+    launch_stream<TB, 1, 4, 64, 64, TRANS, LOWER>(S, lds, B, ldb, C, ldc, M, K, R, alpha, s);
+  } else if (K <= 128 && M <= 64) {
+    launch_stream<TB, 1, 4, 128, 32, TRANS, LOWER>(S, lds, B, ldb, C, ldc, M, K, R, alpha, s);
+  } else if (K <= 128 && M <= 512) {
+    launch_stream<TB, 2, 4, 128, 32, TRANS, LOWER>(S, lds, B, ldb, C, ldc, M, K, R, alpha, s);
+  } else if (!LOWER && std::is_same<TB, double>::value && K > 192 && K <= 256 && M > 192 && M <= 256) {
+    // longer K leaves registers for one row block per wave, so B is read by
+    // four row blocks: worth it where K and M fill the 256 (200 x 120 and the
+    // triangular 256 x 256 product are faster on the 128 x 128 tiles)
+    launch_stream<TB, 1, 4, 256, 16, TRANS, false>(S, lds, B, ldb, C, ldc, M, K, R, alpha, s);
   } else if (M > 64) {
     dim3 grid(unsigned((R + TT - 1) / TT), unsigned((M + TT - 1) / TT));
     // FP32 right operands run 8 waves per tile; with FP64 ones the 512-thread
