@@ -1953,13 +1953,9 @@ static int features_impl(ace_ctx* c, const ace_grid* g, int norb, const double* 
   const int m = n / stride;
   const int64_t ngs = int64_t(m) * m * m;
   const double dVs = grid_dv(g) * double(stride) * stride * stride;
-  const double* phis = phi;
-  if (stride > 1) {
-    double* sub;
-    WS(c, "f_sub", size_t(norb) * ngs * sizeof(double), sub);
-    launch_subsample(phi, norb, n, stride, sub, s);
-    phis = sub;
-  }
+  double* sub = nullptr;
+  if (stride > 1) WS(c, "f_sub", size_t(norb) * ngs * sizeof(double), sub);
+  const double* phis = sub ? sub : phi;
   int64_t kchunk;
   const int64_t nsplit = gemm_nt_nsplit(norb, norb, ngs, &kchunk);
   WS(c, "f_pz", size_t(norb) * n * sizeof(double), pz);
@@ -1970,7 +1966,7 @@ static int features_impl(ace_ctx* c, const ace_grid* g, int norb, const double* 
   WS(c, "O", size_t(norb) * norb * sizeof(double), O);
   WS(c, "f_P", size_t(norb) * norb * sizeof(double), P);
   WS(c, "mpart", size_t(nsplit) * norb * norb * sizeof(double), part);
-  launch_marginals(phi, norb, n, pz, py, px, s);
+  launch_marginals(phi, norb, n, stride, pz, py, px, sub, s);
   launch_centroids(pz, py, px, norb, n, g->L[0], grid_dv(g), cen, spr, s);
   HIPCHK(c, gemm_nt(0, 1, phis, ngs, phis, ngs, norb, norb, ngs, dVs, part, O, s, nullptr, true));
   HIPCHK(c, gemm_nt(0, 2, phis, ngs, phis, ngs, norb, norb, ngs, dVs, part, P, s, nullptr, true));

@@ -7,6 +7,7 @@
 #include <hip/hip_runtime.h>
 #include <cstdint>
 #include "ace_internal.h"
+#include "tri_pairs.h"
 
 namespace ace {
 
@@ -1246,52 +1247,19 @@ __global__ void k_dev_identity(const double* __restrict__ G, int n, double* __re
 // ---------------------------------------------------------------- screening
 // Upper-triangle entries (i <= j) with O_ij >= rho_cut, or i == j, in
 // row-major order; writes at most cap pairs and the full count to *count.
-__global__ __launch_bounds__(1024) void k_compact_pairs(const double* __restrict__ O, int n, double rho_cut,
-                                                        int64_t cap, int32_t* __restrict__ pairs,
-                                                        double* __restrict__ ov, int64_t* __restrict__ count) {
-  __shared__ int64_t wsum[16];
-  __shared__ int64_t base;
-  if (threadIdx.x == 0) base = 0;
-  __syncthreads();
-  const int64_t tot = int64_t(n) * (n + 1) / 2;
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  for (int64_t c0 = 0; c0 < tot; c0 += blockDim.x) {
-    const int64_t t = c0 + threadIdx.x;
-    int i = 0, j = 0;
-    bool keep = false;
-    if (t < tot) {
-      // t -> (i, j), i <= j, row-major over the upper triangle
-      // row i starts at i*n - i*(i-1)/2
-      double a = 2.0 * n + 1.0;
-      i = int((a - sqrt(a * a - 8.0 * double(t))) * 0.5);
-      while (i > 0 && int64_t(i) * n - int64_t(i) * (i - 1) / 2 > t) --i;
-      while (int64_t(i + 1) * n - int64_t(i + 1) * i / 2 <= t) ++i;
-      j = i + int(t - (int64_t(i) * n - int64_t(i) * (i - 1) / 2));
-      keep = (i == j) || (O[int64_t(i) * n + j] >= rho_cut);
-    }
-    const unsigned long long m = __ballot(keep);
-    const int before = __popcll(m & ((1ull << lane) - 1ull));
-    if (lane == 0) wsum[wv] = __popcll(m);
-    __syncthreads();
-    int64_t off = base;
-    for (int w = 0; w < wv; ++w) off += wsum[w];
-    if (keep) {
-      const int64_t p = off + before;
-      if (p < cap) {
-        pairs[2 * p] = i;
-        pairs[2 * p + 1] = j;
-        if (ov) ov[p] = O[int64_t(i) * n + j];
-      }
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      int64_t s = 0;
-      for (int w = 0; w < int(blockDim.x / 64); ++w) s += wsum[w];
-      base += s;
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) count[0] = base;
+__global__ __launch_bounds__(CNT) void k_compact_pairs(const double* __restrict__ O, int n, double rho_cut,
+                                                       int64_t cap, int32_t* __restrict__ pairs,
+                                                       double* __restrict__ ov, int64_t* __restrict__ count) {
+  compact_tri(
+      n, [&](int64_t, int i, int j) { return i == j || O[int64_t(i) * n + j] >= rho_cut; },
+      [&](int64_t p, int i, int j) {
+        if (p < cap) {
+          pairs[2 * p] = i;
+          pairs[2 * p + 1] = j;
+          if (ov) ov[p] = O[int64_t(i) * n + j];
+        }
+      },
+      count);
 }
 
 // ---------------------------------------------------------------- pair energies
@@ -1464,7 +1432,7 @@ void launch_dev_identity(const double* G, int n, double* out, hipStream_t s) {
 }
 void launch_compact_pairs(const double* O, int n, double rho_cut, int64_t cap, int32_t* pairs, double* ov,
                           int64_t* count, hipStream_t s) {
-  hipLaunchKernelGGL(k_compact_pairs, dim3(1), dim3(1024), 0, s, O, n, rho_cut, cap, pairs, ov, count);
+  hipLaunchKernelGGL(k_compact_pairs, dim3(1), dim3(CNT), 0, s, O, n, rho_cut, cap, pairs, ov, count);
 }
 void launch_pair_energy(const double* epart, int npacks, int nblk, const Pack* packs, const int64_t* pidx, double dV,
                         double* e, hipStream_t s) {

@@ -22,6 +22,7 @@
 #include <cstdint>
 
 #include "ace_internal.h"
+#include "tri_pairs.h"
 
 namespace ace {
 
@@ -35,34 +36,67 @@ static_assert(NMODEL == 4631, "model size");
 
 // ---------------------------------------------------------------- orbital moments
 // Per (orbital, z-plane): the plane's total |phi|^2 and its row (y) and column
-// (x) sums; pz[orb][z], py[orb][z][y], px[orb][z][x].
-__global__ __launch_bounds__(256) void k_plane_marginals(const double* __restrict__ phi, int n, double* __restrict__ pz,
-                                                         double* __restrict__ py, double* __restrict__ px) {
-  // one read of the plane: wave w takes rows y = w, w + 4, ...; lanes read the
-  // row coalesced, its sum comes from a shuffle reduction, and each lane keeps
-  // its columns' partial sums, combined over the waves in LDS at the end
-  constexpr int CPL = 4;  // columns per lane (n <= 256)
+// (x) sums; pz[orb][z], py[orb][z][y], px[orb][z][x].  With sub also the grid
+// subsampled by the stride st per axis, sub[orb][zs][ys][xs] = phi[orb][st zs]
+// [st ys][st xs], from the same read.  Bound by that read: 256 orbitals on
+// 120^3 (3.5 GB, 0.44 GB written) take 0.92 ms; one row at a time in flight
+// and a second kernel for the subsampling took 0.87 + 0.27 ms.
+template <int CPL>  // columns per lane, n <= 64 CPL
+__global__ __launch_bounds__(256) void k_plane_marginals(const double* __restrict__ phi, int n, int st,
+                                                         double* __restrict__ pz, double* __restrict__ py,
+                                                         double* __restrict__ px, double* __restrict__ sub) {
+  // wave w takes rows y = w, w + 4, ..., RU of them at a time; lanes read a row
+  // coalesced, its sum comes from a shuffle reduction, and each lane keeps its
+  // columns' partial sums, combined over the waves in LDS at the end
+  constexpr int RU = 4;
   const int z = blockIdx.x, orb = blockIdx.y, tid = threadIdx.x;
   const int lane = tid & 63, wv = tid >> 6;
   const int64_t ng = int64_t(n) * n * n;
   const double* P = phi + int64_t(orb) * ng + int64_t(z) * n * n;
-  __shared__ double col[4][256];
+  const int m = n / st;
+  const bool sz = sub && z % st == 0;
+  double* Sp = sz ? sub + (int64_t(orb) * m + z / st) * m * m : nullptr;
+  __shared__ double col[4][64 * CPL];
   double cs[CPL];
 #pragma unroll
   for (int c = 0; c < CPL; ++c) cs[c] = 0.0;
-  for (int y = wv; y < n; y += 4) {
-    double rs = 0.0;
+  for (int y0 = wv; y0 < n; y0 += 4 * RU) {
+    double v[RU][CPL], rs[RU];
 #pragma unroll
-    for (int c = 0; c < CPL; ++c) {
-      const int x = lane + 64 * c;
-      if (x < n) {
-        const double v = P[y * n + x];
-        cs[c] += v * v;
-        rs += v * v;
+    for (int u = 0; u < RU; ++u)
+#pragma unroll
+      for (int c = 0; c < CPL; ++c) {
+        const int x = lane + 64 * c, y = y0 + 4 * u;
+        v[u][c] = (x < n && y < n) ? P[y * n + x] : 0.0;
+      }
+#pragma unroll
+    for (int u = 0; u < RU; ++u) {
+      rs[u] = 0.0;
+#pragma unroll
+      for (int c = 0; c < CPL; ++c) {
+        cs[c] += v[u][c] * v[u][c];
+        rs[u] += v[u][c] * v[u][c];
       }
     }
-    for (int off = 32; off > 0; off >>= 1) rs += __shfl_down(rs, off, 64);
-    if (lane == 0) py[(int64_t(orb) * n + z) * n + y] = rs;
+    if (sz) {
+#pragma unroll
+      for (int u = 0; u < RU; ++u) {
+        const int y = y0 + 4 * u;
+        if (y >= n || y % st != 0) continue;
+#pragma unroll
+        for (int c = 0; c < CPL; ++c) {
+          const int x = lane + 64 * c;
+          if (x < n && x % st == 0) Sp[(y / st) * m + x / st] = v[u][c];
+        }
+      }
+    }
+    for (int off = 32; off > 0; off >>= 1)
+#pragma unroll
+      for (int u = 0; u < RU; ++u) rs[u] += __shfl_down(rs[u], off, 64);
+    if (lane == 0)
+#pragma unroll
+      for (int u = 0; u < RU; ++u)
+        if (y0 + 4 * u < n) py[(int64_t(orb) * n + z) * n + y0 + 4 * u] = rs[u];
   }
 #pragma unroll
   for (int c = 0; c < CPL; ++c) col[wv][lane + 64 * c] = cs[c];
@@ -80,75 +114,62 @@ __global__ __launch_bounds__(256) void k_plane_marginals(const double* __restric
   if (tid == 0) pz[int64_t(orb) * n + z] = col[0][0] + col[0][1] + col[0][2] + col[0][3];
 }
 
-// out[orb][zs][ys][xs] = phi[orb][s zs][s ys][s xs]: the grid subsampled by
-// the stride s per axis (m = n / s points per axis).
-__global__ void k_subsample(const double* __restrict__ phi, int norb, int n, int st, double* __restrict__ out) {
-  const int m = n / st;
-  const int64_t tot = int64_t(norb) * m * m * m;
-  for (int64_t e = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; e < tot; e += int64_t(gridDim.x) * blockDim.x) {
-    const int xs = int(e % m);
-    int64_t r = e / m;
-    const int ys = int(r % m);
-    r /= m;
-    const int zs = int(r % m);
-    const int64_t orb = r / m;
-    out[e] = phi[((orb * n + int64_t(zs) * st) * n + int64_t(ys) * st) * n + int64_t(xs) * st];
-  }
-}
-
 // Per orbital: marginals along each axis, periodic centroid (argument of the
 // first Fourier coefficient of the marginal) and spread with minimum-image
-// displacements.  cen[orb][3] (x, y, z), spr[orb].
-__global__ __launch_bounds__(256) void k_centroids(const double* __restrict__ pz, const double* __restrict__ py,
-                                                   const double* __restrict__ px, int n, double L, double dV,
-                                                   double* __restrict__ cen, double* __restrict__ spr) {
-  const int orb = blockIdx.x, tid = threadIdx.x;
-  __shared__ double m[3][512];
-  __shared__ double c3[3];
-  for (int a = tid; a < n; a += 256) {
-    double sx = 0.0, sy = 0.0;
-    for (int z = 0; z < n; ++z) {
+// displacements.  cen[orb][3] (x, y, z), spr[orb].  One workgroup per orbital,
+// so a chain of latencies: the sums over planes run in four groups, then wave
+// w takes axis w (one thread per axis and 120 planes in turn took 145 us at
+// 120^3, now 17).
+__global__ __launch_bounds__(1024) void k_centroids(const double* __restrict__ pz, const double* __restrict__ py,
+                                                    const double* __restrict__ px, int n, double L, double dV,
+                                                    double* __restrict__ cen, double* __restrict__ spr) {
+  const int orb = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  __shared__ double m[3][256], part[2][4][256];
+  __shared__ double s3[3];
+  const int a = tid & 255, g = tid >> 8;
+  double sx = 0.0, sy = 0.0;
+  if (a < n) {
+#pragma unroll 8
+    for (int z = g; z < n; z += 4) {
       sx += px[(int64_t(orb) * n + z) * n + a];
       sy += py[(int64_t(orb) * n + z) * n + a];
     }
-    m[0][a] = sx;
-    m[1][a] = sy;
-    m[2][a] = pz[int64_t(orb) * n + a];
   }
+  part[0][g][a] = sx;
+  part[1][g][a] = sy;
+  __syncthreads();
+  if (g < 2) m[g][a] = (part[g][0][a] + part[g][1][a]) + (part[g][2][a] + part[g][3][a]);
+  else if (g == 2) m[2][a] = a < n ? pz[int64_t(orb) * n + a] : 0.0;
   __syncthreads();
   const double two_pi = 6.283185307179586476925286766559005768;
-  if (tid < 3) {
+  if (wv < 3) {
     double cs = 0.0, sn = 0.0;
-    for (int a = 0; a < n; ++a) {
-      const double ang = two_pi * double(a) / double(n);
-      cs += m[tid][a] * cos(ang);
-      sn += m[tid][a] * sin(ang);
+    for (int i = lane; i < n; i += 64) {
+      double s, c;
+      sincos(two_pi * double(i) / double(n), &s, &c);
+      cs += m[wv][i] * c;
+      sn += m[wv][i] * s;
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+      cs += __shfl_xor(cs, off, 64);
+      sn += __shfl_xor(sn, off, 64);
     }
     double c = atan2(sn, cs) * L / two_pi;
     c = c - L * floor(c / L);
-    c3[tid] = c;
-    cen[orb * 3 + tid] = c;
+    double s2 = 0.0;
+    for (int i = lane; i < n; i += 64) {
+      double d = double(i) * L / double(n) - c;
+      d -= L * rint(d / L);
+      s2 += m[wv][i] * d * d;
+    }
+    for (int off = 32; off > 0; off >>= 1) s2 += __shfl_down(s2, off, 64);
+    if (lane == 0) {
+      cen[orb * 3 + wv] = c;
+      s3[wv] = s2;
+    }
   }
   __syncthreads();
-  if (tid == 0) {
-    double s2 = 0.0;
-    for (int ax = 0; ax < 3; ++ax)
-      for (int a = 0; a < n; ++a) {
-        double d = double(a) * L / double(n) - c3[ax];
-        d -= L * rint(d / L);
-        s2 += m[ax][a] * d * d;
-      }
-    spr[orb] = sqrt(s2 * dV);
-  }
-}
-
-// Pair t -> (i, j), i <= j, row-major over the upper triangle.
-__device__ __forceinline__ void tri_ij(int64_t t, int n, int& i, int& j) {
-  const double a = 2.0 * n + 1.0;
-  i = int((a - sqrt(a * a - 8.0 * double(t))) * 0.5);
-  while (i > 0 && int64_t(i) * n - int64_t(i) * (i - 1) / 2 > t) --i;
-  while (int64_t(i + 1) * n - int64_t(i + 1) * i / 2 <= t) ++i;
-  j = i + int(t - (int64_t(i) * n - int64_t(i) * (i - 1) / 2));
+  if (tid == 0) spr[orb] = sqrt((s3[0] + s3[1] + s3[2]) * dV);
 }
 
 // Features of listed pairs (pairs != nullptr) or of every pair i <= j.
@@ -251,35 +272,54 @@ __global__ void k_stats_final(const double* __restrict__ part, int nb, int64_t n
 }
 
 // Prediction (de-standardized target, log10 |e|) of every sample; with clamp
-// the features are first clipped to the training ranges.
+// the features are first clipped to the training ranges.  Four waves share 64
+// samples, one per lane: wave w has hidden units 16 w ... 16 w + 15 of both
+// layers, which pass through LDS (a chain of 64 dependent operations per unit:
+// all units in one lane took 44 us at 32896 samples, now 23).  The sums of a
+// unit and of the output run in the order of their indices.
+constexpr int FP = 65;
 __global__ __launch_bounds__(256) void k_mlp_forward(const float* __restrict__ model, const float* __restrict__ x,
                                                      int64_t n, int clamp, float* __restrict__ y) {
   __shared__ float w[NMODEL];
+  __shared__ float h[64 * FP];
   for (int e = threadIdx.x; e < NMODEL; e += 256) w[e] = model[e];
-  __syncthreads();
-  for (int64_t s = blockIdx.x * int64_t(256) + threadIdx.x; s < n; s += int64_t(gridDim.x) * 256) {
+  const int lane = threadIdx.x & 63, u0 = (threadIdx.x >> 6) * 16;
+  float* hl = h + lane * FP;
+  for (int64_t s0 = blockIdx.x * int64_t(64); s0 < n; s0 += int64_t(gridDim.x) * 64) {
+    const int64_t s = s0 + lane < n ? s0 + lane : n - 1;
+    __syncthreads();
     float xs[NIN];
     for (int k = 0; k < NIN; ++k) {
       float v = x[s * NIN + k];
       if (clamp) v = fminf(fmaxf(v, w[OXMIN + k]), w[OXMAX + k]);
       xs[k] = (v - w[OXM + k]) / w[OXS + k];
     }
-    float h1[NH];
 #pragma unroll
-    for (int j = 0; j < NH; ++j) {
+    for (int j = u0; j < u0 + 16; ++j) {
       float a = w[OB1 + j];
 #pragma unroll
       for (int k = 0; k < NIN; ++k) a += w[OW1 + j * NIN + k] * xs[k];
-      h1[j] = tanhf(a);
+      hl[j] = tanhf(a);
     }
-    float out = w[OB3];
-    for (int j = 0; j < NH; ++j) {
+    __syncthreads();
+    float h1[NH];
+#pragma unroll
+    for (int k = 0; k < NH; ++k) h1[k] = hl[k];
+    __syncthreads();
+#pragma unroll 4
+    for (int j = u0; j < u0 + 16; ++j) {
       float a = w[OB2 + j];
 #pragma unroll
       for (int k = 0; k < NH; ++k) a += w[OW2 + j * NH + k] * h1[k];
-      out += w[OW3 + j] * tanhf(a);
+      hl[j] = tanhf(a);
     }
-    y[s] = w[OTM] + w[OTS] * out;
+    __syncthreads();
+    if (u0 == 0 && s0 + lane < n) {
+      float out = w[OB3];
+#pragma unroll
+      for (int j = 0; j < NH; ++j) out += w[OW3 + j] * hl[j];
+      y[s] = w[OTM] + w[OTS] * out;
+    }
   }
 }
 
@@ -526,12 +566,18 @@ __global__ __launch_bounds__(RG * RPB) void k_mlp_adam(const float* __restrict__
 // (each widened by tol * span).  Pairs beyond the box on the far side
 // (farther apart, smaller overlaps) are predicted with features clipped to
 // the box, which over-estimates their contribution.
-__global__ void k_ood_count(const float* __restrict__ f, int64_t np, int n, const float* __restrict__ model, float tol,
-                            int* __restrict__ count) {
+// The same pass prepares the threshold: q[t] = pred[t] for off-diagonal pairs
+// and +inf for the diagonal (never dropped), w[t] = 10^pred[t] (0 there).
+__global__ void k_budget_prep(const float* __restrict__ f, const float* __restrict__ pred, int64_t np, int n,
+                              const float* __restrict__ model, float tol, int* __restrict__ count,
+                              float* __restrict__ q, double* __restrict__ w) {
   int c = 0;
   for (int64_t t = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; t < np; t += int64_t(gridDim.x) * blockDim.x) {
     int i, j;
     tri_ij(t, n, i, j);
+    const float p = pred[t];
+    q[t] = (i == j) ? INFINITY : p;
+    w[t] = (i == j) ? 0.0 : pow(10.0, double(p));
     if (i == j) continue;
     for (int k = 0; k < NIN; ++k) {
       const float lo = model[OXMIN + k], hi = model[OXMAX + k], span = hi - lo;
@@ -544,66 +590,120 @@ __global__ void k_ood_count(const float* __restrict__ f, int64_t np, int n, cons
   if (c) atomicAdd(count, c);
 }
 
-// Budget threshold preparation: q[t] = pred[t] for off-diagonal pairs and
-// +inf for the diagonal (never dropped), w[t] = 10^pred[t] (0 on the diagonal).
-__global__ void k_budget_prep(const float* __restrict__ pred, int64_t np, int n, float* __restrict__ q,
-                              double* __restrict__ w) {
-  for (int64_t t = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; t < np; t += int64_t(gridDim.x) * blockDim.x) {
-    int i, j;
-    tri_ij(t, n, i, j);
-    const double p = double(pred[t]);
-    q[t] = (i == j) ? INFINITY : pred[t];
-    w[t] = (i == j) ? 0.0 : pow(10.0, p);
-  }
+// Threshold tau (in log10): the smallest prediction v whose pairs up to and
+// including v have a sum of 10^pred above the budget (the pairs below tau are
+// dropped), or one more than the largest prediction if the sum of all is within
+// it.  Radix selection in one workgroup over the prepared arrays: predictions
+// map to 32-bit keys in their order, and each of eight passes finds the next
+// four bits of v from the sums of the 16 bins of the keys that share the bits
+// so far.  A thread has its own 16 bins in LDS and these are added in a fixed
+// order, so tau does not vary between runs.  Bound by the eight reads of the
+// keys by one CU (32896 pairs: 70 us; 64 bisections over keys and weights
+// took 599).  NaN and +inf belong to no bin; a prediction of -inf keeps all.
+constexpr int TNT = 1024, TREG = 24;
+constexpr unsigned NOKEY = 0xffffffffu;  // the pattern of a NaN
+__device__ __forceinline__ unsigned order_key(float v) {
+  const unsigned u = __float_as_uint(v);
+  return v < INFINITY ? ((u & 0x80000000u) ? ~u : u | 0x80000000u) : NOKEY;
 }
-
-// Largest tau (in log10) with sum over off-diagonal pairs of 10^pred below
-// tau at most budget; bisection in one workgroup over the prepared arrays.
-__global__ __launch_bounds__(1024) void k_budget_threshold(const float* __restrict__ q, const double* __restrict__ w,
-                                                           int64_t np, double budget, double* __restrict__ tau) {
-  __shared__ double red[1024];
-  __shared__ double lohi[2];
-  // bracket: prediction range over the off-diagonal pairs
-  double mn = 1e300, mx = -1e300;
-  for (int64_t t = threadIdx.x; t < np; t += 1024) {
-    const float v = q[t];
-    if (v == INFINITY) continue;
-    mn = fmin(mn, double(v));
-    mx = fmax(mx, double(v));
-  }
-  red[threadIdx.x] = mn;
-  __syncthreads();
-  for (int h = 512; h > 0; h >>= 1) {
-    if (threadIdx.x < h) red[threadIdx.x] = fmin(red[threadIdx.x], red[threadIdx.x + h]);
+__device__ __forceinline__ double key_value(unsigned k) {
+  return double(__uint_as_float((k & 0x80000000u) ? k & 0x7fffffffu : ~k));
+}
+__global__ __launch_bounds__(TNT) void k_budget_threshold(const float* __restrict__ q, const double* __restrict__ w,
+                                                          int64_t np, double budget, double* __restrict__ tau) {
+  __shared__ double bin[16][TNT];
+  __shared__ double tot[16];
+  __shared__ unsigned s_prefix;
+  __shared__ double s_base;
+  __shared__ int s_all;
+  __shared__ unsigned s_max[TNT / 64], s_min[TNT / 64];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  // the first keys of a thread stay in registers
+  unsigned key[TREG];
+#pragma unroll
+  for (int u = 0; u < TREG; ++u) key[u] = tid + u * TNT < np ? order_key(q[tid + u * TNT]) : NOKEY;
+  unsigned prefix = 0, mx = 0, mn = NOKEY;
+  double base = 0.0;
+  for (int p = 0; p < 8; ++p) {
+    const int sh = 28 - 4 * p;
+#pragma unroll
+    for (int d = 0; d < 16; ++d) bin[d][tid] = 0.0;
+    // eight keys at a time: the weights of those that count, all in flight
+    const auto add8 = [&](const unsigned* k, int64_t t0) {
+      bool on[8], any = false;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        on[u] = k[u] != NOKEY && (p == 0 || ((k[u] ^ prefix) >> (sh + 4)) == 0);
+        any = any || on[u];
+      }
+      if (!__any(any)) return;
+      double wt[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) wt[u] = w[on[u] ? t0 + u * TNT : 0];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (on[u]) {
+          bin[(k[u] >> sh) & 15][tid] += wt[u];
+          mx = k[u] > mx ? k[u] : mx;
+          mn = k[u] < mn ? k[u] : mn;
+        }
+    };
+#pragma unroll
+    for (int u = 0; u < TREG; u += 8) add8(key + u, tid + int64_t(u) * TNT);
+    for (int64_t t0 = tid + int64_t(TREG) * TNT; t0 - tid < np; t0 += 8 * TNT) {
+      unsigned k[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) k[u] = t0 + u * TNT < np ? order_key(q[t0 + u * TNT]) : NOKEY;
+      add8(k, t0);
+    }
     __syncthreads();
-  }
-  if (threadIdx.x == 0) lohi[0] = red[0] - 1.0;
-  __syncthreads();
-  red[threadIdx.x] = mx;
-  __syncthreads();
-  for (int h = 512; h > 0; h >>= 1) {
-    if (threadIdx.x < h) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + h]);
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) lohi[1] = red[0] + 1.0;
-  __syncthreads();
-  for (int it = 0; it < 64; ++it) {
-    const double mid = 0.5 * (lohi[0] + lohi[1]);
+    // wave wv adds up bin wv (16 waves, 16 bins)
     double s = 0.0;
-    for (int64_t t = threadIdx.x; t < np; t += 1024)
-      if (double(q[t]) < mid) s += w[t];
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int h = 512; h > 0; h >>= 1) {
-      if (threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
-      __syncthreads();
+#pragma unroll
+    for (int u = 0; u < TNT / 64; ++u) s += bin[wv][lane + 64 * u];
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
+    if (lane == 0) tot[wv] = s;
+    if (p == 0) {
+      for (int off = 32; off > 0; off >>= 1) {
+        mx = max(mx, unsigned(__shfl_down(int(mx), off, 64)));
+        mn = min(mn, unsigned(__shfl_down(int(mn), off, 64)));
+      }
+      if (lane == 0) {
+        s_max[wv] = mx;
+        s_min[wv] = mn;
+      }
     }
-    if (threadIdx.x == 0) {
-      if (red[0] <= budget) lohi[0] = mid; else lohi[1] = mid;
+    __syncthreads();
+    if (tid == 0) {
+      int d = 0;
+      double cum = base;
+      for (; d < 16; ++d) {
+        if (cum + tot[d] > budget) break;
+        if (d < 15 || p == 0) cum += tot[d];
+      }
+      if (p == 0) {
+        unsigned a = s_max[0], b = s_min[0];
+        for (int i = 1; i < TNT / 64; ++i) {
+          a = max(a, s_max[i]);
+          b = min(b, s_min[i]);
+        }
+        const bool low = b == order_key(-INFINITY);
+        s_all = d == 16 || low;
+        if (low) tau[0] = -INFINITY;
+        else if (d == 16) tau[0] = b == NOKEY ? 0.0 : key_value(a) + 1.0;
+      }
+      // past the first pass the bins of a prefix can fall short of the sum that
+      // chose it by a rounding: its last bin then holds the threshold
+      if (d > 15) d = 15;
+      s_prefix = prefix | (unsigned(d) << sh);
+      s_base = cum;
     }
     __syncthreads();
+    if (s_all) return;
+    prefix = s_prefix;
+    base = s_base;
   }
-  if (threadIdx.x == 0) tau[0] = lohi[0];
+  if (tid == 0) tau[0] = key_value(prefix);
 }
 
 // keep[t] = diagonal, or off-diagonal with pred >= tau (learned rule), or
@@ -624,41 +724,18 @@ __global__ void k_keep_flags(const float* __restrict__ pred, int64_t np, int n, 
 }
 
 // Ordered compaction of kept pairs (triangle order = sorted by i, then j).
-__global__ __launch_bounds__(1024) void k_compact_keep(const uint8_t* __restrict__ keep, int64_t np, int n,
-                                                       int64_t cap, int32_t* __restrict__ pairs,
-                                                       int64_t* __restrict__ count) {
-  __shared__ int64_t wsum[16];
-  __shared__ int64_t base;
-  if (threadIdx.x == 0) base = 0;
-  __syncthreads();
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  for (int64_t c0 = 0; c0 < np; c0 += blockDim.x) {
-    const int64_t t = c0 + threadIdx.x;
-    const bool k = t < np && keep[t];
-    const unsigned long long bal = __ballot(k);
-    const int before = __popcll(bal & ((1ull << lane) - 1ull));
-    if (lane == 0) wsum[wv] = __popcll(bal);
-    __syncthreads();
-    int64_t off = base;
-    for (int w = 0; w < wv; ++w) off += wsum[w];
-    if (k) {
-      const int64_t p = off + before;
-      if (p < cap) {
-        int i, j;
-        tri_ij(t, n, i, j);
-        pairs[2 * p] = i;
-        pairs[2 * p + 1] = j;
-      }
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-      int64_t s = 0;
-      for (int w = 0; w < int(blockDim.x / 64); ++w) s += wsum[w];
-      base += s;
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) count[0] = base;
+__global__ __launch_bounds__(CNT) void k_compact_keep(const uint8_t* __restrict__ keep, int64_t np, int n,
+                                                      int64_t cap, int32_t* __restrict__ pairs,
+                                                      int64_t* __restrict__ count) {
+  compact_tri(
+      n, [&](int64_t t, int, int) { return keep[t] != 0; },
+      [&](int64_t p, int i, int j) {
+        if (p < cap) {
+          pairs[2 * p] = i;
+          pairs[2 * p + 1] = j;
+        }
+      },
+      count);
 }
 
 // ---------------------------------------------------------------- launchers
@@ -668,16 +745,16 @@ static unsigned gridn(int64_t n, int nt, int cap = 4096) {
   return unsigned(g < 1 ? 1 : g);
 }
 
-void launch_marginals(const double* phi, int norb, int n, double* pz, double* py, double* px, hipStream_t s) {
-  hipLaunchKernelGGL(k_plane_marginals, dim3(n, norb), dim3(256), 0, s, phi, n, pz, py, px);
-}
-void launch_subsample(const double* phi, int norb, int n, int st, double* out, hipStream_t s) {
-  const int m = n / st;
-  hipLaunchKernelGGL(k_subsample, dim3(gridn(int64_t(norb) * m * m * m, 256)), dim3(256), 0, s, phi, norb, n, st, out);
+void launch_marginals(const double* phi, int norb, int n, int st, double* pz, double* py, double* px, double* sub,
+                      hipStream_t s) {
+  if (n <= 128)
+    hipLaunchKernelGGL(k_plane_marginals<2>, dim3(n, norb), dim3(256), 0, s, phi, n, st, pz, py, px, sub);
+  else
+    hipLaunchKernelGGL(k_plane_marginals<4>, dim3(n, norb), dim3(256), 0, s, phi, n, st, pz, py, px, sub);
 }
 void launch_centroids(const double* pz, const double* py, const double* px, int norb, int n, double L, double dV,
                       double* cen, double* spr, hipStream_t s) {
-  hipLaunchKernelGGL(k_centroids, dim3(norb), dim3(256), 0, s, pz, py, px, n, L, dV, cen, spr);
+  hipLaunchKernelGGL(k_centroids, dim3(norb), dim3(1024), 0, s, pz, py, px, n, L, dV, cen, spr);
 }
 void launch_pair_features(const int32_t* pairs, int64_t np, int norb, const double* cen, const double* spr,
                           const double* O, const double* P, double L, float* f, hipStream_t s) {
@@ -693,7 +770,7 @@ void launch_mlp_stats(const float* x, const float* t, int64_t n, double* part, f
   hipLaunchKernelGGL(k_stats_final, dim3(1), dim3(1), 0, s, part, nb, n, m);
 }
 void launch_mlp_forward(const float* m, const float* x, int64_t n, int clamp, float* y, hipStream_t s) {
-  hipLaunchKernelGGL(k_mlp_forward, dim3(gridn(n, 256, 2048)), dim3(256), 0, s, m, x, n, clamp, y);
+  hipLaunchKernelGGL(k_mlp_forward, dim3(gridn(n, 64, 2048)), dim3(256), 0, s, m, x, n, clamp, y);
 }
 int mlp_grad_blocks(int bsz) { return int(gridn(bsz, GCH, 1024)); }
 void launch_mlp_grad_partial(const float* m, const float* x, const float* t, int64_t n, int64_t off, int64_t stride,
@@ -712,11 +789,11 @@ void launch_mlp_adam(const float* gpart, const float* lpart, int nb, float* m, f
 void launch_select(const float* pred, const float* feats, int64_t np, int norb, const float* model, double budget,
                    const double* O, double rho_cut, float ood_tol, int* ood, double* tau, uint8_t* keep, int64_t cap,
                    int32_t* pairs, int64_t* count, float* q, double* w, hipStream_t s) {
-  hipLaunchKernelGGL(k_ood_count, dim3(gridn(np, 256)), dim3(256), 0, s, feats, np, norb, model, ood_tol, ood);
-  hipLaunchKernelGGL(k_budget_prep, dim3(gridn(np, 256)), dim3(256), 0, s, pred, np, norb, q, w);
-  hipLaunchKernelGGL(k_budget_threshold, dim3(1), dim3(1024), 0, s, q, w, np, budget, tau);
+  hipLaunchKernelGGL(k_budget_prep, dim3(gridn(np, 256)), dim3(256), 0, s, feats, pred, np, norb, model, ood_tol, ood,
+                     q, w);
+  hipLaunchKernelGGL(k_budget_threshold, dim3(1), dim3(TNT), 0, s, q, w, np, budget, tau);
   hipLaunchKernelGGL(k_keep_flags, dim3(gridn(np, 256)), dim3(256), 0, s, pred, np, norb, tau, O, rho_cut, ood, keep);
-  hipLaunchKernelGGL(k_compact_keep, dim3(1), dim3(1024), 0, s, keep, np, norb, cap, pairs, count);
+  hipLaunchKernelGGL(k_compact_keep, dim3(1), dim3(CNT), 0, s, keep, np, norb, cap, pairs, count);
 }
 
 }  // namespace ace
