@@ -783,7 +783,7 @@ hipError_t gemm_nt(int prec, int op, const void* A, int64_t lda, const void* B, 
 // out between the MFMAs spilled registers and was slower).  Before and after:
 // 64 x 64 on 160^3 1.84 -> 0.87 ms (4.8 TB/s), 40 x 40 on 64^3 67 -> 43 us,
 // 128 x 128 on 96^3 0.75 -> 0.69 ms, triangular 0.545 -> 0.414 ms, the same
-// with FP32 B 0.658 -> 0.402 ms, 256 x 256 on 120^3 4.44 -> 4.16 ms.
+// with FP32 B 0.658 -> 0.402 ms.
 // The two rows of k that a half-wave reads are moved to opposite halves of the
 // banks by swapping 16-column blocks on every second row (pair of rows in FP32).
 // LOWER: S(m, k) = 0 for k > m.  The row blocks are dealt so that the waves
@@ -801,16 +801,17 @@ __device__ __forceinline__ int ls_rowblk(int w, int i) {
 template <typename TB, int RW, int NWV, int KMAX, int NC, bool TRANS, bool LOWER>
 __global__ __launch_bounds__(64 * NWV, 2) void k_ls_stream(const double* __restrict__ S, int lds,
                                                            const TB* __restrict__ B, int64_t ldb,
-                                                           double* __restrict__ C, int64_t ldc, int M, int K,
+                                                           double* __restrict__ C, int64_t ldc, int mb, int M, int K,
                                                            int64_t R, double alpha, LsSplit sp) {
   constexpr int NT = 64 * NWV, PER = KMAX * NC / NT, JB = NC / 16, KSTEPS = KMAX / 4, KR = NT / NC;
+  constexpr bool CLAMP = KMAX > 128;  // (with fewer rows: more registers, and rows loaded for nothing)
   static_assert(NT % NC == 0 && KMAX % KR == 0 && NC % 16 == 0, "tile shape");
   __shared__ TB Bs[2][KMAX * NC];
   const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, q = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   int rb = 0;
   while (int(blockIdx.x) >= sp.first[rb + 1]) ++rb;
-  const int m0 = rb * sp.rows;
+  const int m0 = mb + rb * sp.rows;
   const int64_t ns = sp.first[rb + 1] - sp.first[rb], ntile = (R + NC - 1) / NC;
   const int kt = LOWER && m0 + sp.rows < K ? m0 + sp.rows : K;  // rows of B this row block reads
   double a[RW][KSTEPS];
@@ -836,8 +837,15 @@ __global__ __launch_bounds__(64 * NWV, 2) void k_ls_stream(const double* __restr
     if (kt == KMAX && tile * NC + NC <= R) {
 #pragma unroll
       for (int u = 0; u < PER; ++u, p += int64_t(KR) * ldb) vb[u] = *p;
+    } else if constexpr (CLAMP) {
+      // past the edges: the last column, the last row (zeroed by store)
+      const TB* e = B + (c < R ? c : R - 1);
+      int k = kr;  // opaque: the rows are not kept in registers from tile to tile
+      asm volatile("" : "+v"(k));
+#pragma unroll
+      for (int u = 0; u < PER; ++u) vb[u] = e[int64_t(k + KR * u < kt ? k + KR * u : kt - 1) * ldb];
     } else {
-      int k = kr;  // opaque: the bounds are not kept in registers from tile to tile
+      int k = kr;
       asm volatile("" : "+v"(k));
 #pragma unroll
       for (int u = 0; u < PER; ++u) {
@@ -851,7 +859,7 @@ __global__ __launch_bounds__(64 * NWV, 2) void k_ls_stream(const double* __restr
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
       const int k = kr + KR * u;
-      dst[k * NC + (nc ^ swap16(k))] = vb[u];
+      dst[k * NC + (nc ^ swap16(k))] = !CLAMP || k < kt ? vb[u] : TB(0);
     }
   };
   int64_t tile = int(blockIdx.x) - sp.first[rb];
@@ -917,19 +925,19 @@ __global__ __launch_bounds__(64 * NWV, 2) void k_ls_stream(const double* __restr
   }
 }
 
-// Row blocks and the workgroups of each, two per CU in all: shares follow the
-// work (with LOWER the later row blocks have more).
+// Rows mb ... M - 1 of C.  Row blocks and the workgroups of each, eight waves per
+// CU in all: shares follow the work (with LOWER the later row blocks have more).
 template <typename TB, int RW, int NWV, int KMAX, int NC, bool TRANS, bool LOWER>
-static void launch_stream(const double* S, int lds, const TB* B, int64_t ldb, double* C, int64_t ldc, int M, int K,
-                          int64_t R, double alpha, hipStream_t s) {
+static void launch_stream(const double* S, int lds, const TB* B, int64_t ldb, double* C, int64_t ldc, int mb, int M,
+                          int K, int64_t R, double alpha, hipStream_t s) {
   LsSplit sp;
   sp.rows = 16 * RW * NWV;
-  const int nrb = (M + sp.rows - 1) / sp.rows;
+  const int nrb = (M - mb + sp.rows - 1) / sp.rows;
   const int64_t ntile = (R + NC - 1) / NC;
-  const int total = int(std::min<int64_t>(512, ntile * nrb));
+  const int total = int(std::min<int64_t>(2048 / NWV, ntile * nrb));
   double w[4], sum = 0.0;
   for (int b = 0; b < nrb; ++b) {
-    const int lo = b * sp.rows, hi = std::min(M, lo + sp.rows);
+    const int lo = mb + b * sp.rows, hi = std::min(M, lo + sp.rows);
     w[b] = LOWER ? 0.5 * (double(hi) * hi - double(lo) * lo) : double(hi - lo);
     sum += w[b];
   }
@@ -942,7 +950,7 @@ static void launch_stream(const double* S, int lds, const TB* B, int64_t ldb, do
   }
   for (int b = nrb; b < 4; ++b) sp.first[b + 1] = sp.first[b];
   hipLaunchKernelGGL((k_ls_stream<TB, RW, NWV, KMAX, NC, TRANS, LOWER>), dim3(unsigned(sp.first[nrb])), dim3(64 * NWV),
-                     0, s, S, lds, B, ldb, C, ldc, M, K, R, alpha, sp);
+                     0, s, S, lds, B, ldb, C, ldc, mb, M, K, R, alpha, sp);
 }
 
 template <typename TB, bool TRANS, bool LOWER>
@@ -952,16 +960,24 @@ static void launch_ls(const double* S, int lds, const TB* B, int64_t ldb, double
     dim3 grid(unsigned((R + 15) / 16), unsigned((M + 15) / 16));
     hipLaunchKernelGGL((k_gemm_tiny<TB, TRANS, LOWER>), grid, dim3(64), 0, s, S, lds, B, ldb, C, ldc, M, K, R, alpha);
   } else if (K <= 64 && M <= 64) {
-    launch_stream<TB, 1, 4, 64, 64, TRANS, LOWER>(S, lds, B, ldb, C, ldc, M, K, R, alpha, s);
+    launch_stream<TB, 1, 4, 64, 64, TRANS, LOWER>(S, lds, B, ldb, C, ldc, 0, M, K, R, alpha, s);
   } else if (K <= 128 && M <= 64) {
-    launch_stream<TB, 1, 4, 128, 32, TRANS, LOWER>(S, lds, B, ldb, C, ldc, M, K, R, alpha, s);
+    launch_stream<TB, 1, 4, 128, 32, TRANS, LOWER>(S, lds, B, ldb, C, ldc, 0, M, K, R, alpha, s);
   } else if (K <= 128 && M <= 512) {
-    launch_stream<TB, 2, 4, 128, 32, TRANS, LOWER>(S, lds, B, ldb, C, ldc, M, K, R, alpha, s);
-  } else if (!LOWER && std::is_same<TB, double>::value && K > 192 && K <= 256 && M > 192 && M <= 256) {
-    // longer K leaves registers for one row block per wave, so B is read by
-    // four row blocks: worth it where K and M fill the 256 (200 x 120 and the
-    // triangular 256 x 256 product are faster on the 128 x 128 tiles)
-    launch_stream<TB, 1, 4, 256, 16, TRANS, false>(S, lds, B, ldb, C, ldc, M, K, R, alpha, s);
+    launch_stream<TB, 2, 4, 128, 32, TRANS, LOWER>(S, lds, B, ldb, C, ldc, 0, M, K, R, alpha, s);
+  } else if (LOWER && M > 128 && M <= 256 && (K <= 192 || (K <= 256 && (K > 224 || sizeof(TB) == 4)))) {
+    // Rows 0 ... 127 need 128 rows of B, the others up to 256, for which two
+    // waves per SIMD have registers.  Against the 128 x 128 tiles: FP32 160 on
+    // 96^3 1.12 -> 0.84 ms, 256 on 120^3 3.46 -> 2.65; FP64 144 on 96^3 0.90 ->
+    // 0.79, 240 1.50 -> 1.34, but 200 on 100^3 1.38 -> 1.43 (padded to 256).
+    // The full 256 x 256 product of FP64 values was the same on both.
+    if constexpr (LOWER) {
+      launch_stream<TB, 2, 4, 128, 32, TRANS, true>(S, lds, B, ldb, C, ldc, 0, 128, 128, R, alpha, s);
+      if (K <= 192)
+        launch_stream<TB, 1, 8, 192, 32, TRANS, true>(S, lds, B, ldb, C, ldc, 128, M, K, R, alpha, s);
+      else
+        launch_stream<TB, 1, 8, 256, 32, TRANS, true>(S, lds, B, ldb, C, ldc, 128, M, K, R, alpha, s);
+    }
   } else if (M > 64) {
     dim3 grid(unsigned((R + TT - 1) / TT), unsigned((M + TT - 1) / TT));
     // FP32 right operands run 8 waves per tile; with FP64 ones the 512-thread
