@@ -175,9 +175,18 @@ void launch_count_above(const double* res, int64_t ng, const double* t, int64_t*
 void launch_scatter_res(const int32_t* list, int64_t cnt, const double* v, double* res, hipStream_t s);
 void launch_retire(const int32_t* piv, int k, double* res, hipStream_t s);
 void launch_gather_cols(const double* A, int n, int64_t ng, const int32_t* piv, double* AC, hipStream_t s);
-void launch_scale_inf(double* X, const double* G, int n, hipStream_t s);
-void launch_ns_combine(const double* X, const double* Z, double* Y, int64_t cnt, hipStream_t s);
-void launch_dev_identity(const double* G, int n, double* out, hipStream_t s);
+// Loewdin rotation (polar.hip): in one launch for n where polar_fits_one, stat
+// one double; else G = X^T X with polar_tiles(n) partial maxima of |G - I|,
+// the row sums of |G|, and the step Y = (3 X - X G) / 2.
+bool polar_fits_one(int n);
+int polar_tiles(int n);
+void launch_polar_small(const double* psi, int n, int64_t ng, const int32_t* piv, double* X, double* U, double* stat,
+                        hipStream_t s);
+void launch_ns_gram(const double* X, int n, double* G, double* dev, hipStream_t s);
+void launch_row_abs(const double* G, int n, double* rows, hipStream_t s);
+void launch_ns_step(const double* X, const double* G, const double* rows, int n, double* Y, hipStream_t s);
+// dg = {largest, smallest diagonal element of A, *info}
+void launch_diag_range(const double* A, int n, const int* info, double* dg, hipStream_t s);
 void launch_compact_pairs(const double* O, int n, double rho_cut, int64_t cap, int32_t* pairs, double* ov,
                           int64_t* count, hipStream_t s);
 void launch_pair_energy(const double* epart, int npacks, int nblk, const Pack* packs, const int64_t* pidx, double dV,

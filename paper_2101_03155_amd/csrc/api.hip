@@ -564,44 +564,52 @@ int ace_get_pair_shape(ace_ctx* c, int prec, int n, int* fused, int* max_packs) 
 
 // ------------------------------------------------------------------ (a) localize
 // Loewdin step on the columns `pivots`: U = A_C (A_C^T A_C)^-1/2 into U
-// (nullable) and phi_k = sum_i psi_i U_ik.  AC, X, G, Z are norb x norb
-// workspaces, dev one double.
-static int lowdin(ace_ctx* c, int norb, int64_t ng, const double* psi, const int32_t* pivots, double* AC, double* X,
-                  double* G, double* Z, double* dev, double* phi, double* U) {
+// (nullable) and phi_k = sum_i psi_i U_ik.  X, G, Z are norb x norb workspaces,
+// red room for polar_tiles(norb) + norb doubles.
+static int lowdin(ace_ctx* c, int norb, int64_t ng, const double* psi, const int32_t* pivots, double* X, double* G,
+                  double* Z, double* red, double* phi, double* U) {
   hipStream_t s = c->stream;
-  // Loewdin rotation U = A_C (A_C^T A_C)^-1/2 = polar factor of A_C, by the
-  // Newton-Schulz iteration X <- X (3 I - X^T X) / 2 from X = A_C scaled so
-  // that every singular value is at most 1 (max row sum of |A_C^T A_C|).
-  launch_gather_cols(psi, norb, ng, pivots, AC, s);
-  HIPCHK(c, hipMemcpyAsync(X, AC, size_t(norb) * norb * sizeof(double), hipMemcpyDeviceToDevice, s));
-  HIPCHK(c, gemm_ls(0, true, false, X, norb, X, norb, G, norb, norb, norb, norb, 1.0, s, nullptr));
-  launch_scale_inf(X, G, norb, s);
+  if (polar_fits_one(norb)) {
+    launch_polar_small(psi, norb, ng, pivots, X, U, red, s);
+    double h = 0.0;
+    HIPCHK(c, hipMemcpyAsync(&h, red, sizeof(double), hipMemcpyDeviceToHost, s));
+    HIPCHK(c, hipStreamSynchronize(s));
+    if (h == 1.0) return fail(c, ACE_E_NONFINITE, "non-finite Loewdin iteration (singular A_C?)");
+    if (h != 0.0) return fail(c, ACE_E_NONFINITE, "Loewdin polar iteration did not converge");
+    HIPCHK(c, gemm_ls(0, true, false, X, norb, psi, ng, phi, ng, norb, norb, ng, 1.0, s, c->R()));
+    return ACE_OK;
+  }
+  const int nt = polar_tiles(norb);
+  double* rows = red + nt;
+  launch_gather_cols(psi, norb, ng, pivots, X, s);
+  launch_ns_gram(X, norb, G, red, s);
+  launch_row_abs(G, norb, rows, s);
   // Each iteration forms G = X^T X, which also measures max|X^T X - I|; it is
   // read back every second iteration from the fourth on.  Once below 1e-11,
   // two more iterations (the first reusing that G) take the quadratically
-  // converging iterate to rounding.
+  // converging iterate to rounding.  X alternates between two buffers.
   int converged_at = -1;
+  std::vector<double> hdev(static_cast<size_t>(nt));
   for (int it = 0; it < 200; ++it) {
-    HIPCHK(c, gemm_ls(0, true, false, X, norb, X, norb, G, norb, norb, norb, norb, 1.0, s, nullptr));
+    if (it > 0) launch_ns_gram(X, norb, G, red, s);
     if (it >= 4 && it % 2 == 0) {
-      launch_dev_identity(G, norb, dev, s);
-      double h = 0.0;
-      HIPCHK(c, hipMemcpyAsync(&h, dev, sizeof(double), hipMemcpyDeviceToHost, s));
+      HIPCHK(c, hipMemcpyAsync(hdev.data(), red, size_t(nt) * sizeof(double), hipMemcpyDeviceToHost, s));
       HIPCHK(c, hipStreamSynchronize(s));
+      const double h = *std::max_element(hdev.begin(), hdev.end());
       if (!std::isfinite(h)) return fail(c, ACE_E_NONFINITE, "non-finite Loewdin iteration (singular A_C?)");
       if (h < 1e-11) {
         converged_at = it;
         break;
       }
     }
-    HIPCHK(c, gemm_ls(0, false, false, X, norb, G, norb, Z, norb, norb, norb, norb, 1.0, s, nullptr));
-    launch_ns_combine(X, Z, X, int64_t(norb) * norb, s);
+    launch_ns_step(X, G, it == 0 ? rows : nullptr, norb, Z, s);
+    std::swap(X, Z);
   }
   if (converged_at < 0) return fail(c, ACE_E_NONFINITE, "Loewdin polar iteration did not converge");
   for (int j = 0; j < 2; ++j) {
-    if (j > 0) HIPCHK(c, gemm_ls(0, true, false, X, norb, X, norb, G, norb, norb, norb, norb, 1.0, s, nullptr));
-    HIPCHK(c, gemm_ls(0, false, false, X, norb, G, norb, Z, norb, norb, norb, norb, 1.0, s, nullptr));
-    launch_ns_combine(X, Z, X, int64_t(norb) * norb, s);
+    if (j > 0) launch_ns_gram(X, norb, G, red, s);
+    launch_ns_step(X, G, nullptr, norb, Z, s);
+    std::swap(X, Z);
   }
   // phi_k = sum_i psi_i U_ik
   HIPCHK(c, gemm_ls(0, true, false, X, norb, psi, ng, phi, ng, norb, norb, ng, 1.0, s, c->R()));
@@ -619,7 +627,7 @@ int ace_localize(ace_ctx* c, const ace_grid* g, int norb, const double* psi, dou
   if (ng < norb) return fail(c, ACE_E_ARG, "grid smaller than the number of orbitals");
   hipStream_t s = c->stream;
   rec_begin(c->R(), ST_LOCALIZE, s);
-  double *res, *pv, *Q, *q, *AC, *X, *G, *Z, *dev, *Ub, *pres, *Apool, *tvals, *tmax, *Lc;
+  double *res, *pv, *Q, *q, *X, *G, *Z, *red, *Ub, *pres, *Apool, *tvals, *tmax, *Lc;
   int64_t *pi, *pcnt;
   int32_t* pool;
   unsigned* hist;
@@ -639,12 +647,11 @@ int ace_localize(ace_ctx* c, const ace_grid* g, int norb, const double* psi, dou
   WS(c, "pi", ncand * sizeof(int64_t), pi);
   WS(c, "Q", size_t(norb) * norb * sizeof(double), Q);
   WS(c, "q", size_t(norb) * sizeof(double), q);
-  WS(c, "AC", size_t(norb) * norb * sizeof(double), AC);
   WS(c, "X", size_t(norb) * norb * sizeof(double), X);
   WS(c, "G", size_t(norb) * norb * sizeof(double), G);
   WS(c, "Z", size_t(norb) * norb * sizeof(double), Z);
   WS(c, "U", size_t(norb) * norb * sizeof(double), Ub);
-  WS(c, "scal", 64 * sizeof(double), dev);
+  WS(c, "nsred", size_t(polar_tiles(norb) + norb) * sizeof(double), red);
   WS(c, "pres", size_t(pmax) * sizeof(double), pres);
   WS(c, "pool", size_t(pmax) * sizeof(int32_t), pool);
   WS(c, "Apool", size_t(pmax) * norb * sizeof(double), Apool);
@@ -789,7 +796,7 @@ int ace_localize(ace_ctx* c, const ace_grid* g, int norb, const double* psi, dou
     k = hk[0];
   }
   HIPCHK(c, hipGetLastError());
-  rc = lowdin(c, norb, ng, psi, pivots, AC, X, G, Z, dev, phi, U);
+  rc = lowdin(c, norb, ng, psi, pivots, X, G, Z, red, phi, U);
   if (rc) return rc;
   rec_end(c->R(), ST_LOCALIZE, s);
   HIPCHK(c, hipGetLastError());
@@ -816,13 +823,12 @@ int ace_localize_pivots(ace_ctx* c, const ace_grid* g, int norb, const double* p
   if (std::adjacent_find(sorted.begin(), sorted.end()) != sorted.end())
     return fail(c, ACE_E_ARG, "repeated pivot column");
   rec_begin(c->R(), ST_LOCALIZE, s);
-  double *AC, *X, *G, *Z, *dev;
-  WS(c, "AC", size_t(norb) * norb * sizeof(double), AC);
+  double *X, *G, *Z, *red;
   WS(c, "X", size_t(norb) * norb * sizeof(double), X);
   WS(c, "G", size_t(norb) * norb * sizeof(double), G);
   WS(c, "Z", size_t(norb) * norb * sizeof(double), Z);
-  WS(c, "scal", 64 * sizeof(double), dev);
-  rc = lowdin(c, norb, ng, psi, pivots, AC, X, G, Z, dev, phi, U);
+  WS(c, "nsred", size_t(polar_tiles(norb) + norb) * sizeof(double), red);
+  rc = lowdin(c, norb, ng, psi, pivots, X, G, Z, red, phi, U);
   if (rc) return rc;
   rec_end(c->R(), ST_LOCALIZE, s);
   HIPCHK(c, hipGetLastError());
@@ -863,27 +869,22 @@ int ace_localize_step(ace_ctx* c, const ace_grid* g, int norb, const double* psi
   HIPCHK(c, gemm_ls(0, true, false, AC, norb, AC, norb, G, norb, norb, norb, norb, 1.0, s, nullptr));
   launch_zero(dinfo, sizeof(int), s);
   launch_cholesky(G, norb, dinfo, tinv, s);
-  std::vector<double> hg(size_t(norb) * norb);
-  int hinfo = 0;
-  HIPCHK(c, hipMemcpyAsync(hg.data(), G, hg.size() * sizeof(double), hipMemcpyDeviceToHost, s));
-  HIPCHK(c, hipMemcpyAsync(&hinfo, dinfo, sizeof(int), hipMemcpyDeviceToHost, s));
+  launch_diag_range(G, norb, dinfo, tinv, s);
+  double hd[3] = {0.0, 0.0, 0.0};
+  HIPCHK(c, hipMemcpyAsync(hd, tinv, sizeof(hd), hipMemcpyDeviceToHost, s));
   HIPCHK(c, hipStreamSynchronize(s));
-  double dmax = 0.0, dmin = INFINITY;
-  for (int k = 0; k < norb; ++k) {
-    const double d = hg[size_t(k) * norb + k];
-    dmax = std::max(dmax, d);
-    dmin = std::min(dmin, d);
-  }
+  const double dmax = hd[0], dmin = hd[1];
+  const int hinfo = int(hd[2]);
   const double cond = (hinfo == 0 && dmin > 0.0 && std::isfinite(dmax)) ? (dmax / dmin) * (dmax / dmin) : INFINITY;
   info->gram_cond = cond;
   info->pairs_added = info->pairs_removed = 0;
   if (cond <= cond_max) {
     info->reused_columns = 1;
-    double *X, *Z, *dev;
+    double *X, *Z, *red;
     WS(c, "X", size_t(norb) * norb * sizeof(double), X);
     WS(c, "Z", size_t(norb) * norb * sizeof(double), Z);
-    WS(c, "scal", 64 * sizeof(double), dev);
-    rc = lowdin(c, norb, ng, psi, pivots, AC, X, G, Z, dev, phi, U);
+    WS(c, "nsred", size_t(polar_tiles(norb) + norb) * sizeof(double), red);
+    rc = lowdin(c, norb, ng, psi, pivots, X, G, Z, red, phi, U);
     if (rc != ACE_E_NONFINITE) return rc;
     c->err.clear();  // the polar iteration failed on these columns: fresh SCDM below
   }

@@ -20,6 +20,7 @@
 #include <cstdint>
 #include <type_traits>
 #include "ace_internal.h"
+#include "tiny_tile.h"
 
 namespace ace {
 
@@ -225,29 +226,21 @@ __global__ __launch_bounds__(256) void k_gemm_ls(const double* __restrict__ S, i
 }
 
 // ---------------------------------------------------------------- small outputs
-// Same contraction as the left-small kernel for small outputs (R <= 1024):
-// one wave per 16 x 16 output tile, operands read straight from global memory
-// (L2-resident at these sizes), so even a 128^3 product spreads over 64 CUs.
+// Same contraction as the left-small kernel for small outputs (R <= 1024): a
+// workgroup per 16 x 16 output tile, so even a 128^3 product spreads over 64 CUs.
 template <typename TB, bool TRANS, bool LOWER>
-__global__ __launch_bounds__(64) void k_gemm_tiny(const double* __restrict__ S, int lds, const TB* __restrict__ B,
-                                                  int64_t ldb, double* __restrict__ C, int64_t ldc, int M, int K,
-                                                  int64_t R, double alpha) {
+__global__ __launch_bounds__(256) void k_gemm_tiny(const double* __restrict__ S, int lds, const TB* __restrict__ B,
+                                                   int64_t ldb, double* __restrict__ C, int64_t ldc, int M, int K,
+                                                   int64_t R, double alpha) {
   const int lane = threadIdx.x;
   const int r0 = blockIdx.x * 16, m0 = blockIdx.y * 16;
-  const int li = lane % 16, lk = lane / 16;
-  d4 acc = d4{0, 0, 0, 0};
   const int kend = LOWER ? ((m0 + 16 < K) ? m0 + 16 : K) : K;
-  for (int k0 = 0; k0 < kend; k0 += 4) {
-    const int k = k0 + lk, m = m0 + li;
-    const int64_t r = r0 + li;
-    double a = 0.0, b = 0.0;
-    if (k < K && m < M) a = TRANS ? S[int64_t(k) * lds + m] : S[int64_t(m) * lds + k];
-    if (k < K && r < R) b = double(B[int64_t(k) * ldb + r]);
-    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc, 0, 0, 0);
-  }
+  const tiny_d4 acc = tiny_tile<TB, TRANS>(S, lds, B, ldb, m0, r0, M, K, R, kend);
+  if (lane >= 64) return;
+#pragma unroll
   for (int q = 0; q < 4; ++q) {
-    const int i = m0 + lk + 4 * q;
-    const int64_t j = r0 + li;
+    const int i = m0 + lane / 16 + 4 * q;
+    const int64_t j = r0 + lane % 16;
     if (i < M && j < R) C[int64_t(i) * ldc + j] = alpha * acc[q];
   }
 }
@@ -958,7 +951,7 @@ static void launch_ls(const double* S, int lds, const TB* B, int64_t ldb, double
                       int64_t R, double alpha, hipStream_t s) {
   if (R <= 1024) {
     dim3 grid(unsigned((R + 15) / 16), unsigned((M + 15) / 16));
-    hipLaunchKernelGGL((k_gemm_tiny<TB, TRANS, LOWER>), grid, dim3(64), 0, s, S, lds, B, ldb, C, ldc, M, K, R, alpha);
+    hipLaunchKernelGGL((k_gemm_tiny<TB, TRANS, LOWER>), grid, dim3(256), 0, s, S, lds, B, ldb, C, ldc, M, K, R, alpha);
   } else if (K <= 64 && M <= 64) {
     launch_stream<TB, 1, 4, 64, 64, TRANS, LOWER>(S, lds, B, ldb, C, ldc, 0, M, K, R, alpha, s);
   } else if (K <= 128 && M <= 64) {

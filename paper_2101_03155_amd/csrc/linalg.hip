@@ -2,7 +2,6 @@
 //   * symmetrization, trace and sign flip of M (Appendix A: -M = L L^T);
 //   * FP64 Cholesky and triangular inverse of the N_orb x N_orb factor;
 //   * the column-pivoted QR pivot search of the SCDM localization;
-//   * Newton-Schulz polar iteration for the Loewdin rotation;
 //   * screening-pair compaction; pair-energy reduction; conversions.
 #include <hip/hip_runtime.h>
 #include <cstdint>
@@ -1196,54 +1195,6 @@ __global__ void k_gather_cols(const double* __restrict__ A, int n, int64_t ng, c
   }
 }
 
-// ---------------------------------------------------------------- Newton-Schulz helpers
-// X <- alpha * X (scale by 1/||X||_F computed in one workgroup)
-// X <- X / sqrt(max_i sum_j |G_ij|) with G = X^T X (n x n): the largest
-// absolute row sum of G bounds its largest eigenvalue, so every singular
-// value of the scaled X is at most 1 (the Newton-Schulz polar iteration then
-// converges from any nonsingular start).  One block.
-__global__ void k_scale_inf(double* __restrict__ X, const double* __restrict__ G, int n) {
-  __shared__ double red[1024];
-  double m = 0.0;
-  for (int i = threadIdx.x; i < n; i += blockDim.x) {
-    double r = 0.0;
-    for (int j = 0; j < n; ++j) r += fabs(G[int64_t(i) * n + j]);
-    m = fmax(m, r);
-  }
-  red[threadIdx.x] = m;
-  __syncthreads();
-  for (int h = blockDim.x / 2; h > 0; h >>= 1) {
-    if (threadIdx.x < h) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + h]);
-    __syncthreads();
-  }
-  const double inv = 1.0 / sqrt(red[0]);
-  for (int64_t e = threadIdx.x; e < int64_t(n) * n; e += blockDim.x) X[e] *= inv;
-}
-
-// Y <- 1.5 X - 0.5 Z ; also dev = max |G - I| where G = X^T X (given)
-__global__ void k_ns_combine(const double* __restrict__ X, const double* __restrict__ Z, double* __restrict__ Y,
-                             int64_t cnt) {
-  for (int64_t e = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; e < cnt; e += int64_t(gridDim.x) * blockDim.x)
-    Y[e] = 1.5 * X[e] - 0.5 * Z[e];
-}
-
-__global__ void k_dev_identity(const double* __restrict__ G, int n, double* __restrict__ out) {
-  __shared__ double red[1024];
-  double m = 0.0;
-  for (int e = threadIdx.x; e < n * n; e += blockDim.x) {
-    const int i = e / n, j = e % n;
-    const double d = fabs(G[e] - (i == j ? 1.0 : 0.0));
-    m = d > m ? d : m;
-  }
-  red[threadIdx.x] = m;
-  __syncthreads();
-  for (int h = blockDim.x / 2; h > 0; h >>= 1) {
-    if (threadIdx.x < h) red[threadIdx.x] = fmax(red[threadIdx.x], red[threadIdx.x + h]);
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) out[0] = red[0];
-}
-
 // ---------------------------------------------------------------- screening
 // Upper-triangle entries (i <= j) with O_ij >= rho_cut, or i == j, in
 // row-major order; writes at most cap pairs and the full count to *count.
@@ -1420,15 +1371,6 @@ void launch_retire(const int32_t* piv, int k, double* res, hipStream_t s) {
 }
 void launch_gather_cols(const double* A, int n, int64_t ng, const int32_t* piv, double* AC, hipStream_t s) {
   hipLaunchKernelGGL(k_gather_cols, dim3(grid_for(int64_t(n) * n, 256)), dim3(256), 0, s, A, n, ng, piv, AC);
-}
-void launch_scale_inf(double* X, const double* G, int n, hipStream_t s) {
-  hipLaunchKernelGGL(k_scale_inf, dim3(1), dim3(1024), 0, s, X, G, n);
-}
-void launch_ns_combine(const double* X, const double* Z, double* Y, int64_t cnt, hipStream_t s) {
-  hipLaunchKernelGGL(k_ns_combine, dim3(grid_for(cnt, 256)), dim3(256), 0, s, X, Z, Y, cnt);
-}
-void launch_dev_identity(const double* G, int n, double* out, hipStream_t s) {
-  hipLaunchKernelGGL(k_dev_identity, dim3(1), dim3(1024), 0, s, G, n, out);
 }
 void launch_compact_pairs(const double* O, int n, double rho_cut, int64_t cap, int32_t* pairs, double* ov,
                           int64_t* count, hipStream_t s) {
