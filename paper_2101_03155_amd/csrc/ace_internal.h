@@ -125,7 +125,8 @@ hipError_t gemm_nt(int prec, int op, const void* A, int64_t lda, const void* B, 
 // Split count of gemm_nt; the default (sym = true) is the largest count any
 // product of this shape uses, for sizing the partial-sum buffer.  max_split > 0
 // caps the count (K is then cut into longer chunks).
-int64_t gemm_nt_nsplit(int M, int Nn, int64_t K, int64_t* kchunk_out, bool sym = true, int64_t max_split = 0);
+int64_t gemm_nt_nsplit(int M, int Nn, int64_t K, int64_t* kchunk_out, bool sym = true, int64_t max_split = 0,
+                       int prec = 0);
 hipError_t gemm_ls(int bprec, bool trans, bool lower, const double* S, int lds, const void* B, int64_t ldb,
                    double* C, int64_t ldc, int M, int K, int64_t R, double alpha, hipStream_t s,
                    EventRecorder* rec);
@@ -164,6 +165,11 @@ void launch_qrcp_select(const double* A, int n, int64_t ng, int* kdev, const dou
 int pool_blocks(int64_t ng);
 void launch_pool_build(const double* res, int64_t ng, int pmax, unsigned* hist, double* t, int64_t* cnt,
                        double* tmax, int* total, double* t_out, hipStream_t s);
+// In one launch where pool_fits_one: the threshold t, the pool and its residuals,
+// iv = {0 if first, 0, size}, and the largest residual outside it (t_out).
+bool pool_fits_one(int64_t ng);
+void launch_pool_small(const double* res, int64_t ng, int pmax, bool first, double* t, int* iv, double* t_out,
+                       int32_t* pool, double* pres, hipStream_t s);
 void launch_pool_write(const double* res, int64_t ng, const double* t, const int64_t* off, int32_t* pool,
                        double* pres, hipStream_t s);
 void launch_pool_gather(const double* A, int n, int64_t ng, const int32_t* pool, int np, double* Apool,

@@ -675,7 +675,8 @@ int ace_localize(ace_ctx* c, const ace_grid* g, int norb, const double* psi, dou
   // took 4.5: the localization went from 13.2 to 10.3 ms).  Residual norms only decrease, so every stored
   // bound stays valid until it is recomputed.
   launch_colnorm(psi, norb, ng, ng, res, s);
-  HIPCHK(c, hipMemsetAsync(iv, 0, 64, s));
+  const bool one = pool_fits_one(ng);
+  if (!one) HIPCHK(c, hipMemsetAsync(iv, 0, 64, s));
   // algorithmic bytes of one pool step per pool column: R read and written, residual read and written
   const double qbytes_pool = double(2 * norb + 2) * sizeof(double);
   // res[r] = |a_r|^2 - |Q_k a_r|^2 over w columns at a (pitch ld), by blocks of
@@ -719,15 +720,19 @@ int ace_localize(ace_ctx* c, const ace_grid* g, int norb, const double* psi, dou
     bool use_pool = refresh < 16;
     int np = 0;
     if (use_pool) {
-      HIPCHK(c, hipMemsetAsync(hist, 0, size_t(1 << 14) * sizeof(unsigned), s));
-      launch_pool_build(res, ng, pmax, hist, tvals, pcnt, tmax, iv + 2, tvals + 1, s);
+      if (one) {
+        launch_pool_small(res, ng, pmax, k == 0, tvals, iv, tvals + 1, pool, pres, s);
+      } else {
+        HIPCHK(c, hipMemsetAsync(hist, 0, size_t(1 << 14) * sizeof(unsigned), s));
+        launch_pool_build(res, ng, pmax, hist, tvals, pcnt, tmax, iv + 2, tvals + 1, s);
+      }
       HIPCHK(c, hipMemcpyAsync(&np, iv + 2, sizeof(int), hipMemcpyDeviceToHost, s));
       HIPCHK(c, hipStreamSynchronize(s));
       use_pool = np > 0 && np <= pmax;
     }
-    HIPCHK(c, hipMemsetAsync(iv + 1, 0, sizeof(int), s));  // clear stop
+    if (!one || !use_pool) HIPCHK(c, hipMemsetAsync(iv + 1, 0, sizeof(int), s));  // clear stop
     if (use_pool) {
-      launch_pool_write(res, ng, tvals, pcnt, pool, pres, s);
+      if (!one) launch_pool_write(res, ng, tvals, pcnt, pool, pres, s);
       launch_pool_gather(psi, norb, ng, pool, np, Apool, s);
       // the pool holds explicit residual columns R = (I - Q^T Q) A_pool:
       // project out the k directions already taken, twice for accuracy

@@ -692,23 +692,25 @@ hipError_t refresh_bounds(const double* Q, int ldq, const double* Psi, int64_t l
 
 // ---------------------------------------------------------------- host wrappers
 
-int64_t gemm_nt_nsplit(int M, int Nn, int64_t K, int64_t* kchunk_out, bool sym, int64_t max_split) {
+int64_t gemm_nt_nsplit(int M, int Nn, int64_t K, int64_t* kchunk_out, bool sym, int64_t max_split, int prec) {
   // about 512 workgroups (two per CU) over the 128 x 128 tiles that are
   // computed (the upper triangle only for a symmetric product), K chunks a
-  // multiple of 256 (the compensated FP32 sub-chunk).  With sym = true for a
-  // square product the count is the larger of the two cases, which is what
+  // multiple of 256 in FP32 (the compensated sub-chunk) and of 64 in FP64: a
+  // workgroup is a chain of steps of 16, and 8 orbitals on 24^3 (54 chunks of
+  // 256) took 18 us, with 216 of 64 it is 7.  With sym = true for a square
+  // product and prec = 0 the count is the largest of all cases, which is what
   // partial-sum buffers are sized for.
   const int64_t tm = (M + TT - 1) / TT, tn = (Nn + TT - 1) / TT;
   const int64_t tiles = (sym && M == Nn) ? tm * (tm + 1) / 2 : tm * tn;
   const int64_t want = (512 + tiles - 1) / tiles;
-  int64_t kchunk = (K + want - 1) / want;
-  kchunk = ((kchunk + 255) / 256) * 256;
-  if (kchunk < 256) kchunk = 256;
+  // (from 256 on the multiple stays 256: 64 would only move the boundaries)
+  const auto chunk = [&](int64_t parts) {
+    const int64_t k = (K + parts - 1) / parts, g = prec == 0 && k <= 192 ? 64 : 256;
+    return (k + g - 1) / g * g;
+  };
+  int64_t kchunk = chunk(want);
   // a caller with a fixed partial-sum buffer caps the split count: longer chunks
-  if (max_split > 0 && (K + kchunk - 1) / kchunk > max_split) {
-    kchunk = (K + max_split - 1) / max_split;
-    kchunk = ((kchunk + 255) / 256) * 256;
-  }
+  if (max_split > 0 && (K + kchunk - 1) / kchunk > max_split) kchunk = chunk(max_split);
   const int64_t nsplit = (K + kchunk - 1) / kchunk;
   *kchunk_out = kchunk;
   return nsplit;
@@ -719,7 +721,7 @@ hipError_t gemm_nt(int prec, int op, const void* A, int64_t lda, const void* B, 
                    EventRecorder* rec, bool sym, int64_t max_split) {
   int64_t kchunk;
   sym = sym && prec == 0 && M == Nn && A == B && lda == ldb;
-  const int64_t nsplit = gemm_nt_nsplit(M, Nn, K, &kchunk, sym, max_split);
+  const int64_t nsplit = gemm_nt_nsplit(M, Nn, K, &kchunk, sym, max_split, prec);
   rec_begin(rec, KC_GEMM_NT, s);
   const int64_t mn = int64_t(M) * Nn;
   const unsigned nbr = unsigned((mn + RO - 1) / RO);

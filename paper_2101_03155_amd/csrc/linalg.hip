@@ -1031,9 +1031,8 @@ __global__ __launch_bounds__(256) void k_res_hist(const double* __restrict__ res
 }
 
 // Lowest bin b such that the columns in bins >= b number at most pmax;
-// t = lower edge of bin b (as a double).
-__global__ __launch_bounds__(1024) void k_pool_threshold(const unsigned* __restrict__ hist, int pmax,
-                                                         double* __restrict__ t) {
+// returns the lower edge of bin b (as a double) in every thread of 1024.
+__device__ __forceinline__ double pool_edge(const unsigned* __restrict__ hist, int pmax) {
   constexpr int SEG = HBIN / 1024;
   __shared__ unsigned long long above[1024];
   __shared__ int tb;
@@ -1063,7 +1062,83 @@ __global__ __launch_bounds__(1024) void k_pool_threshold(const unsigned* __restr
   }
   __syncthreads();
   // tb == HBIN: not even the top bin fits; an infinite threshold empties the pool
-  if (threadIdx.x == 0) t[0] = tb >= HBIN ? INFINITY : __longlong_as_double((long long)tb << 49);
+  return tb >= HBIN ? INFINITY : __longlong_as_double((long long)tb << 49);
+}
+
+__global__ __launch_bounds__(1024) void k_pool_threshold(const unsigned* __restrict__ hist, int pmax,
+                                                         double* __restrict__ t) {
+  const double e = pool_edge(hist, pmax);
+  if (threadIdx.x == 0) t[0] = e;
+}
+
+// The whole pool of a small grid in one workgroup: histogram, threshold, count
+// and ordered list, as the five kernels of larger grids (whose launches took
+// 33 us at 24^3, this 15).  Clears iv[1], and iv[0] with first.
+// The chunk of a wave is a stretch of columns, so its list positions follow from
+// the counts of the waves before it.
+constexpr int64_t POOL_SMALL = 65536;
+__global__ __launch_bounds__(1024) void k_pool_small(const double* __restrict__ res, int ng, int pmax, int first,
+                                                     double* __restrict__ t, int* __restrict__ iv,
+                                                     double* __restrict__ t_out, int32_t* __restrict__ pool,
+                                                     double* __restrict__ pres) {
+  __shared__ unsigned hist[HBIN];
+  __shared__ int wcnt[16];
+  __shared__ double wmax[16];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  for (int i = tid; i < HBIN; i += 1024) hist[i] = 0u;
+  __syncthreads();
+#pragma unroll 4
+  for (int r = tid; r < ng; r += 1024) {
+    const double v = res[r];
+    if (v > 0.0) atomicAdd(&hist[res_bin(v)], 1u);
+  }
+  __syncthreads();
+  const double th = pool_edge(hist, pmax);
+  const int len = (ng + 1023) / 1024 * 64, r0 = wv * len, r1 = r0 + len < ng ? r0 + len : ng;
+  int c = 0;
+  double m = 0.0;
+#pragma unroll 4
+  for (int r = r0 + lane; r < r1; r += 64) {
+    const double v = res[r];
+    if (v >= th && v > 0.0) ++c;
+    else if (v > 0.0 && v > m) m = v;
+  }
+  for (int off = 32; off > 0; off >>= 1) {
+    c += __shfl_down(c, off, 64);
+    m = fmax(m, __shfl_down(m, off, 64));
+  }
+  if (lane == 0) {
+    wcnt[wv] = c;
+    wmax[wv] = m;
+  }
+  __syncthreads();
+  int off = 0, total = 0;
+  for (int w = 0; w < 16; ++w) {
+    if (w < wv) off += wcnt[w];
+    total += wcnt[w];
+  }
+  if (tid == 0) {
+    for (int w = 0; w < 16; ++w) m = fmax(m, wmax[w]);
+    t[0] = th;
+    t_out[0] = m;
+    if (first) iv[0] = 0;
+    iv[1] = 0;
+    iv[2] = total;
+  }
+  if (total > pmax) return;  // (the caller then takes the whole grid)
+#pragma unroll 4
+  for (int g = r0; g < r1; g += 64) {
+    const int r = g + lane;
+    const double v = r < r1 ? res[r] : 0.0;
+    const bool keep = v >= th && v > 0.0;
+    const unsigned long long bal = __ballot(keep);
+    if (keep) {
+      const int p = off + __popcll(bal & ((1ull << lane) - 1ull));
+      pool[p] = r;
+      pres[p] = v;
+    }
+    off += __popcll(bal);
+  }
 }
 
 // Per block (contiguous chunk of columns): count of res >= t, max of 0 < res < t.
@@ -1344,6 +1419,12 @@ void launch_pool_build(const double* res, int64_t ng, int pmax, unsigned* hist, 
   hipLaunchKernelGGL(k_res_hist, dim3(grid_for(ng, 256, 1024)), dim3(256), 0, s, res, ng, hist);
   hipLaunchKernelGGL(k_pool_threshold, dim3(1), dim3(1024), 0, s, hist, pmax, t);
   launch_count_above(res, ng, t, cnt, tmax, total, t_out, s);
+}
+bool pool_fits_one(int64_t ng) { return ng <= POOL_SMALL; }
+void launch_pool_small(const double* res, int64_t ng, int pmax, bool first, double* t, int* iv, double* t_out,
+                       int32_t* pool, double* pres, hipStream_t s) {
+  hipLaunchKernelGGL(k_pool_small, dim3(1), dim3(1024), 0, s, res, int(ng), pmax, first ? 1 : 0, t, iv, t_out, pool,
+                     pres);
 }
 void launch_pool_write(const double* res, int64_t ng, const double* t, const int64_t* off, int32_t* pool,
                        double* pres, hipStream_t s) {
