@@ -116,6 +116,10 @@ struct Schedule {
   // graph, so that the owners in flight together are neighbours and read the
   // same partner rows and spectra; each owner's entries follow it too
   std::vector<int32_t> operm;
+  // the owner tables as one upload: opacks, adj_ptr, adj, operm, and last opidx
+  // (read for pair energies only), each at a multiple of 16 bytes
+  std::vector<char> table;
+  size_t adjp_off = 0, adj_off = 0, operm_off = 0, pidx_off = 0;
 };
 
 struct ace_ctx {
@@ -414,9 +418,23 @@ static void make_owner_schedule(const std::vector<int32_t>& pr, int64_t npairs, 
   }
 }
 
+static void make_owner_table(Schedule& S) {
+  auto add = [&S](const void* p, size_t bytes) {
+    const size_t at = (S.table.size() + 15) / 16 * 16;
+    S.table.resize(at + bytes);
+    if (bytes) std::memcpy(S.table.data() + at, p, bytes);
+    return at;
+  };
+  add(S.opacks.data(), S.opacks.size() * sizeof(Pack));
+  S.adjp_off = add(S.adj_ptr.data(), S.adj_ptr.size() * sizeof(int32_t));
+  S.adj_off = add(S.adj.data(), S.adj.size() * sizeof(int32_t));
+  S.operm_off = add(S.operm.data(), S.operm.size() * sizeof(int32_t));
+  S.pidx_off = add(S.opidx.data(), S.opidx.size() * sizeof(int64_t));
+}
 
+// The rounds (packs, launches) are formed only for callers that launch them.
 static int schedule_for(ace_ctx* c, const std::vector<int32_t>& pr, int64_t npairs, int norb, int max_packs,
-                        std::shared_ptr<const Schedule>* out) {
+                        bool rounds, std::shared_ptr<const Schedule>* out) {
   uint64_t h = 1469598103934665603ull;
   std::vector<uint8_t> seen(size_t(norb) * norb, 0);
   for (int64_t p = 0; p < npairs; ++p) {
@@ -432,9 +450,14 @@ static int schedule_for(ace_ctx* c, const std::vector<int32_t>& pr, int64_t npai
   if (sit == c->schedules.end()) {
     if (c->schedules.size() > 64) c->schedules.clear();
     auto S = std::make_shared<Schedule>();
-    make_schedule(pr, npairs, norb, max_packs, *S);
     make_owner_schedule(pr, npairs, norb, *S);
+    make_owner_table(*S);
     sit = c->schedules.emplace(key, std::move(S)).first;
+  }
+  if (rounds && sit->second->packs.empty()) {
+    auto S = std::make_shared<Schedule>(*sit->second);  // (others may hold the one without)
+    make_schedule(pr, npairs, norb, max_packs, *S);
+    sit->second = std::move(S);
   }
   *out = sit->second;
   return ACE_OK;
@@ -1055,18 +1078,10 @@ static int build_impl(ace_ctx* c, const ace_grid* g, int norb, const double* phi
   std::vector<int32_t> pr(size_t(2 * npairs));
   HIPCHK(c, hipMemcpyAsync(pr.data(), pairs, pr.size() * sizeof(int32_t), hipMemcpyDeviceToHost, s));
   HIPCHK(c, hipStreamSynchronize(s));
-  const int mp = max_packs_for(c, prec, N);
-  std::shared_ptr<const Schedule> Sp;
-  rc = schedule_for(c, pr, npairs, norb, mp, &Sp);
-  if (rc) return rc;
-  const Schedule& S = *Sp;
-  const int npk = int(S.packs.size());
-  rec_begin(R, ST_BUILD, s);
-
   const size_t es = prec == 0 ? sizeof(double) : sizeof(float);
   PairShape sh = shape_for(c, prec, N);
   // owner-computes W when every pair's half spectrum fits the budget
-  const int64_t onpk = int64_t(S.opacks.size());
+  const int64_t onpk = (npairs + 1) / 2;
   const size_t slot_bytes = pair_owner_slot_elems(prec, N) * 2 * es;
   // ... and when the spectra, beyond what the workspace already holds, take
   // at most 60% of the free device memory (a fuller device slows down)
@@ -1079,6 +1094,14 @@ static int build_impl(ace_ctx* c, const ace_grid* g, int norb, const double* phi
     if (need > have && hipMemGetInfo(&freeb, &totb) == hipSuccess)
       owner = double(need) <= 0.6 * double(freeb + have);
   }
+  const int mp = max_packs_for(c, prec, N);
+  std::shared_ptr<const Schedule> Sp;
+  rc = schedule_for(c, pr, npairs, norb, mp, !owner, &Sp);
+  if (rc) return rc;
+  const Schedule& S = *Sp;
+  const int npk = int(S.packs.size());
+  rec_begin(R, ST_BUILD, s);
+
   if (!owner) sh = pair_rounds_shape(prec, N, sh);
   const int nblk = owner ? pair_owner_ntile(prec, N) : pair_energy_blocks(N, sh);
   void *W, *spec, *phiw;
@@ -1094,11 +1117,13 @@ static int build_impl(ace_ctx* c, const ace_grid* g, int norb, const double* phi
   else W = Wout;
   if (owner) {
     WS(c, "spec", size_t(2 * onpk) * slot_bytes, spec);
-    WS(c, "packs", size_t(onpk) * sizeof(Pack), dpk);
-    WS(c, "pidx", size_t(onpk) * 2 * sizeof(int64_t), dpidx);
-    WS(c, "adjp", S.adj_ptr.size() * sizeof(int32_t), dadjp);
-    WS(c, "adj", std::max<size_t>(S.adj.size(), 2) * sizeof(int32_t), dadj);
-    WS(c, "operm", size_t(norb) * sizeof(int32_t), doperm);
+    char* tab;
+    WS(c, "otab", S.table.size(), tab);
+    dpk = reinterpret_cast<Pack*>(tab);
+    dadjp = reinterpret_cast<int32_t*>(tab + S.adjp_off);
+    dadj = reinterpret_cast<int32_t*>(tab + S.adj_off);
+    doperm = reinterpret_cast<int32_t*>(tab + S.operm_off);
+    dpidx = reinterpret_cast<int64_t*>(tab + S.pidx_off);
     if (pair_energy) WS(c, "epart", size_t(onpk) * nblk * 2 * sizeof(double), epart);
     WS(c, "vtab", size_t(N / 2 + 1) * (N / 2 + 1) * (N / 2 + 1) * es, vtab);
   } else {
@@ -1124,12 +1149,8 @@ static int build_impl(ace_ctx* c, const ace_grid* g, int norb, const double* phi
   if (rc) return rc;
 
   if (owner) {
-    HIPCHK(c, hipMemcpyAsync(dpk, S.opacks.data(), size_t(onpk) * sizeof(Pack), hipMemcpyHostToDevice, s));
-    HIPCHK(c, hipMemcpyAsync(dpidx, S.opidx.data(), size_t(onpk) * 2 * sizeof(int64_t), hipMemcpyHostToDevice, s));
-    HIPCHK(c, hipMemcpyAsync(dadjp, S.adj_ptr.data(), S.adj_ptr.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
-    if (!S.adj.empty())
-      HIPCHK(c, hipMemcpyAsync(dadj, S.adj.data(), S.adj.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
-    HIPCHK(c, hipMemcpyAsync(doperm, S.operm.data(), size_t(norb) * sizeof(int32_t), hipMemcpyHostToDevice, s));
+    // one copy (five of them took some 50 us of a small build)
+    HIPCHK(c, hipMemcpyAsync(dpk, S.table.data(), pair_energy ? S.table.size() : S.pidx_off, hipMemcpyHostToDevice, s));
   } else {
     HIPCHK(c, hipMemcpyAsync(dpk, S.packs.data(), size_t(npk) * sizeof(Pack), hipMemcpyHostToDevice, s));
     HIPCHK(c, hipMemcpyAsync(dpidx, S.pidx.data(), size_t(npk) * 2 * sizeof(int64_t), hipMemcpyHostToDevice, s));
@@ -1381,9 +1402,8 @@ int ace_build_kpoints(ace_ctx* c, const ace_grid* g, int norb, int nk, const dou
   HIPCHK(c, hipMemcpyAsync(pr.data(), pairs, pr.size() * sizeof(int32_t), hipMemcpyDeviceToHost, s));
   HIPCHK(c, hipStreamSynchronize(s));
   std::shared_ptr<const Schedule> Sp;
-  rc = schedule_for(c, pr, npairs, ntot, 16, &Sp);
+  rc = schedule_for(c, pr, npairs, ntot, 16, false, &Sp);
   if (rc) return rc;
-  const Schedule& S = *Sp;
   const void* tw;
   rc = twiddles(c, N, 0, &tw);
   if (rc) return rc;
@@ -1421,6 +1441,7 @@ int ace_build_kpoints(ace_ctx* c, const ace_grid* g, int norb, int nk, const dou
   if (chunk > 0) {
     // owner-computes, the spectra of `chunk` pairs resident at a time; the
     // entries of a chunk are the schedule's, in its order, by chunk-local slot
+    const Schedule& S = *Sp;
     std::vector<KPair> slots(static_cast<size_t>(npairs));
     for (int64_t p = 0; p < npairs; ++p) slots[size_t(p)] = slot_of(pr[size_t(2 * p)], pr[size_t(2 * p + 1)]);
     const int64_t nchunk = (npairs + chunk - 1) / chunk;
@@ -1458,6 +1479,9 @@ int ace_build_kpoints(ace_ctx* c, const ace_grid* g, int norb, int nk, const dou
   } else {
     // conflict-free launches of the split passes, one slot per pair of every
     // pack, in the schedule's order
+    rc = schedule_for(c, pr, npairs, ntot, 16, true, &Sp);
+    if (rc) return rc;
+    const Schedule& S = *Sp;
     std::vector<KPair> slots(2 * S.packs.size());
     for (size_t p = 0; p < S.packs.size(); ++p) {
       slots[2 * p] = slot_of(S.packs[p].ia, S.packs[p].ja);
@@ -1584,7 +1608,7 @@ int ace_build_batched(ace_ctx* c, int nsys, ace_system* sys, int prec, int mode)
   mix(uint64_t(c->b_layout));
   int nrounds = 0;
   for (int q = 0; q < nsys; ++q) {
-    int rc = schedule_for(c, prs[q], sys[q].npairs, sys[q].norb, 1 << 30, &sch[q]);
+    int rc = schedule_for(c, prs[q], sys[q].npairs, sys[q].norb, 1 << 30, true, &sch[q]);
     if (rc) return fail(c, rc, "system %d: %s", q, c->err.c_str());
     nrounds = std::max(nrounds, int(sch[q]->round_first.size()));
     const ace_system& y = sys[q];
