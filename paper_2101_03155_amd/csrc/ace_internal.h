@@ -136,13 +136,12 @@ hipError_t refresh_bounds(const double* Q, int ldq, const double* Psi, int64_t l
                           double* res, hipStream_t s);
 void launch_symmetrize(const double* M, int n, double* out, double* negM, double* ex, double* asym, hipStream_t s);
 void launch_neg_sumsq(const double* c, int64_t n, double* out, hipStream_t s);
-// Blocked Cholesky of the lower triangle of A (n <= 512) in place; info must
-// be zero on entry; tinv is 64 x 64 doubles of scratch.
-void launch_cholesky(double* A, int n, int* info, double* tinv, hipStream_t s);
-void launch_trinv(const double* L, int n, double* X, hipStream_t s);
-// -A = L L^T and X = L^-1 (zeros above the diagonal); info zero on entry, set
-// as by launch_cholesky.  A holds L afterwards only where n > 128.
-void launch_chol_inv(double* A, int n, int* info, double* X, double* tinv, hipStream_t s);
+// Cholesky of the lower triangle of A (n <= 512) in place; info must be zero on
+// entry; X is n x n doubles of scratch where n > 128.
+void launch_cholesky(double* A, int n, int* info, double* X, hipStream_t s);
+// X = L^-1 of A = L L^T (zeros above the diagonal); info zero on entry, set as by
+// launch_cholesky.  A is overwritten.
+void launch_chol_inv(double* A, int n, int* info, double* X, hipStream_t s);
 void launch_colnorm(const double* A, int n, int64_t ld, int64_t ng, double* res, hipStream_t s);
 int qrcp_blocks(int64_t ng);
 void launch_qrcp_update(const double* A, int n, int64_t ng, const double* q, double* res, double* pv, int64_t* pi,

@@ -674,7 +674,7 @@ int ace_localize(ace_ctx* c, const ace_grid* g, int norb, const double* psi, dou
   WS(c, "G", size_t(norb) * norb * sizeof(double), G);
   WS(c, "Z", size_t(norb) * norb * sizeof(double), Z);
   WS(c, "U", size_t(norb) * norb * sizeof(double), Ub);
-  WS(c, "nsred", size_t(polar_tiles(norb) + norb) * sizeof(double), red);
+  WS(c, "nsred", size_t(polar_tiles(norb) + norb + 3) * sizeof(double), red);
   WS(c, "pres", size_t(pmax) * sizeof(double), pres);
   WS(c, "pool", size_t(pmax) * sizeof(int32_t), pool);
   WS(c, "Apool", size_t(pmax) * norb * sizeof(double), Apool);
@@ -855,7 +855,7 @@ int ace_localize_pivots(ace_ctx* c, const ace_grid* g, int norb, const double* p
   WS(c, "X", size_t(norb) * norb * sizeof(double), X);
   WS(c, "G", size_t(norb) * norb * sizeof(double), G);
   WS(c, "Z", size_t(norb) * norb * sizeof(double), Z);
-  WS(c, "nsred", size_t(polar_tiles(norb) + norb) * sizeof(double), red);
+  WS(c, "nsred", size_t(polar_tiles(norb) + norb + 3) * sizeof(double), red);
   rc = lowdin(c, norb, ng, psi, pivots, X, G, Z, red, phi, U);
   if (rc) return rc;
   rec_end(c->R(), ST_LOCALIZE, s);
@@ -887,19 +887,20 @@ int ace_localize_step(ace_ctx* c, const ace_grid* g, int norb, const double* psi
   // factor of A_C^T A_C taken in pivot order is R^T of the QR factorization
   // of A_C, so (max_k R_kk / min_k R_kk)^2 is the diagonal ratio greedy
   // pivoting keeps small, and a lower bound on the condition number.
-  double *AC, *G, *tinv;
+  double *AC, *G, *X, *red;
   int* dinfo;
   WS(c, "AC", size_t(norb) * norb * sizeof(double), AC);
   WS(c, "G", size_t(norb) * norb * sizeof(double), G);
-  WS(c, "tinv", 64 * 64 * sizeof(double), tinv);
+  WS(c, "X", size_t(norb) * norb * sizeof(double), X);
+  WS(c, "nsred", size_t(polar_tiles(norb) + norb + 3) * sizeof(double), red);
   WS(c, "info", 64, dinfo);
   launch_gather_cols(psi, norb, ng, pivots, AC, s);
   HIPCHK(c, gemm_ls(0, true, false, AC, norb, AC, norb, G, norb, norb, norb, norb, 1.0, s, nullptr));
   launch_zero(dinfo, sizeof(int), s);
-  launch_cholesky(G, norb, dinfo, tinv, s);
-  launch_diag_range(G, norb, dinfo, tinv, s);
+  launch_cholesky(G, norb, dinfo, X, s);
+  launch_diag_range(G, norb, dinfo, red, s);
   double hd[3] = {0.0, 0.0, 0.0};
-  HIPCHK(c, hipMemcpyAsync(hd, tinv, sizeof(hd), hipMemcpyDeviceToHost, s));
+  HIPCHK(c, hipMemcpyAsync(hd, red, sizeof(hd), hipMemcpyDeviceToHost, s));
   HIPCHK(c, hipStreamSynchronize(s));
   const double dmax = hd[0], dmin = hd[1];
   const int hinfo = int(hd[2]);
@@ -908,10 +909,8 @@ int ace_localize_step(ace_ctx* c, const ace_grid* g, int norb, const double* psi
   info->pairs_added = info->pairs_removed = 0;
   if (cond <= cond_max) {
     info->reused_columns = 1;
-    double *X, *Z, *red;
-    WS(c, "X", size_t(norb) * norb * sizeof(double), X);
+    double* Z;
     WS(c, "Z", size_t(norb) * norb * sizeof(double), Z);
-    WS(c, "nsred", size_t(polar_tiles(norb) + norb) * sizeof(double), red);
     rc = lowdin(c, norb, ng, psi, pivots, X, G, Z, red, phi, U);
     if (rc != ACE_E_NONFINITE) return rc;
     c->err.clear();  // the polar iteration failed on these columns: fresh SCDM below
@@ -1140,8 +1139,6 @@ static int build_impl(ace_ctx* c, const ace_grid* g, int norb, const double* phi
   WS(c, "Linv", size_t(norb) * norb * sizeof(double), Li);
   WS(c, "scal", 64 * sizeof(double), scal);
   WS(c, "info", 64, info);
-  double* tinv;
-  WS(c, "tinv", 64 * 64 * sizeof(double), tinv);
   if (prec == 1) WS(c, "phi32", size_t(norb) * ng * sizeof(float), phiw);
   else phiw = (void*)phi;
   const void* tw;
@@ -1204,7 +1201,7 @@ static int build_impl(ace_ctx* c, const ace_grid* g, int norb, const double* phi
     return ACE_OK;
   }
   launch_zero(info, sizeof(int), s);
-  launch_chol_inv(Lb, norb, info, Li, tinv, s);
+  launch_chol_inv(Lb, norb, info, Li, s);
   // (e) xi = L^-1 W; the factorization's status is read once, after it (on
   // failure the outputs are unspecified)
   HIPCHK(c, gemm_ls(prec, false, true, Li, norb, W, ng, xi, ng, norb, norb, ng, 1.0, s, R));
@@ -1814,8 +1811,6 @@ int ace_build_batched(ace_ctx* c, int nsys, ace_system* sys, int prec, int mode)
   WS(c, "bLinv", NBR * mat_elems * sizeof(double), Li);
   WS(c, "bex", size_t(nsys) * 2 * sizeof(double), exs);
   WS(c, "binfo", size_t(nsys) * sizeof(int), infos);
-  double* btinv;
-  WS(c, "btinv", NBR * 64 * 64 * sizeof(double), btinv);
   WS(c, "bsys", size_t(nsys) * sizeof(BSys), dsys);
   WS(c, "bpacks", std::max<size_t>(bp.size(), 1) * sizeof(BPack), dbp);
   WS(c, "bsegs", std::max<size_t>(segs.size(), 1) * sizeof(BRound), dsegs);
@@ -1905,7 +1900,6 @@ int ace_build_batched(ace_ctx* c, int nsys, ace_system* sys, int prec, int mode)
       double* bM = Mraw + br * mat_elems;
       double* bL = Lb + br * mat_elems;
       double* bLi = Li + br * mat_elems;
-      double* btv = btinv + br * 64 * 64;
       const ace_system& y = sys[q];
       const int n = y.norb;
       const int64_t ng = grid_size(&y.grid);
@@ -1914,7 +1908,7 @@ int ace_build_batched(ace_ctx* c, int nsys, ace_system* sys, int prec, int mode)
       hipError_t e = gemm_nt(prec, 0, ph, ng, W, ng, n, n, ng, grid_dv(&y.grid), bpart, bM, sb, nullptr);
       if (e != hipSuccess) return fail(c, ACE_E_HIP, "batched M launch failed: %s", hipGetErrorString(e));
       launch_symmetrize(bM, n, y.M, bL, y.ex ? y.ex : exs + 2 * q, exs + 2 * q + 1, sb);
-      launch_chol_inv(bL, n, infos + q, bLi, btv, sb);
+      launch_chol_inv(bL, n, infos + q, bLi, sb);
       e = gemm_ls(prec, false, true, bLi, n, W, ng, y.xi, ng, n, n, ng, 1.0, sb, nullptr);
       if (e != hipSuccess) return fail(c, ACE_E_HIP, "batched projector launch failed: %s", hipGetErrorString(e));
     }

@@ -1,6 +1,5 @@
 // Small dense kernels around the ACE build and the localization:
 //   * symmetrization, trace and sign flip of M (Appendix A: -M = L L^T);
-//   * FP64 Cholesky and triangular inverse of the N_orb x N_orb factor;
 //   * the column-pivoted QR pivot search of the SCDM localization;
 //   * screening-pair compaction; pair-energy reduction; conversions.
 #include <hip/hip_runtime.h>
@@ -42,359 +41,6 @@ __global__ void k_symmetrize(const double* __restrict__ M, int n, double* __rest
   }
 }
 
-
-// ---------------------------------------------------------------- blocked Cholesky
-// -M = L L^T for n <= 512, right-looking over panels of CB = 64 columns:
-//   diagonal block: factor in LDS and form its inverse (one workgroup);
-//   panel:          L21 = A21 L11^-T (rows below the block);
-//   update:         A22 -= L21 L21^T (lower 64 x 64 tiles of the trailing matrix).
-// Only the lower triangle is read; the strict upper triangle is zeroed.  info
-// = k + 1 when the pivot of column k is not positive, -(k + 1) when it is not
-// finite; every kernel returns at once when info is already set.
-constexpr int CB = 64;
-
-__global__ __launch_bounds__(256) void k_chol_diag(double* __restrict__ A, int n, int k0,
-                                                   double* __restrict__ Tinv, int* __restrict__ info) {
-  __shared__ double D[CB][CB + 1];
-  __shared__ double X[CB][CB + 1];
-  __shared__ double col[2][CB];
-  if (*info) return;
-  const int b = (n - k0 < CB) ? n - k0 : CB;
-  const int tid = threadIdx.x;
-  // thread (tr, tc) owns rows 4 tr .. 4 tr + 3 and columns 4 tc .. 4 tc + 3,
-  // kept in registers during the elimination
-  const int r0 = (tid >> 4) * 4, c0 = (tid & 15) * 4;
-  double v[4][4];
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int i = r0 + a, j = c0 + q;
-      v[a][q] = (i < b && j <= i) ? A[int64_t(k0 + i) * n + k0 + j] : 0.0;
-    }
-  // a_ij -= a_ik a_jk / a_kk on unscaled columns.  Column k is published by
-  // the threads that own it to an LDS vector (two alternating buffers, so one
-  // barrier per column suffices); every element sees the same updates in the
-  // same order as an in-place elimination.
-  int bad = 0;
-  for (int k = 0; k < b; ++k) {
-    double* ck = col[k & 1];
-    if ((tid & 15) == (k >> 2)) {
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          if (q == (k & 3)) ck[r0 + a] = v[a][q];
-    }
-    __syncthreads();
-    const double d = ck[k];
-    if (!isfinite(d)) { bad = -(k0 + k + 1); break; }
-    if (!(d > 0.0)) { bad = k0 + k + 1; break; }
-    const double inv = 1.0 / d;
-    double li[4], lj[4];
-#pragma unroll
-    for (int a = 0; a < 4; ++a) { li[a] = ck[r0 + a] * inv; lj[a] = ck[c0 + a]; }
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int i = r0 + a, j = c0 + q;
-        if (j > k && j <= i) v[a][q] -= li[a] * lj[q];
-      }
-  }
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) D[r0 + a][c0 + q] = v[a][q];
-  __syncthreads();
-  if (bad) {
-    if (tid == 0) *info = bad;
-    return;
-  }
-  // scale: L[i][k] = a_ik / sqrt(a_kk) (zero above the diagonal and beyond b)
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int i = r0 + a, k = c0 + q;
-      X[i][k] = (i < b && k <= i) ? D[i][k] / sqrt(D[k][k]) : 0.0;
-    }
-  __syncthreads();
-#pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) D[r0 + a][c0 + q] = X[r0 + a][c0 + q];
-  __syncthreads();
-  // inverse by rows: X[i][c] = (delta_ic - sum_{c <= k < i} L[i][k] X[k][c]) / L[i][i],
-  // four lanes per column c, combined with shuffles.  Only the panel below
-  // the block reads it, so the last block skips it (uniform over the block).
-  const bool last = k0 + b >= n;
-  const int c = tid >> 2, part = tid & 3;
-  for (int i = 0; i < (last ? 0 : b); ++i) {
-    double acc = 0.0;
-    if (c < i)
-      for (int k = c + part; k < i; k += 4) acc += D[i][k] * X[k][c];
-    acc += __shfl_xor(acc, 1, 64);
-    acc += __shfl_xor(acc, 2, 64);
-    if (part == 0 && c < b) X[i][c] = (c > i) ? 0.0 : (((i == c) ? 1.0 : 0.0) - acc) / D[i][i];
-    __syncthreads();
-  }
-  for (int e = tid; e < b * b; e += 256) {
-    const int i = e / b, j = e % b;
-    A[int64_t(k0 + i) * n + k0 + j] = D[i][j];
-    if (!last) Tinv[i * CB + j] = X[i][j];
-  }
-  // the strict upper triangle right of the block
-  for (int e = tid; e < b * (n - k0 - b); e += 256) {
-    const int i = e / (n - k0 - b), j = k0 + b + e % (n - k0 - b);
-    A[int64_t(k0 + i) * n + j] = 0.0;
-  }
-}
-
-// Rows r0 .. r0 + 63 (below the block): L21[i][c] = sum_{d <= c} A21[i][d] Tinv[c][d].
-__global__ __launch_bounds__(256) void k_chol_panel(double* __restrict__ A, int n, int k0,
-                                                    const double* __restrict__ Tinv, const int* __restrict__ info) {
-  __shared__ double T[CB][CB + 1];
-  __shared__ double R[CB][CB + 1];
-  if (*info) return;
-  const int b = (n - k0 < CB) ? n - k0 : CB;
-  const int r0 = k0 + b + blockIdx.x * CB;
-  const int rows = (n - r0 < CB) ? n - r0 : CB;
-  const int tid = threadIdx.x;
-  for (int e = tid; e < CB * CB; e += 256) {
-    const int i = e / CB, j = e % CB;
-    T[i][j] = (i < b && j < b) ? Tinv[i * CB + j] : 0.0;
-    R[i][j] = (i < rows && j < b) ? A[int64_t(r0 + i) * n + k0 + j] : 0.0;
-  }
-  __syncthreads();
-  for (int e = tid; e < rows * b; e += 256) {
-    const int i = e / b, c = e % b;
-    double acc = 0.0;
-    for (int d = 0; d <= c; ++d) acc += R[i][d] * T[c][d];
-    A[int64_t(r0 + i) * n + k0 + c] = acc;
-  }
-}
-
-// Trailing update of the lower 64 x 64 tile (ti, tj), tj <= ti, of rows and
-// columns from k0 + b: A[i][j] -= sum_c L21[i][c] L21[j][c] for j <= i.
-__global__ __launch_bounds__(256) void k_chol_update(double* __restrict__ A, int n, int k0,
-                                                     const int* __restrict__ info) {
-  __shared__ double Li[CB][CB + 1];
-  __shared__ double Lj[CB][CB + 1];
-  if (*info) return;
-  const int b = (n - k0 < CB) ? n - k0 : CB;
-  const int base = k0 + b;
-  int t = blockIdx.x, ti = 0;
-  while (t > ti) { t -= ti + 1; ++ti; }
-  const int tj = t;
-  const int i0 = base + ti * CB, j0 = base + tj * CB;
-  const int ri = (n - i0 < CB) ? n - i0 : CB, rj = (n - j0 < CB) ? n - j0 : CB;
-  const int tid = threadIdx.x;
-  for (int e = tid; e < CB * CB; e += 256) {
-    const int r = e / CB, c = e % CB;
-    Li[r][c] = (r < ri && c < b) ? A[int64_t(i0 + r) * n + k0 + c] : 0.0;
-    Lj[r][c] = (r < rj && c < b) ? A[int64_t(j0 + r) * n + k0 + c] : 0.0;
-  }
-  __syncthreads();
-  for (int e = tid; e < ri * rj; e += 256) {
-    const int r = e / rj, q = e % rj;
-    if (j0 + q > i0 + r) continue;
-    double acc = 0.0;
-    for (int c = 0; c < b; ++c) acc += Li[r][c] * Lj[q][c];
-    A[int64_t(i0 + r) * n + j0 + q] -= acc;
-  }
-}
-
-// For n <= 128 the factorization and the inverse in one workgroup with the
-// matrix resident in LDS.  A (n x n, lower triangle read) = L L^T, X = L^-1
-// (lower triangular, zeros above the diagonal).  Right-looking over panels
-// of 16 columns: wave 0 factors a panel in registers (lane l holds panel
-// rows k0 + l and k0 + l + 64, the pivot column passed through LDS), then
-// all threads apply the panel to the trailing lower triangle in 4 x 4
-// blocks.  The inverse runs by 16-row block rows: the diagonal blocks'
-// inverses by substitution, one thread per column, then each block row from
-// the ones above it (all its blocks at once).  Both triangles sit packed in
-// LDS (row i at i (i + 1) / 2).  info as the blocked factorization: k + 1 for a
-// non-positive pivot in column k, -(k + 1) for a non-finite one.
-constexpr int SMALL_N = 128;
-__device__ __forceinline__ int pk(int i, int j) { return i * (i + 1) / 2 + j; }
-
-__global__ __launch_bounds__(1024) void k_chol_inv_small(const double* __restrict__ A, int n, int* __restrict__ info,
-                                                         double* __restrict__ X) {
-  constexpr int PB = 16, NP = SMALL_N * (SMALL_N + 1) / 2;
-  __shared__ double S[NP];
-  __shared__ double XP[NP];
-  __shared__ double T[(SMALL_N / 16 - 1) * 256];
-  __shared__ double pc[17];
-  __shared__ int sbad;
-  const int tid = threadIdx.x, lane = tid & 63;
-  if (tid == 0) sbad = 0;
-  for (int e = tid; e < n * (n + 1) / 2; e += 1024) {
-    // row i of the packed triangle holds elements i (i + 1) / 2 .. + i
-    int i = int((sqrt(8.0 * e + 1.0) - 1.0) * 0.5);
-    while (i * (i + 1) / 2 > e) --i;
-    while ((i + 1) * (i + 2) / 2 <= e) ++i;
-    const int j = e - i * (i + 1) / 2;
-    S[e] = A[int64_t(i) * n + j];
-  }
-  __syncthreads();
-  for (int k0 = 0; k0 < n; k0 += PB) {
-    const int kb = n - k0 < PB ? n - k0 : PB;
-    if (tid < 64) {
-      const int r0 = k0 + lane, r1 = k0 + lane + 64;
-      double v0[PB], v1[PB];
-#pragma unroll
-      for (int jj = 0; jj < PB; ++jj) {
-        v0[jj] = (jj < kb && r0 < n && k0 + jj <= r0) ? S[pk(r0, k0 + jj)] : 0.0;
-        v1[jj] = (jj < kb && r1 < n && k0 + jj <= r1) ? S[pk(r1, k0 + jj)] : 0.0;
-      }
-      // the pivot and the scaled pivot column inside the panel reach the
-      // other lanes through pc[] (one wave: its LDS accesses run in order)
-      int bad = 0;
-#pragma unroll
-      for (int kk = 0; kk < PB; ++kk) {
-        if (kk < kb && !bad) {
-          const int k = k0 + kk;
-          if (lane == kk) pc[0] = v0[kk];
-          __builtin_amdgcn_wave_barrier();
-          const double d = pc[0];
-          if (!isfinite(d)) bad = -(k + 1);
-          else if (!(d > 0.0)) bad = k + 1;
-          if (!bad) {
-            const double r = sqrt(d), inv = 1.0 / r;
-            if (r0 > k) v0[kk] *= inv;
-            else if (r0 == k) v0[kk] = r;
-            if (r1 < n) v1[kk] *= inv;  // r1 >= k0 + 64 > k
-            if (lane > kk && lane < PB) pc[1 + lane] = v0[kk];  // L[k0 + lane][k]
-            __builtin_amdgcn_wave_barrier();
-#pragma unroll
-            for (int jj = kk + 1; jj < PB; ++jj) {
-              if (jj < kb) {
-                const double lj = pc[1 + jj];
-                if (r0 >= k0 + jj) v0[jj] -= v0[kk] * lj;
-                if (r1 < n) v1[jj] -= v1[kk] * lj;
-              }
-            }
-          }
-          __builtin_amdgcn_wave_barrier();
-        }
-      }
-#pragma unroll
-      for (int jj = 0; jj < PB; ++jj) {
-        if (jj < kb && r0 < n && k0 + jj <= r0) S[pk(r0, k0 + jj)] = v0[jj];
-        if (jj < kb && r1 < n) S[pk(r1, k0 + jj)] = v1[jj];
-      }
-      if (lane == 0 && bad) sbad = bad;
-    }
-    __syncthreads();
-    if (sbad) break;
-    // trailing update S[i][j] -= sum_kk L[i][k0 + kk] L[j][k0 + kk], k0 + kb <= j <= i < n
-    const int t0 = k0 + kb, nt = (n - t0 + 3) / 4;
-    for (int b = tid; b < nt * (nt + 1) / 2; b += 1024) {
-      int bi = int((sqrt(8.0 * b + 1.0) - 1.0) * 0.5);
-      while (bi * (bi + 1) / 2 > b) --bi;
-      while ((bi + 1) * (bi + 2) / 2 <= b) ++bi;
-      const int bj = b - bi * (bi + 1) / 2;
-      const int i0 = t0 + 4 * bi, j0 = t0 + 4 * bj;
-      double acc[4][4];
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) acc[a][q] = 0.0;
-      for (int kk = 0; kk < kb; ++kk) {
-        double li[4], lj[4];
-#pragma unroll
-        for (int a = 0; a < 4; ++a) {
-          li[a] = i0 + a < n ? S[pk(i0 + a, k0 + kk)] : 0.0;
-          lj[a] = j0 + a < n ? S[pk(j0 + a, k0 + kk)] : 0.0;
-        }
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) acc[a][q] += li[a] * lj[q];
-      }
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int i = i0 + a, j = j0 + q;
-          if (i < n && j <= i) S[pk(i, j)] -= acc[a][q];
-        }
-    }
-    __syncthreads();
-  }
-  if (sbad) {
-    if (tid == 0) *info = sbad;
-    return;
-  }
-  // X = L^-1 by 16-row block rows.  First the inverses of the diagonal
-  // blocks, one thread per column (forward substitution within the block),
-  // into X's diagonal blocks; then for each block row I: T_IJ = sum over
-  // K = J .. I-1 of L_IK X_KJ for every J < I, and X_IJ = -X_II T_IJ.
-  {
-    const int b = tid >> 4, lc = tid & 15, r0 = b * 16;
-    if (tid < n) {
-      const int m = n - r0 < 16 ? n - r0 : 16;  // rows of this diagonal block
-      double x[16];
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        double v = 0.0;
-        if (r >= lc && r < m) {
-          double acc = r == lc ? 1.0 : 0.0;
-#pragma unroll
-          for (int t = 0; t < 16; ++t)
-            if (t >= lc && t < r) acc -= S[pk(r0 + r, r0 + t)] * x[t];
-          v = acc / S[pk(r0 + r, r0 + r)];
-          XP[pk(r0 + r, r0 + lc)] = v;
-        }
-        x[r] = v;
-      }
-    }
-  }
-  __syncthreads();
-  for (int I = 1; I * 16 < n; ++I) {
-    const int i0 = I * 16, m = n - i0 < 16 ? n - i0 : 16;
-    for (int f = tid; f < I * 256; f += 1024) {
-      const int J = f >> 8, r = (f >> 4) & 15, q = f & 15, col = J * 16 + q;
-      double acc = 0.0;
-      if (r < m)
-        for (int k = col; k < i0; ++k) acc += S[pk(i0 + r, k)] * XP[pk(k, col)];
-      T[f] = acc;
-    }
-    __syncthreads();
-    for (int f = tid; f < I * 256; f += 1024) {
-      const int J = f >> 8, r = (f >> 4) & 15, q = f & 15;
-      if (r < m) {
-        double acc = 0.0;
-        for (int t = 0; t <= r; ++t) acc += XP[pk(i0 + r, i0 + t)] * T[(J << 8) + (t << 4) + q];
-        XP[pk(i0 + r, J * 16 + q)] = -acc;
-      }
-    }
-    __syncthreads();
-  }
-  for (int e = tid; e < n * n; e += 1024) {
-    const int i = e / n, j = e % n;
-    X[e] = j <= i ? XP[pk(i, j)] : 0.0;
-  }
-}
-
-// Inverse of a lower-triangular L (n x n, n <= 512): one 64-lane wave per
-// column c solves L x = e_c by forward substitution, each step a wave-wide
-// dot product; x lives in LDS.  X is lower triangular.
-__global__ __launch_bounds__(64) void k_trinv_lower(const double* __restrict__ L, int n, double* __restrict__ X) {
-  __shared__ double x[512];
-  const int c = blockIdx.x, lane = threadIdx.x;
-  for (int i = lane; i < n; i += 64) x[i] = 0.0;
-  __syncthreads();
-  for (int i = c; i < n; ++i) {
-    double s = 0.0;
-    for (int k = c + lane; k < i; k += 64) s += L[int64_t(i) * n + k] * x[k];
-    for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
-    if (lane == 0) x[i] = ((i == c ? 1.0 : 0.0) - s) / L[int64_t(i) * n + i];
-    __syncthreads();
-  }
-  for (int i = lane; i < n; i += 64) X[int64_t(i) * n + c] = x[i];
-}
 
 // ---------------------------------------------------------------- SCDM pivot search
 // Residual column norms res[r] = sum_i A[i][r]^2 of ng columns, A = psi [n]
@@ -1346,28 +992,6 @@ void launch_neg_sumsq(const double* c, int64_t n, double* out, hipStream_t s) {
 }
 void launch_symmetrize(const double* M, int n, double* out, double* negM, double* ex, double* asym, hipStream_t s) {
   hipLaunchKernelGGL(k_symmetrize, dim3(1), dim3(256), 0, s, M, n, out, negM, ex, asym);
-}
-// info must be zero on entry (the blocked kernels skip work once it is set).
-void launch_cholesky(double* A, int n, int* info, double* tinv, hipStream_t s) {
-  for (int k0 = 0; k0 < n; k0 += CB) {
-    hipLaunchKernelGGL(k_chol_diag, dim3(1), dim3(256), 0, s, A, n, k0, tinv, info);
-    const int rest = n - k0 - CB;
-    if (rest <= 0) break;
-    const int tiles = (rest + CB - 1) / CB;
-    hipLaunchKernelGGL(k_chol_panel, dim3(tiles), dim3(256), 0, s, A, n, k0, tinv, info);
-    hipLaunchKernelGGL(k_chol_update, dim3(tiles * (tiles + 1) / 2), dim3(256), 0, s, A, n, k0, info);
-  }
-}
-void launch_trinv(const double* L, int n, double* X, hipStream_t s) {
-  hipLaunchKernelGGL(k_trinv_lower, dim3(n), dim3(64), 0, s, L, n, X);
-}
-void launch_chol_inv(double* A, int n, int* info, double* X, double* tinv, hipStream_t s) {
-  if (n <= SMALL_N) {
-    hipLaunchKernelGGL(k_chol_inv_small, dim3(1), dim3(1024), 0, s, A, n, info, X);
-  } else {
-    launch_cholesky(A, n, info, tinv, s);
-    launch_trinv(A, n, X, s);
-  }
 }
 void launch_colnorm(const double* A, int n, int64_t ld, int64_t ng, double* res, hipStream_t s) {
   hipLaunchKernelGGL(k_colnorm, dim3(grid_for(ng, 256)), dim3(256), 0, s, A, n, ld, ng, res);

@@ -8,14 +8,15 @@ namespace ace {
 
 typedef double tiny_d4 __attribute__((ext_vector_type(4)));
 
-// sum_{k < kend} S(m, k) B[k][r] over the tile of rows m0 .. m0 + 15 < M and
-// columns r0 .. r0 + 15 < R; S(m, k) = TRANS ? S[k][m] : S[m][k], kend <= K.
+// sum_{k < kend} S(m, k) B(k, r) over the tile of rows m0 .. m0 + 15 < M and
+// columns r0 .. r0 + 15 < R; S(m, k) = TRANS ? S[k][m] : S[m][k],
+// B(k, r) = BT ? B[r][k] : B[k][r], kend <= K.
 // 256 threads: each wave takes a quarter of k with four steps' loads in flight,
 // the sums meet in LDS, and wave 0 returns the tile (element q of lane l: row
 // l / 16 + 4 q, column l % 16).  Operands come straight from global memory.
 // Bound by latency: one wave per tile, a step at a time, took 13.7 us for
 // 128^3 and 23.9 us for 256^3, this takes 3.8 and 5.1.
-template <typename TB, bool TRANS>
+template <typename TB, bool TRANS, bool BT = false>
 __device__ __forceinline__ tiny_d4 tiny_tile(const double* __restrict__ S, int lds, const TB* __restrict__ B,
                                              int64_t ldb, int m0, int64_t r0, int M, int K, int64_t R, int kend) {
   __shared__ double part[3][256];
@@ -32,7 +33,7 @@ __device__ __forceinline__ tiny_d4 tiny_tile(const double* __restrict__ S, int l
     for (int u = 0; u < 4; ++u) {
       const int k = k0 + 4 * u + lk, kc = k < K ? k : K - 1;
       a[u] = TRANS ? S[int64_t(kc) * lds + m] : S[int64_t(m) * lds + kc];
-      b[u] = double(B[int64_t(kc) * ldb + r]);
+      b[u] = double(BT ? B[r * ldb + kc] : B[int64_t(kc) * ldb + r]);
       a[u] = k < ke && mok ? a[u] : 0.0;
       b[u] = k < ke && rok ? b[u] : 0.0;
     }
