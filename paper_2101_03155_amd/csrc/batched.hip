@@ -366,6 +366,14 @@ __global__ __launch_bounds__(256) void k_batched_owner_conv_r(const BSys* __rest
                                    static_cast<const T*>(sy.vt));
 }
 
+template <typename P>
+__device__ __forceinline__ P* uniform_ptr(P* p) {
+  const uint64_t v = reinterpret_cast<uint64_t>(p);
+  const uint64_t lo = uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(v))));
+  const uint64_t hi = uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(v >> 32))));
+  return reinterpret_cast<P*>(hi << 32 | lo);
+}
+
 // W_k of plane z of one system: one workgroup per (system, orbital, plane)
 // item.  The items are dealt to the eight XCDs in turn: XCD x is given the
 // planes z = x mod 8, with the orbitals of all systems fastest (as in the
@@ -373,7 +381,7 @@ __global__ __launch_bounds__(256) void k_batched_owner_conv_r(const BSys* __rest
 // offsets.  Adjacency entries (slot, partner) index the slots of the
 // segment's spectra.
 template <typename T, int N, int V>
-__global__ __launch_bounds__(BNTR, 4) void k_batched_owner_r(int nown, const BOwner* __restrict__ own,
+__global__ __launch_bounds__(BNTR, (own_inv_waves<T, N>())) void k_batched_owner_r(int nown, const BOwner* __restrict__ own,
                                                           const BSys* __restrict__ sys,
                                                           const int32_t* __restrict__ adj,
                                                           const cplx<T>* __restrict__ spec) {
@@ -395,9 +403,11 @@ __global__ __launch_bounds__(BNTR, 4) void k_batched_owner_r(int nown, const BOw
   const cplx<T>* twg = static_cast<const cplx<T>*>(sy.tw);
   for (int t = threadIdx.x; t < N; t += BNTR) tw[t] = twg[t];
   const size_t zo = size_t(z) * N * N;
-  T* W = static_cast<T*>(sy.W) + size_t(k) * NG + zo;
-  body_inv_owner_r<T, N, BNTR, V>(static_cast<const T*>(sy.phi), spec, adj, o.adj_ptr[k], o.adj_ptr[k + 1], zo, W,
-                                  buf, tw, threadIdx.x);
+  // what the system's tables say is the same for all lanes: in scalar registers
+  T* W = uniform_ptr(static_cast<T*>(sy.W)) + size_t(__builtin_amdgcn_readfirstlane(k)) * NG + zo;
+  const int a0 = __builtin_amdgcn_readfirstlane(o.adj_ptr[k]), a1 = __builtin_amdgcn_readfirstlane(o.adj_ptr[k + 1]);
+  body_inv_owner_r<T, N, BNTR, V>(uniform_ptr(static_cast<const T*>(sy.phi)), spec, adj, a0, a1, zo, W, buf, tw,
+                                  threadIdx.x);
 }
 
 template <typename T, int N, int V>

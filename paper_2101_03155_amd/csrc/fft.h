@@ -373,11 +373,13 @@ __device__ __forceinline__ void fft_pass_ls(cplx<T>* buf, TW tw, int tid, L load
   if (END_SYNC) __syncthreads();
 }
 
-template <typename T, int N, int P, int LINES, int LS, int PS, int NT, int S, bool JFAST, int V, typename TW>
+// Passes P .. plan_len(N) - 1, the last one left out with SKIP.
+template <typename T, int N, int P, int LINES, int LS, int PS, int NT, int S, bool JFAST, int V, bool SKIP = false,
+          typename TW>
 __device__ __forceinline__ void fft_lines_from(cplx<T>* buf, TW tw, int tid) {
-  if constexpr (P < plan_len(N)) {
+  if constexpr (P < plan_len(N) - (SKIP ? 1 : 0)) {
     fft_pass<T, N, P, LINES, LS, PS, NT, S, JFAST, V>(buf, tw, tid);
-    fft_lines_from<T, N, P + 1, LINES, LS, PS, NT, S, JFAST, V>(buf, tw, tid);
+    fft_lines_from<T, N, P + 1, LINES, LS, PS, NT, S, JFAST, V, SKIP>(buf, tw, tid);
   }
 }
 

@@ -269,7 +269,7 @@ __global__ __launch_bounds__(NT) void k_conv_z_c(cplx<T>* __restrict__ spec, con
 // planes and spectra they read in that XCD's L2 (3-6% faster at 32 waters).
 // YC > 1: the z index runs over (plane, row class).
 template <typename T, int N, int NT, bool XCD = false, int YC = 1>
-__global__ __launch_bounds__(NT, 4) void k_inv_owner_r(const T* __restrict__ phi, const cplx<T>* __restrict__ spec,
+__global__ __launch_bounds__(NT, (own_inv_waves<T, N>())) void k_inv_owner_r(const T* __restrict__ phi, const cplx<T>* __restrict__ spec,
                                                     const int32_t* __restrict__ adj_ptr,
                                                     const int32_t* __restrict__ adj,
                                                     const int32_t* __restrict__ operm, T* __restrict__ W,
@@ -291,7 +291,7 @@ __global__ __launch_bounds__(NT, 4) void k_inv_owner_r(const T* __restrict__ phi
   for (int t = threadIdx.x; t < N; t += NT) tw[t] = twg[t];
   const int cls = z % YC;
   const size_t zo = size_t(z / YC) * N * N;
-  body_inv_owner_r<T, N, NT, 0, YC, cls_pitch<T, N, YC>()>(phi, spec, adj, adj_ptr[k], adj_ptr[k + 1], zo,
+  body_inv_owner_r<T, N, NT, own_inv_plan<T, N>(), YC, cls_pitch<T, N, YC>()>(phi, spec, adj, adj_ptr[k], adj_ptr[k + 1], zo,
                                     W + size_t(k) * NG + zo + size_t(cls) * N, buf, tw, threadIdx.x, cls);
 }
 

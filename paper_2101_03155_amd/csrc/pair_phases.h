@@ -530,7 +530,8 @@ __device__ __forceinline__ void body_inv_xy_r(const cplx<T>* in, cplx<T>* buf, c
 }
 
 // The x transforms of body_inv_xy_t (buf holds the y-transformed plane).
-template <typename T, int N, int NT, int V, int YC = 1>
+// LAST = false leaves the last pass to the caller.
+template <typename T, int N, int NT, int V, int YC = 1, bool LAST = true>
 __device__ __forceinline__ void inv_x_repacked(cplx<T>* buf, const cplx<T>* tw, int tid);
 
 template <typename T, int N, int NT, int V>
@@ -546,7 +547,7 @@ __device__ __forceinline__ void body_inv_xy_t(cplx<T>* buf, const cplx<T>* tw, i
 // The same from the half-spectrum plane in global memory: the first pass of
 // the y transforms reads it directly (no staging copy).  Needs no barrier
 // before it: the first pass reads before its barrier and writes after.
-template <typename T, int N, int NT, int V = 0, int YC = 1>
+template <typename T, int N, int NT, int V = 0, int YC = 1, bool LAST = true>
 __device__ __forceinline__ void body_inv_xy_g(const cplx<T>* __restrict__ in, cplx<T>* buf, const cplx<T>* tw,
                                               int tid) {
   using Lay = InvLayout<T, N, V, YC>;
@@ -554,41 +555,49 @@ __device__ __forceinline__ void body_inv_xy_g(const cplx<T>* __restrict__ in, cp
   fft_lines_ls<T, N / YC, XS, 1, XS, NT, +1, false, V, true>(
       buf, TwStride<T, YC>{tw}, tid, [in](int l, int p) { return in[p * XS + l]; },
       [buf](int l, int p, cplx<T> x) { buf[l + Lay::ysig(p) * XS] = x; });
-  inv_x_repacked<T, N, NT, V, YC>(buf, tw, tid);
+  inv_x_repacked<T, N, NT, V, YC, LAST>(buf, tw, tid);
 }
 
-template <typename T, int N, int NT, int V, int YC>
-__device__ __forceinline__ void inv_x_repacked(cplx<T>* buf, const cplx<T>* tw, int tid) {
+// Element p of x line l from the y-transformed plane: rows l and l + H re-packed
+// as Z[k] = X1[k] + i X2[k] and Z[N-k] = conj X1[k] + i conj X2[k] for k <= N/2
+// (X1, X2 = rows l, l + H of the [y][kx] layout); the zero and Nyquist bins of a
+// real row are real, as a c2r transform takes them.
+template <typename T, int N, int V, int YC>
+__device__ __forceinline__ cplx<T> inv_repack(const cplx<T>* buf, int l, int p) {
   using C = cplx<T>;
-  constexpr int H = N / YC / 2, NH = N / 2, XS = r2c_xs<N>();
-  // The x transforms, whose first pass re-packs rows l and l + H into line
-  // l on the way in: Z[k] = X1[k] + i X2[k] and Z[N-k] = conj X1[k] +
-  // i conj X2[k] for k <= N/2 (X1, X2 = rows l, l + H of the [y][kx] layout);
-  // the zero and Nyquist bins of a real row are real, as a c2r transform
-  // takes them.  This pass keeps consecutive butterflies of one line on
-  // consecutive threads (with consecutive lines its re-pack spills registers
-  // in FP64), with the radix order reversed: the larger first radix spreads
-  // its writes over more banks.  The later passes take consecutive lines.
   using Lay = InvLayout<T, N, V, YC>;
-  fft_pass_l<T, N, 0, H, Lay::XL, 1, NT, +1, true, V ^ 1, Lay::WROT>(buf, tw, tid, [buf](int l, int p) {
-    const bool lowk = p <= NH;
-    const int k = lowk ? p : N - p;
-    C x1 = buf[Lay::ysig(l) * XS + k], x2 = buf[Lay::ysig(l + H) * XS + k];
-    if (k == 0 || k == NH) {
-      x1.y = T(0);
-      x2.y = T(0);
-    }
-    C z;
-    if (lowk) {
-      z.x = x1.x - x2.y;
-      z.y = x1.y + x2.x;
-    } else {
-      z.x = x1.x + x2.y;
-      z.y = x2.x - x1.y;
-    }
-    return z;
-  });
-  fft_lines_from<T, N, 1, H, Lay::XL, 1, NT, +1, false, V ^ 1>(buf, tw, tid);
+  constexpr int H = N / YC / 2, NH = N / 2, XS = r2c_xs<N>();
+  const bool lowk = p <= NH;
+  const int k = lowk ? p : N - p;
+  C x1 = buf[Lay::ysig(l) * XS + k], x2 = buf[Lay::ysig(l + H) * XS + k];
+  if (k == 0 || k == NH) {
+    x1.y = T(0);
+    x2.y = T(0);
+  }
+  C z;
+  if (lowk) {
+    z.x = x1.x - x2.y;
+    z.y = x1.y + x2.x;
+  } else {
+    z.x = x1.x + x2.y;
+    z.y = x2.x - x1.y;
+  }
+  return z;
+}
+
+template <typename T, int N, int NT, int V, int YC, bool LAST>
+__device__ __forceinline__ void inv_x_repacked(cplx<T>* buf, const cplx<T>* tw, int tid) {
+  // The x transforms, whose first pass re-packs the rows on the way in.  This
+  // pass keeps consecutive butterflies of one line on consecutive threads
+  // (with consecutive lines its re-pack spills registers in FP64), with the
+  // radix order reversed: the larger first radix spreads its writes over more
+  // banks.  The later passes take consecutive lines.
+  using Lay = InvLayout<T, N, V, YC>;
+  constexpr int H = N / YC / 2;
+  if constexpr (LAST || plan_len(N) > 1)
+    fft_pass_l<T, N, 0, H, Lay::XL, 1, NT, +1, true, V ^ 1, Lay::WROT>(
+        buf, tw, tid, [buf](int l, int p) { return inv_repack<T, N, V, YC>(buf, l, p); });
+  fft_lines_from<T, N, 1, H, Lay::XL, 1, NT, +1, false, V ^ 1, !LAST>(buf, tw, tid);
 }
 
 // W_i -= v phi_j and (i != j) W_j -= v phi_i over plane z for one pair, with
@@ -655,57 +664,150 @@ __device__ __forceinline__ void accumulate_w_r(const T* __restrict__ pi_, const 
 // the pair's half-spectrum plane is transformed back and v_kj phi_j is added
 // to an accumulator in registers; the row is written once, never read.
 // PP: pitch of a class (a plane where YC is 1) of the spectra.
+//
+// Where the registers allow (own_fused) the last x pass keeps its outputs: a
+// thread multiplies them by the partner's values at their places, loaded ahead
+// of the pass, and adds them to its accumulators, so a pair's plane is not
+// written to LDS and read again for the product, and two barriers and the waits
+// of the partner's loads (in five batches) are gone.  Owner pass before and
+// after, ms: FP32 120^3 13.2 -> 11.6, 96^3 4.77 -> 4.45, 80^3 0.86 -> 0.76, 160^3
+// 8.7 -> 8.0; FP64 80^3 1.94 -> 1.67, 120^3 9.8 -> 8.2, 160^3 12.0 -> 11.4.
+// The separate product stays for FP64 at 96^3 in whole planes (128 registers
+// are not enough: 8.3 -> 11.7), at 64^3 (94 registers instead of 70 leave two
+// workgroups per CU instead of three: 0.39 -> 0.41) and for 12 and 16, whose
+// single pass of that radix spills.
+template <typename T, int N, int YC> __host__ __device__ constexpr bool own_fused() {
+  return sizeof(T) == 4 || (N != 12 && N != 16 && N != 64 && !(N == 96 && YC == 1));
+}
+// Waves per SIMD of the owner pass: six keep three workgroups per CU for FP32
+// at 96^3 (81 registers had left two).
+template <typename T, int N> __host__ __device__ constexpr int own_inv_waves() { return sizeof(T) == 4 && N == 96 ? 6 : 4; }
+// Plan order of the owner pass: reversed for FP64 at 160^3, where a last radix
+// of 16 would need more registers than there are.
+template <typename T, int N> __host__ __device__ constexpr int own_inv_plan() { return sizeof(T) == 8 && N == 160 ? 1 : 0; }
+
 template <typename T, int N, int NT, int V = 0, int YC = 1, int PP = N / YC * r2c_xs<N>()>
 __device__ __forceinline__ void body_inv_owner_r(const T* __restrict__ phi, const cplx<T>* __restrict__ spec,
                                                  const int32_t* __restrict__ adj, int a0, int a1, size_t zo,
                                                  T* __restrict__ wk, cplx<T>* buf, const cplx<T>* tw, int tid,
                                                  int cls = 0) {
-  constexpr int HN = (N / YC / 2) * N;  // elements of the packed lines
-  constexpr size_t NG = size_t(N) * N * N, PL = size_t(YC) * PP;
-  // offset in the class's rows (row pitch N * YC) of packed element e
-  auto at = [](int e) { return YC == 1 ? e : e + e / N * (N * (YC - 1)); };
-  constexpr int LP = (HN + NT - 1) / NT;
-  T acc0[LP], acc1[LP];
+  if constexpr (own_fused<T, N, YC>()) {
+    using C = cplx<T>;
+    constexpr int H = N / YC / 2, RP = N * YC, HR = H * RP;  // packed lines, pitch of the class's rows
+    constexpr size_t NG = size_t(N) * N * N, PL = size_t(YC) * PP;
+    constexpr int VX = V ^ 1, P = plan_len(N) - 1;
+    constexpr int R = plan_radix_v(N, P, VX), NB = N / R, TOT = H * NB, PER = (TOT + NT - 1) / NT;
+    static_assert(plan_ns(N, P, VX) == NB, "last pass");
+    constexpr int XL = InvLayout<T, N, V, YC>::XL;
+    C acc[PER][R];
 #pragma unroll
-  for (int q = 0; q < LP; ++q) { acc0[q] = T(0); acc1[q] = T(0); }
-  // offset of the plane's class in a pair's half spectrum
-  const size_t zp = zo / (size_t(N) * N) * PL + size_t(cls) * PP;
-  zo += size_t(cls) * N;  // (wk points at the class's first row)
-  for (int a = a0; a < a1; ++a) {
-    // an opaque copy of the thread index keeps the transform's index
-    // arithmetic inside the loop (hoisted, it would all stay live)
-    int t = tid;
-    asm volatile("" : "+v"(t));
-    const int p = adj[2 * a], j = adj[2 * a + 1];
-    // (the first pass's barrier also orders the previous entry's reads of buf
-    // before this entry's writes)
-    body_inv_xy_g<T, N, NT, V, YC>(spec + size_t(p) * N * PL + zp, buf, tw, t);
-    const T* fj = phi + size_t(j) * NG + zo;
-    // partner row in batches of U elements per thread, loads first
-    constexpr int U = 3;
+    for (int s = 0; s < PER; ++s)
 #pragma unroll
-    for (int q0 = 0; q0 < LP; q0 += U) {
-      T f0[U], f1[U];
+      for (int r = 0; r < R; ++r) acc[s][r].x = acc[s][r].y = T(0);
+    // offset of the plane's class in a pair's half spectrum
+    const size_t zp = zo / (size_t(N) * N) * PL + size_t(cls) * PP;
+    zo += size_t(cls) * N;  // (wk points at the class's first row)
+    for (int a = a0; a < a1; ++a) {
+      // an opaque copy of the thread index keeps the transform's index
+      // arithmetic inside the loop (hoisted, it would all stay live)
+      int t = tid;
+      asm volatile("" : "+v"(t));
+      const int p = adj[2 * a], j = adj[2 * a + 1];
+      // (the first pass's barrier also orders the previous entry's reads of buf
+      // before this entry's writes)
+      body_inv_xy_g<T, N, NT, V, YC, false>(spec + size_t(p) * N * PL + zp, buf, tw, t);
+      const T* fj = phi + size_t(j) * NG + zo;
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int e = t + (q0 + u) * NT;
-        if (q0 + u < LP && (HN % NT == 0 || e < HN)) { f0[u] = fj[at(e)]; f1[u] = fj[at(e) + HN * YC]; }
-      }
+      for (int s = 0; s < PER; ++s) {
+        const int b = t + s * NT;
+        if (TOT % NT == 0 || b < TOT) {
+          const int l = b / NB, i = b % NB;
+          const T* f = fj + l * RP + i;
+          T f0[R], f1[R];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int e = t + (q0 + u) * NT;
-        if (q0 + u < LP && (HN % NT == 0 || e < HN)) {
-          const cplx<T> v = buf[xpos<N>(e)];
-          acc0[q0 + u] += v.x * f0[u];
-          acc1[q0 + u] += v.y * f1[u];
+          for (int r = 0; r < R; ++r) {
+            f0[r] = f[r * NB];
+            f1[r] = f[r * NB + HR];
+          }
+          C v[R];
+#pragma unroll
+          for (int r = 0; r < R; ++r) {
+            if constexpr (P == 0) v[r] = inv_repack<T, N, V, YC>(buf, l, r * NB);
+            else v[r] = buf[l * XL + i + r * NB];
+          }
+          if constexpr (P > 0) {
+#pragma unroll
+            for (int r = 1; r < R; ++r) v[r] = cmulc(v[r], tw[r * i]);
+          }
+          Dft<R, +1, C>::run(v);
+#pragma unroll
+          for (int r = 0; r < R; ++r) {
+            acc[s][r].x += v[r].x * f0[r];
+            acc[s][r].y += v[r].y * f1[r];
+          }
         }
       }
     }
-  }
 #pragma unroll
-  for (int q = 0; q < LP; ++q) {
-    const int e = tid + q * NT;
-    if (HN % NT == 0 || e < HN) { wk[at(e)] = -acc0[q]; wk[at(e) + HN * YC] = -acc1[q]; }
+    for (int s = 0; s < PER; ++s) {
+      const int b = tid + s * NT;
+      if (TOT % NT == 0 || b < TOT) {
+        T* w = wk + b / NB * RP + b % NB;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          w[r * NB] = -acc[s][r].x;
+          w[r * NB + HR] = -acc[s][r].y;
+        }
+      }
+    }
+  } else {
+    constexpr int HN = (N / YC / 2) * N;  // elements of the packed lines
+    constexpr size_t NG = size_t(N) * N * N, PL = size_t(YC) * PP;
+    // offset in the class's rows (row pitch N * YC) of packed element e
+    auto at = [](int e) { return YC == 1 ? e : e + e / N * (N * (YC - 1)); };
+    constexpr int LP = (HN + NT - 1) / NT;
+    T acc0[LP], acc1[LP];
+#pragma unroll
+    for (int q = 0; q < LP; ++q) { acc0[q] = T(0); acc1[q] = T(0); }
+    // offset of the plane's class in a pair's half spectrum
+    const size_t zp = zo / (size_t(N) * N) * PL + size_t(cls) * PP;
+    zo += size_t(cls) * N;  // (wk points at the class's first row)
+    for (int a = a0; a < a1; ++a) {
+      // an opaque copy of the thread index keeps the transform's index
+      // arithmetic inside the loop (hoisted, it would all stay live)
+      int t = tid;
+      asm volatile("" : "+v"(t));
+      const int p = adj[2 * a], j = adj[2 * a + 1];
+      // (the first pass's barrier also orders the previous entry's reads of buf
+      // before this entry's writes)
+      body_inv_xy_g<T, N, NT, V, YC>(spec + size_t(p) * N * PL + zp, buf, tw, t);
+      const T* fj = phi + size_t(j) * NG + zo;
+      // partner row in batches of U elements per thread, loads first
+      constexpr int U = 3;
+#pragma unroll
+      for (int q0 = 0; q0 < LP; q0 += U) {
+        T f0[U], f1[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int e = t + (q0 + u) * NT;
+          if (q0 + u < LP && (HN % NT == 0 || e < HN)) { f0[u] = fj[at(e)]; f1[u] = fj[at(e) + HN * YC]; }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int e = t + (q0 + u) * NT;
+          if (q0 + u < LP && (HN % NT == 0 || e < HN)) {
+            const cplx<T> v = buf[xpos<N>(e)];
+            acc0[q0 + u] += v.x * f0[u];
+            acc1[q0 + u] += v.y * f1[u];
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < LP; ++q) {
+      const int e = tid + q * NT;
+      if (HN % NT == 0 || e < HN) { wk[at(e)] = -acc0[q]; wk[at(e) + HN * YC] = -acc1[q]; }
+    }
   }
 }
 
