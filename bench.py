@@ -416,13 +416,13 @@ def form_kpoints(ctx, log, with_oracle=True):
                                                want_W=True), 3)
     npairs = int(pairs.shape[0])
     ntot = u.shape[0]
-    per_pair = 16 * spec.N ** 3 * 16
+    per_pair = 9 * spec.N ** 3 * 16  # owner form: forward 3, z pass 2, owner pass 2 per end of the pair
     tbs = per_pair * npairs / (ms_b / 1000.0) / 1e9
     out = {"workload": f"8 waters per cell, 2x2x2 k-points, {spec.norb} bands per k-point ({ntot} in all), "
                        f"{spec.N}^3, L={spec.L}, erfc omega={spec.omega}, rho_cut={rho_cut}",
            "pairs": npairs, "pairs_full": ntot * (ntot + 1) // 2, "pairlist_ms": round(ms_pl, 3),
            "build_ms": round(ms_b, 3), "pair_solves_per_s": round(npairs / ms_b * 1000, 1),
-           "bytes_per_pair_16N3x16": per_pair, "achieved_gbs": round(tbs, 1),
+           "bytes_per_pair_9N3x16": per_pair, "achieved_gbs": round(tbs, 1),
            "frac_hbm_peak": round(tbs / HBM_PEAK_GBS, 4), "ex": float(r["ex"].item())}
     if with_oracle:
         from oracle import kpoint_oracle as ko

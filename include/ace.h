@@ -343,9 +343,9 @@ int ace_profile_classes(ace_ctx* ctx, unsigned mask);
  *              ace_create; results agree to rounding).  When the spectra
  *              exceed ACE_OWNER_SPECTRA_MAX bytes (default 96 GiB) the build
  *              uses fused = 2 (or 0, where that does not fit) instead.  FP64
- *      planes that do not fit twice in one CU's LDS are taken as two or four
- *      interleaved classes of rows, so this path runs at every size.  The
- *      default.
+ *              planes that do not fit twice in one CU's LDS are taken as two
+ *              or four interleaved classes of rows, so this path runs at every
+ *              size.  The default.
  * A path whose plane does not fit in LDS for this size falls back to 0; other
  * values of fused are ACE_E_ARG.
  * max_packs (>= 1) caps the packs per launch.  Results agree between paths to
