@@ -1,7 +1,7 @@
 // FP64 Cholesky factorization A = L L^T and X = L^-1 of the norb x norb matrices
 // (n <= 512).  Up to 128 columns one workgroup does both in LDS; larger matrices
 // take 128-column blocks: a block's factor and inverse, the rows below it
-// (L21 = A21 X11^T), the trailing update, and at the end the block rows of X,
+// (L21 = A21 X11^T with one correction), the trailing update, and at the end the block rows of X,
 // products of 16 x 16 tiles.
 //
 // info = k + 1 when the pivot of column k is not positive, -(k + 1) when it is
@@ -21,15 +21,21 @@ namespace ace {
 // what is left, element (i, j) at (j, i + 1).  Columns go by panels of 16.  Wave 0
 // factors the panel's diagonal block and inverts it in registers, a row per lane
 // (four copies of the block) with broadcasts in rows of 16 lanes; the rows below
-// are multiplied by that inverse and the trailing matrix is updated by 16 x 16
-// tiles on the FP64 matrix cores, as are the block rows of X: X_IJ = -X_II sum_K
-// L_IK X_KJ, where a tile's accumulators are directly the right operand of the
-// second product (step u takes the k's lk + 4 u).  Rows and columns past n are
-// those of the identity, so there are no edges.
+// are multiplied by that inverse, corrected once for what its rounding leaves of
+// A21, and the trailing matrix is updated by 16 x 16 tiles on the FP64 matrix
+// cores, as are the block rows of X: X_IJ = -X_II Y, Y = sum_K L_IK X_KJ, corrected
+// once by the residual of L_II X_IJ = -Y.  A tile's accumulators are directly the
+// right operand of the next product (step u takes the k's lk + 4 u).  The
+// corrections make up for the explicit inverses: without them 64 columns of
+// which every fifth repeats its neighbour to 1e-6 are taken for not positive
+// definite (condition 1e13), and for 130 such to 1e-5 X^T X times the matrix is
+// off by 4e-7 instead of 1e-11.  Rows and columns past n are those of the
+// identity, so there are no edges.
 // Bound by the chain of the diagonal blocks (sixteen dependent pivots each):
-// 128 columns with the inverse take 70 us, 64 33, 8 9 (a scalar trailing update
+// 128 columns with the inverse take 71 us, 64 31, 8 9 (a scalar trailing update
 // and pivots passed through LDS took 172, 73 and 11; 256 columns by blocks of 64
-// and a wave per column of the inverse 620, now 160).  512 threads, as wave 0
+// and a wave per column of the inverse 620, now 187, of which the corrections'
+// launches are 20).  512 threads, as wave 0
 // needs 185 registers: with 1024 it spilled and took 115.
 constexpr int CBN = 128, CP = CBN + 1, CNT = 512, CW = CNT / 64, CR = CNT / CBN;
 
@@ -126,17 +132,28 @@ __global__ __launch_bounds__(CNT) void k_chol_block(double* __restrict__ A, int 
     }
     __syncthreads();
     if (sbad) break;
-    // rows below: L21 = A21 X11^T, a wave per 16 rows
+    // rows below: L21^T = X11 A21^T and one correction, L21^T += X11 (A21^T - L11
+    // L21^T), a wave per 16 rows; each product's accumulators are the right
+    // operand of the next
     for (int rb = b + 1 + w; rb < nb; rb += CW) {
-      tiny_d4 acc = tiny_d4{0, 0, 0, 0};
+      const double* a21 = S + (16 * rb + li) * CP + k0;
+      double x11[4], l11[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const int k = lk + 4 * u;
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(S[(16 * rb + li) * CP + k0 + k],
-                                                   k <= li ? S[(k0 + k) * CP + k0 + li + 1] : 0.0, acc, 0, 0, 0);
+        x11[u] = k <= li ? S[(k0 + k) * CP + k0 + li + 1] : 0.0;
+        l11[u] = k <= li ? S[(k0 + li) * CP + k0 + k] : 0.0;
       }
+      tiny_d4 t = tiny_d4{0, 0, 0, 0}, p = tiny_d4{0, 0, 0, 0};
 #pragma unroll
-      for (int q = 0; q < 4; ++q) S[(16 * rb + lk + 4 * q) * CP + k0 + li] = acc[q];
+      for (int u = 0; u < 4; ++u) t = __builtin_amdgcn_mfma_f64_16x16x4f64(x11[u], a21[lk + 4 * u], t, 0, 0, 0);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) p = __builtin_amdgcn_mfma_f64_16x16x4f64(l11[u], t[u], p, 0, 0, 0);
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        t = __builtin_amdgcn_mfma_f64_16x16x4f64(x11[u], a21[lk + 4 * u] - p[u], t, 0, 0, 0);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) S[(16 * rb + li) * CP + k0 + lk + 4 * q] = t[q];
     }
     __syncthreads();
     // trailing update of the tiles (bi, bj), b < bj <= bi < nb
@@ -170,7 +187,7 @@ __global__ __launch_bounds__(CNT) void k_chol_block(double* __restrict__ A, int 
   if (!X) return;
   for (int I = 1; I < nb; ++I) {
     for (int J = w; J < I; J += CW) {
-      tiny_d4 y = tiny_d4{0, 0, 0, 0}, z = tiny_d4{0, 0, 0, 0};
+      tiny_d4 y = tiny_d4{0, 0, 0, 0}, z = tiny_d4{0, 0, 0, 0}, p = tiny_d4{0, 0, 0, 0};
       for (int K = J; K < I; ++K)
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -179,12 +196,19 @@ __global__ __launch_bounds__(CNT) void k_chol_block(double* __restrict__ A, int 
               S[(16 * I + li) * CP + 16 * K + k],
               K > J || li <= k ? S[(16 * J + li) * CP + 16 * K + k + 1] : 0.0, y, 0, 0, 0);
         }
+      double xii[4], lii[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const int k = lk + 4 * u;
-        z = __builtin_amdgcn_mfma_f64_16x16x4f64(k <= li ? S[(16 * I + k) * CP + 16 * I + li + 1] : 0.0, y[u], z, 0,
-                                                 0, 0);
+        xii[u] = k <= li ? S[(16 * I + k) * CP + 16 * I + li + 1] : 0.0;
+        lii[u] = k <= li ? S[(16 * I + li) * CP + 16 * I + k] : 0.0;
       }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) z = __builtin_amdgcn_mfma_f64_16x16x4f64(xii[u], y[u], z, 0, 0, 0);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) p = __builtin_amdgcn_mfma_f64_16x16x4f64(lii[u], z[u], p, 0, 0, 0);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) z = __builtin_amdgcn_mfma_f64_16x16x4f64(xii[u], y[u] - p[u], z, 0, 0, 0);
 #pragma unroll
       for (int q = 0; q < 4; ++q) S[(16 * J + li) * CP + 16 * I + lk + 4 * q + 1] = -z[q];
     }
@@ -231,8 +255,13 @@ void launch_cholesky(double* A, int n, int* info, double* X, hipStream_t s) {
     const int64_t d = int64_t(k0) * n + k0, below = d + int64_t(b) * n;
     hipLaunchKernelGGL(k_chol_block, dim3(1), dim3(CNT), 0, s, A + d, n, b, k0, info, X + d, n, rest);
     if (rest == 0) break;
+    // L21 = A21 X11^T, then A21 -= L21 L11^T and L21 += A21 X11^T: one correction
     hipLaunchKernelGGL((k_chol_tile<true, false>), tiles(rest, b), dim3(256), 0, s, A + below, X + d, X + below, n, rest,
                        b, b, 1.0, 0.0, info);
+    hipLaunchKernelGGL((k_chol_tile<true, false>), tiles(rest, b), dim3(256), 0, s, X + below, A + d, A + below, n, rest,
+                       b, b, -1.0, 1.0, info);
+    hipLaunchKernelGGL((k_chol_tile<true, false>), tiles(rest, b), dim3(256), 0, s, A + below, X + d, X + below, n, rest,
+                       b, b, 1.0, 1.0, info);
     hipLaunchKernelGGL((k_chol_tile<true, true>), tiles(rest, rest), dim3(256), 0, s, X + below, X + below,
                        A + below + b, n, rest, b, rest, -1.0, 1.0, info);
   }
@@ -244,14 +273,19 @@ void launch_chol_inv(double* A, int n, int* info, double* X, hipStream_t s) {
     return;
   }
   launch_cholesky(A, n, info, X, s);
-  // block row I of X: Y_IJ = sum_K L_IK X_KJ into A, then X_IJ = -X_II Y_IJ
+  // block row I of X: Y_IJ = sum_K L_IK X_KJ into A, X_IJ = -X_II Y_IJ, and one
+  // correction: Y_IJ += L_II X_IJ, X_IJ -= X_II Y_IJ
   for (int i0 = CBN; i0 < n; i0 += CBN) {
     const int b = n - i0 < CBN ? n - i0 : CBN;
     const int64_t row = int64_t(i0) * n;
-    hipLaunchKernelGGL((k_chol_tile<false, false>), tiles(b, i0), dim3(256), 0, s, X + row, X, A + row, n, b, i0, i0,
-                       1.0, 0.0, info);
-    hipLaunchKernelGGL((k_chol_tile<false, false>), tiles(b, i0), dim3(256), 0, s, X + row + i0, A + row, X + row, n, b,
-                       b, i0, -1.0, 0.0, info);
+    const auto product = [&](const double* S, const double* B, double* C, int K, double alpha, double beta) {
+      hipLaunchKernelGGL((k_chol_tile<false, false>), tiles(b, i0), dim3(256), 0, s, S, B, C, n, b, K, i0, alpha, beta,
+                         info);
+    };
+    product(X + row, X, A + row, i0, 1.0, 0.0);
+    product(X + row + i0, A + row, X + row, b, -1.0, 0.0);
+    product(A + row + i0, X + row, A + row, b, 1.0, 1.0);
+    product(X + row + i0, A + row, X + row, b, -1.0, 1.0);
   }
 }
 
