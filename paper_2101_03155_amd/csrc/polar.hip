@@ -15,6 +15,9 @@
 
 namespace ace {
 
+// The larger of two deviations; one that is not a number counts as infinite.
+__device__ __forceinline__ double worst(double m, double d) { return d <= m ? m : d < INFINITY ? d : INFINITY; }
+
 // ---------------------------------------------------------------- one workgroup
 // The matrix is padded to 64 x 64 with zeros, so the products run on the FP64
 // matrix cores without edges: wave w owns tile (w / 4, w % 4).  The pitch of 65
@@ -81,7 +84,7 @@ __global__ __launch_bounds__(1024) void k_polar_small(const double* __restrict__
       const int i = m0 + lk + 4 * q, j = r0 + li;
       if (mine) Gs[i * PP + j] = g[q];
       const double d = i < n && j < n ? fabs(g[q] - (i == j ? 1.0 : 0.0)) : 0.0;
-      dev = d > dev ? d : dev;
+      dev = worst(dev, d);
     }
     if (test) {
       for (int off = 32; off > 0; off >>= 1) dev = fmax(dev, __shfl_xor(dev, off, 64));
@@ -131,7 +134,7 @@ __global__ __launch_bounds__(256) void k_ns_gram(const double* __restrict__ X, i
     if (i >= n || j >= n) continue;
     G[int64_t(i) * n + j] = g[q];
     const double d = fabs(g[q] - (i == j ? 1.0 : 0.0));
-    m = d > m ? d : m;
+    m = worst(m, d);
   }
   for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_down(m, off, 64));
   if (lane == 0) dev[blockIdx.y * gridDim.x + blockIdx.x] = m;
