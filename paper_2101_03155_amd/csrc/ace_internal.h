@@ -142,7 +142,7 @@ void launch_cholesky(double* A, int n, int* info, double* X, hipStream_t s);
 // X = L^-1 of A = L L^T (zeros above the diagonal); info zero on entry, set as by
 // launch_cholesky.  A is overwritten.
 void launch_chol_inv(double* A, int n, int* info, double* X, hipStream_t s);
-void launch_colnorm(const double* A, int n, int64_t ld, int64_t ng, double* res, hipStream_t s);
+void launch_colnorm(const double* A, int n, int64_t ng, double* res, hipStream_t s);
 int qrcp_blocks(int64_t ng);
 void launch_qrcp_update(const double* A, int n, int64_t ng, const double* q, double* res, double* pv, int64_t* pi,
                         const int* stop, hipStream_t s);

@@ -692,30 +692,48 @@ int ace_localize(ace_ctx* c, const ace_grid* g, int norb, const double* psi, dou
   // largest bound outside the pool.  When certification fails, the next pivot
   // has at least the residual r2 of the pool's best column, so only columns
   // whose bound reaches r2 can be it: the bounds from r2 / 2 up are recomputed
-  // exactly from the picked directions and a new pool is drawn (half, so that
-  // the new pool lasts until the residuals fall by that much; at 64 waters
-  // 7% of the columns are listed and take 0.7 ms, the refresh of all of them
-  // took 4.5: the localization went from 13.2 to 10.3 ms).  Residual norms only decrease, so every stored
-  // bound stays valid until it is recomputed.
-  launch_colnorm(psi, norb, ng, ng, res, s);
+  // exactly and a new pool is drawn (half, so that the new pool lasts until the
+  // residuals fall by that much).  Residual norms only decrease, so every
+  // stored bound stays valid until it is recomputed.
+  // A recomputed bound is the residual after kref directions, which every
+  // column has in res (exact) or base, less the directions picked since.  Few
+  // columns are listed and gathered, and kref stays; many, or once the lists
+  // since kref add up to half of the work, all columns take the directions and
+  // kref moves on.  (At 64 waters 7% are listed and take 0.7 ms, all of them 4.5:
+  // the localization went from 13.9 to 9.6 ms.  256 random orbitals on 80^3: 16.9
+  // ms; with every column refreshed every time 17.8, with lists of up to half of
+  // the columns and from the first direction on 27.5.)
+  launch_colnorm(psi, norb, ng, res, s);
   const bool one = pool_fits_one(ng);
   if (!one) HIPCHK(c, hipMemsetAsync(iv, 0, 64, s));
   // algorithmic bytes of one pool step per pool column: R read and written, residual read and written
   const double qbytes_pool = double(2 * norb + 2) * sizeof(double);
-  // res[r] = |a_r|^2 - |Q_k a_r|^2 over w columns at a (pitch ld), by blocks of
-  // 128 directions whose projections' squares are summed on the MFMA tile
-  auto bounds = [&](const double* a, int64_t ld, int64_t w, int k, double* out) -> hipError_t {
-    launch_colnorm(a, norb, ld, w, out, s);
-    for (int m = 0; m < k; m += 128) {
+  int k = 0, kref = 0;
+  bool exact = true;
+  double listed = 0.0;  // columns listed since kref, times their directions
+  double* base = nullptr;
+  // out[r] -= |q_m a_r|^2 over the directions m = kref .. k - 1 and w columns at a
+  // (pitch ld), by blocks of 128 directions whose projections' squares are summed
+  // on the MFMA tile
+  auto fold = [&](const double* a, int64_t ld, int64_t w, double* out) -> hipError_t {
+    for (int m = kref; m < k; m += 128) {
       hipError_t e = refresh_bounds(Q + size_t(m) * norb, norb, a, ld, std::min(128, k - m), norb, w, out, s);
       if (e != hipSuccess) return e;
     }
     return hipSuccess;
   };
-  int k = 0;
-  bool exact = true;  // every bound in res is the residual itself
+  auto fold_all = [&]() -> hipError_t {
+    hipError_t e = fold(psi, ng, ng, exact ? res : base);
+    if (e == hipSuccess && !exact)
+      e = hipMemcpyAsync(res, base, size_t(ng) * sizeof(double), hipMemcpyDeviceToDevice, s);
+    launch_retire(pivots, k, res, s);
+    kref = k;
+    exact = true;
+    listed = 0.0;
+    return e;
+  };
   for (int refresh = 0; k < norb; ++refresh) {
-    if (k > 0 && refresh < 16) {
+    if (k > kref && refresh < 16) {
       // the listed columns go through Lc chunk by chunk: half of it holds the
       // gathered columns, a quarter the list, a quarter their bounds
       const int64_t w = rchunk / 2, half = int64_t(norb) * w;
@@ -723,22 +741,30 @@ int ace_localize(ace_ctx* c, const ace_grid* g, int norb, const double* psi, dou
       launch_count_above(res, ng, tvals, pcnt, tmax, iv + 2, tvals + 3, s);
       HIPCHK(c, hipMemcpyAsync(&nl, iv + 2, sizeof(int), hipMemcpyDeviceToHost, s));
       HIPCHK(c, hipStreamSynchronize(s));
-      if (nl > 0 && nl <= half && w <= half / 2 && nl <= ng / 2) {
+      const double dk = k - kref;
+      bool part = nl > 0 && nl <= half && w <= half / 2 && nl <= ng / 4 && listed + nl * dk <= 0.5 * double(ng) * dk;
+      if (part && !base && ws_get(c, "resref", size_t(ng) * sizeof(double), (void**)&base) != ACE_OK) {
+        c->err.clear();  // no room for the second copy
+        part = false;
+      }
+      if (part) {
         int32_t* list = reinterpret_cast<int32_t*>(Lc + half);
         double* cres = Lc + half + half / 2;
+        if (exact) HIPCHK(c, hipMemcpyAsync(base, res, size_t(ng) * sizeof(double), hipMemcpyDeviceToDevice, s));
+        exact = false;
+        listed += nl * dk;
         launch_pool_write(res, ng, tvals, pcnt, list, nullptr, s);
         for (int64_t r0 = 0; r0 < nl; r0 += w) {
           const int64_t wc = std::min<int64_t>(w, nl - r0);
           launch_pool_gather(psi, norb, ng, list + r0, int(wc), Lc, s);
-          HIPCHK(c, bounds(Lc, wc, wc, k, cres));
+          launch_pool_gather(base, 1, ng, list + r0, int(wc), cres, s);
+          HIPCHK(c, fold(Lc, wc, wc, cres));
           launch_scatter_res(list + r0, wc, cres, res, s);
         }
-        exact = false;
+        launch_retire(pivots, k, res, s);
       } else {
-        HIPCHK(c, bounds(psi, ng, ng, k, res));
-        exact = true;
+        HIPCHK(c, fold_all());
       }
-      launch_retire(pivots, k, res, s);
     }
     bool use_pool = refresh < 16;
     int np = 0;
@@ -798,10 +824,7 @@ int ace_localize(ace_ctx* c, const ace_grid* g, int norb, const double* psi, dou
     } else {
       // the whole grid is the pool: no certification needed, but every
       // column's residual is
-      if (k > 0 && (!exact || refresh >= 16)) {
-        HIPCHK(c, bounds(psi, ng, ng, k, res));
-        launch_retire(pivots, k, res, s);
-      }
+      if (k > kref || !exact) HIPCHK(c, fold_all());
       launch_qrcp_update(psi, norb, ng, nullptr, res, pv, pi, iv + 1, s);
       const double qbytes = double(norb + 2) * double(ng) * sizeof(double);
       for (int kk = k; kk < norb; ++kk) {

@@ -43,13 +43,12 @@ __global__ void k_symmetrize(const double* __restrict__ M, int n, double* __rest
 
 
 // ---------------------------------------------------------------- SCDM pivot search
-// Residual column norms res[r] = sum_i A[i][r]^2 of ng columns, A = psi [n]
-// with pitch ld.
-__global__ void k_colnorm(const double* __restrict__ A, int n, int64_t ld, int64_t ng, double* __restrict__ res) {
+// Residual column norms res[r] = sum_i A[i][r]^2, A = psi [n][ng].
+__global__ void k_colnorm(const double* __restrict__ A, int n, int64_t ng, double* __restrict__ res) {
   for (int64_t r = blockIdx.x * int64_t(blockDim.x) + threadIdx.x; r < ng; r += int64_t(gridDim.x) * blockDim.x) {
     double s = 0.0;
     for (int i = 0; i < n; ++i) {
-      const double a = A[int64_t(i) * ld + r];
+      const double a = A[int64_t(i) * ng + r];
       s += a * a;
     }
     res[r] = s;
@@ -993,8 +992,8 @@ void launch_neg_sumsq(const double* c, int64_t n, double* out, hipStream_t s) {
 void launch_symmetrize(const double* M, int n, double* out, double* negM, double* ex, double* asym, hipStream_t s) {
   hipLaunchKernelGGL(k_symmetrize, dim3(1), dim3(256), 0, s, M, n, out, negM, ex, asym);
 }
-void launch_colnorm(const double* A, int n, int64_t ld, int64_t ng, double* res, hipStream_t s) {
-  hipLaunchKernelGGL(k_colnorm, dim3(grid_for(ng, 256)), dim3(256), 0, s, A, n, ld, ng, res);
+void launch_colnorm(const double* A, int n, int64_t ng, double* res, hipStream_t s) {
+  hipLaunchKernelGGL(k_colnorm, dim3(grid_for(ng, 256)), dim3(256), 0, s, A, n, ng, res);
 }
 int qrcp_blocks(int64_t ng) { return grid_for(ng, 256, 2048); }
 void launch_qrcp_update(const double* A, int n, int64_t ng, const double* q, double* res, double* pv, int64_t* pi,
