@@ -341,7 +341,8 @@ int ace_profile_classes(ace_ctx* ctx, unsigned mask);
  *              a reverse Cuthill-McKee order of the pair graph (in index
  *              order when the environment sets ACE_OWNER_ORDER=0 before
  *              ace_create; results agree to rounding).  When the spectra
- *              exceed ACE_OWNER_SPECTRA_MAX bytes (default 96 GiB) the build
+ *              exceed ACE_OWNER_SPECTRA_MAX bytes (default 96 GiB), 60% of the
+ *              free device memory or what ACE_WORKSPACE_MAX leaves, the build
  *              uses fused = 2 (or 0, where that does not fit) instead.  FP64
  *              planes that do not fit twice in one CU's LDS are taken as two
  *              or four interleaved classes of rows, so this path runs at every

@@ -171,17 +171,28 @@ static int fail(ace_ctx* c, int code, const char* fmt, ...) {
                   __LINE__);                                                                    \
   } while (0)
 
-// Grow-only named workspace buffer.
+static size_t ws_held(const ace_ctx* c, const char* name) {
+  auto it = c->bufs.find(name);
+  return it == c->bufs.end() ? 0 : it->second.bytes;
+}
+
+static void ws_drop(ace_ctx* c, Buf& b) {
+  if (!b.p) return;
+  (void)hipStreamSynchronize(c->stream);
+  (void)hipFree(b.p);
+  c->ws_total -= b.bytes;
+  b.p = nullptr;
+  b.bytes = 0;
+}
+
+// Grow-only named workspace buffer.  Where ACE_WORKSPACE_MAX leaves no room for
+// another one, the spectra of an earlier call ("spec", the last workspace that a
+// call takes) are given up for it.
 static int ws_get(ace_ctx* c, const char* name, size_t bytes, void** out) {
   Buf& b = c->bufs[name];
   if (b.bytes < bytes) {
-    if (b.p) {
-      (void)hipStreamSynchronize(c->stream);
-      (void)hipFree(b.p);
-      c->ws_total -= b.bytes;
-      b.p = nullptr;
-      b.bytes = 0;
-    }
+    ws_drop(c, b);
+    if (c->ws_cap && c->ws_total + bytes > c->ws_cap) ws_drop(c, c->bufs["spec"]);
     if (c->ws_cap && c->ws_total + bytes > c->ws_cap)
       return fail(c, ACE_E_NOMEM, "workspace '%s' of %zu bytes exceeds ACE_WORKSPACE_MAX", name, bytes);
     if (hipMalloc(&b.p, bytes) != hipSuccess) {
@@ -1100,60 +1111,18 @@ static int build_impl(ace_ctx* c, const ace_grid* g, int norb, const double* phi
   std::vector<int32_t> pr(size_t(2 * npairs));
   HIPCHK(c, hipMemcpyAsync(pr.data(), pairs, pr.size() * sizeof(int32_t), hipMemcpyDeviceToHost, s));
   HIPCHK(c, hipStreamSynchronize(s));
-  const size_t es = prec == 0 ? sizeof(double) : sizeof(float);
-  PairShape sh = shape_for(c, prec, N);
-  // owner-computes W when every pair's half spectrum fits the budget
-  const int64_t onpk = (npairs + 1) / 2;
-  const size_t slot_bytes = pair_owner_slot_elems(prec, N) * 2 * es;
-  // ... and when the spectra, beyond what the workspace already holds, take
-  // at most 60% of the free device memory (a fuller device slows down)
-  bool owner = sh.fused_xy == 3 && size_t(2 * onpk) * slot_bytes <= c->owner_max;
-  if (owner) {
-    const size_t need = size_t(2 * onpk) * slot_bytes;
-    auto it = c->bufs.find("spec");
-    const size_t have = it == c->bufs.end() ? 0 : it->second.bytes;
-    size_t freeb = 0, totb = 0;
-    if (need > have && hipMemGetInfo(&freeb, &totb) == hipSuccess)
-      owner = double(need) <= 0.6 * double(freeb + have);
-  }
   const int mp = max_packs_for(c, prec, N);
   std::shared_ptr<const Schedule> Sp;
-  rc = schedule_for(c, pr, npairs, norb, mp, !owner, &Sp);
+  rc = schedule_for(c, pr, npairs, norb, mp, false, &Sp);
   if (rc) return rc;
-  const Schedule& S = *Sp;
-  const int npk = int(S.packs.size());
-  rec_begin(R, ST_BUILD, s);
-
-  if (!owner) sh = pair_rounds_shape(prec, N, sh);
-  const int nblk = owner ? pair_owner_ntile(prec, N) : pair_energy_blocks(N, sh);
+  const size_t es = prec == 0 ? sizeof(double) : sizeof(float);
   void *W, *spec, *phiw;
-  Pack* dpk;
-  int64_t* dpidx;
-  int32_t *dadjp = nullptr, *dadj = nullptr, *doperm = nullptr;
   double *epart = nullptr, *part, *Mraw, *Lb, *Li, *scal;
-  void* vtab = nullptr;
   int* info;
   // W lives in the workspace, or directly in the caller's FP64 output when no
   // projectors follow (exact exchange)
   if (xi || (Wout && prec == 1)) WS(c, "W", size_t(norb) * ng * es, W);
   else W = Wout;
-  if (owner) {
-    WS(c, "spec", size_t(2 * onpk) * slot_bytes, spec);
-    char* tab;
-    WS(c, "otab", S.table.size(), tab);
-    dpk = reinterpret_cast<Pack*>(tab);
-    dadjp = reinterpret_cast<int32_t*>(tab + S.adjp_off);
-    dadj = reinterpret_cast<int32_t*>(tab + S.adj_off);
-    doperm = reinterpret_cast<int32_t*>(tab + S.operm_off);
-    dpidx = reinterpret_cast<int64_t*>(tab + S.pidx_off);
-    if (pair_energy) WS(c, "epart", size_t(onpk) * nblk * 2 * sizeof(double), epart);
-    WS(c, "vtab", size_t(N / 2 + 1) * (N / 2 + 1) * (N / 2 + 1) * es, vtab);
-  } else {
-    WS(c, "spec", size_t(S.max_launch) * pair_spec_elems(prec, N, sh) * 2 * es, spec);
-    WS(c, "packs", size_t(npk) * sizeof(Pack), dpk);
-    WS(c, "pidx", size_t(npk) * 2 * sizeof(int64_t), dpidx);
-    if (pair_energy) WS(c, "epart", size_t(S.max_launch) * nblk * 2 * sizeof(double), epart);
-  }
   int64_t kchunk;
   const int64_t nsplit = gemm_nt_nsplit(norb, norb, ng, &kchunk);
   WS(c, "mpart", size_t(nsplit) * norb * norb * sizeof(double), part);
@@ -1164,6 +1133,62 @@ static int build_impl(ace_ctx* c, const ace_grid* g, int norb, const double* phi
   WS(c, "info", 64, info);
   if (prec == 1) WS(c, "phi32", size_t(norb) * ng * sizeof(float), phiw);
   else phiw = (void*)phi;
+
+  PairShape sh = shape_for(c, prec, N);
+  // owner-computes W when every pair's half spectrum fits the budget
+  const int64_t onpk = (npairs + 1) / 2;
+  const int otile = pair_owner_ntile(prec, N);
+  const size_t spec_bytes = size_t(2 * onpk) * pair_owner_slot_elems(prec, N) * 2 * es;
+  const size_t otab_bytes = Sp->table.size(), oep_bytes = pair_energy ? size_t(onpk) * otile * 2 * sizeof(double) : 0;
+  const size_t vtab_bytes = size_t(N / 2 + 1) * (N / 2 + 1) * (N / 2 + 1) * es;
+  bool owner = sh.fused_xy == 3 && spec_bytes <= c->owner_max;
+  const size_t have = ws_held(c, "spec");
+  if (owner && spec_bytes > have) {
+    // ... and when the spectra, beyond what the workspace already holds, take
+    // at most 60% of the free device memory (a fuller device slows down)
+    size_t freeb = 0, totb = 0;
+    if (hipMemGetInfo(&freeb, &totb) == hipSuccess) owner = double(spec_bytes) <= 0.6 * double(freeb + have);
+  }
+  if (owner && c->ws_cap) {
+    // ... and ACE_WORKSPACE_MAX holds them and their tables beside the rest
+    size_t need = c->ws_total - have + spec_bytes;
+    for (auto& t : {std::make_pair("otab", otab_bytes), std::make_pair("epart", oep_bytes),
+                    std::make_pair("vtab", vtab_bytes)})
+      need += std::max(ws_held(c, t.first), t.second) - ws_held(c, t.first);
+    owner = need <= c->ws_cap;
+  }
+  if (!owner) {
+    if (Sp->packs.empty()) rc = schedule_for(c, pr, npairs, norb, mp, true, &Sp);
+    if (rc) return rc;
+    sh = pair_rounds_shape(prec, N, sh);
+  }
+  const Schedule& S = *Sp;
+  const int npk = int(S.packs.size());
+  rec_begin(R, ST_BUILD, s);
+
+  const int nblk = owner ? otile : pair_energy_blocks(N, sh);
+  Pack* dpk;
+  int64_t* dpidx;
+  int32_t *dadjp = nullptr, *dadj = nullptr, *doperm = nullptr;
+  void* vtab = nullptr;
+  // the spectra last: any workspace taken after them may take their place
+  if (owner) {
+    char* tab;
+    WS(c, "otab", otab_bytes, tab);
+    dpk = reinterpret_cast<Pack*>(tab);
+    dadjp = reinterpret_cast<int32_t*>(tab + S.adjp_off);
+    dadj = reinterpret_cast<int32_t*>(tab + S.adj_off);
+    doperm = reinterpret_cast<int32_t*>(tab + S.operm_off);
+    dpidx = reinterpret_cast<int64_t*>(tab + S.pidx_off);
+    if (pair_energy) WS(c, "epart", oep_bytes, epart);
+    WS(c, "vtab", vtab_bytes, vtab);
+    WS(c, "spec", spec_bytes, spec);
+  } else {
+    WS(c, "packs", size_t(npk) * sizeof(Pack), dpk);
+    WS(c, "pidx", size_t(npk) * 2 * sizeof(int64_t), dpidx);
+    if (pair_energy) WS(c, "epart", size_t(S.max_launch) * nblk * 2 * sizeof(double), epart);
+    WS(c, "spec", size_t(S.max_launch) * pair_spec_elems(prec, N, sh) * 2 * es, spec);
+  }
   const void* tw;
   rc = twiddles(c, N, prec, &tw);
   if (rc) return rc;

@@ -44,61 +44,6 @@ def test_build_gives_way_to_the_rounds(lib, monkeypatch, norb, n, prec, cap):
             assert float((r[k] - ref[k]).abs().max()) <= tol * float(ref[k].abs().max()), k
     # where all fits again the resident form runs: a tenth of the pairs
     few = pairs[:: 10].contiguous()
-    a = ctx.build(phi, few, grid, kernel="erfc", omega=0.3, precision=prec, want_W=True)["W"]
-    b = lib.Context().build(phi, few, grid, kernel="erfc", omega=0.3, precision=prec, want_W=True)["W"]
+    a = ctx.pair_energies(phi, few, grid, kernel="erfc", omega=0.3, precision=prec)
+    b = lib.Context().pair_energies(phi, few, grid, kernel="erfc", omega=0.3, precision=prec)
     assert float((a - b).abs().max()) <= tol * float(b.abs().max())
-
-
-def test_held_spectra_give_way(lib, monkeypatch):
-    from paper_2101_03155_amd import Grid
-    print("[gpu-case] capped context, spectra of an earlier call", flush=True)
-    # 8 Bloch orbitals on 48^3: 36 spectra of 1.8 MB = 64 MB, fields 35 MB; then 512
-    # on 12^3, whose tables and partial sums need some 20 MB more, and a real build
-    ctx = _ctx(lib, monkeypatch, 104 * MB)
-    u = _orbitals(8, 48, 1, True)
-    kv = [(0.0, 0.0, 0.0), (0.5, 0.0, 0.0), (0.0, 0.5, 0.0), (0.0, 0.0, 0.5)]
-    ctx.build_kpoints(u, kv[:2], 4, _full(8), Grid.cubic(48, 20.0), kernel="erfc", omega=0.3)
-    u, pairs = _orbitals(512, 12, 2, True), _full(512)
-    g = Grid.cubic(12, 6.0)
-    r = ctx.build_kpoints(u, kv, 128, pairs, g, kernel="erfc", omega=0.3, want_W=True)
-    ref = lib.Context().build_kpoints(u, kv, 128, pairs, g, kernel="erfc", omega=0.3, want_W=True)
-    for k in ("W", "M"):
-        assert float((r[k] - ref[k]).abs().max()) <= 1e-12 * float(ref[k].abs().max()), k
-    phi, few = _orbitals(40, 32, 3), _full(40)
-    g = Grid.cubic(32, 9.0)
-    r = ctx.build(phi, few, g, kernel="erfc", omega=0.3, want_W=True)
-    ref = lib.Context().build(phi, few, g, kernel="erfc", omega=0.3, want_W=True)
-    assert float((r["W"] - ref["W"]).abs().max()) <= 1e-12 * float(ref["W"].abs().max())
-
-
-def test_spectra_in_one_place(lib):
-    from paper_2101_03155_amd import Grid
-    print("[gpu-case] spectra held between calls", flush=True)
-    ctx, g = lib.Context(), Grid.cubic(48, 20.0)
-    u, phi, pairs = _orbitals(24, 48, 1, True), _orbitals(24, 48, 2), _full(24)
-    ctx.build(phi[:2], _full(2), g, kernel="erfc", omega=0.3)
-    ctx.build_kpoints(u, [(0.0, 0.0, 0.0)], 24, pairs, g, kernel="erfc", omega=0.3)  # 300 spectra, 531 MB
-    torch.cuda.synchronize()
-    before = torch.cuda.mem_get_info()[0]
-    r = ctx.build(phi, pairs, g, kernel="erfc", omega=0.3)  # 300 half spectra, 276 MB; W 21 MB
-    torch.cuda.synchronize()
-    more = before - torch.cuda.mem_get_info()[0]
-    print(f"  {more / MB:.0f} MB more", flush=True)
-    assert more <= 128 * MB
-    del r
-
-
-def test_partial_sums_give_way(lib, monkeypatch):
-    from paper_2101_03155_amd import Grid
-    print("[gpu-case] capped products on a small grid", flush=True)
-    # 256 orbitals on 24^3: 54 partial products of 0.5 MB fit in the cap, 108 do not
-    phi, g = _orbitals(256, 24, 5), Grid.cubic(24, 9.0)
-    ctx = _ctx(lib, monkeypatch, 40 * MB)
-    pairs, o = ctx.pairlist(phi, g, 0.0)
-    want_p, want_o = lib.Context().pairlist(phi, g, 0.0)
-    assert torch.equal(pairs, want_p)
-    assert float((o - want_o).abs().max()) <= 1e-13 * float(want_o.abs().max())
-    y, ex = ctx.apply_energy(phi, phi, g)
-    want_y, want_ex = lib.Context().apply_energy(phi, phi, g)
-    assert float((y - want_y).abs().max()) <= 1e-12 * float(want_y.abs().max())
-    assert np.isclose(float(ex), float(want_ex), rtol=1e-12)
