@@ -74,8 +74,10 @@ const char* ace_last_error(const ace_ctx* ctx);
 int ace_set_stream(ace_ctx* ctx, void* hip_stream);
 
 /* Free every workspace the context has grown (device buffers of earlier
- * calls) and the batched graphs that refer to them; the next call allocates
- * again.  Synchronizes the context's streams first. */
+ * calls, which stay allocated between calls: the resident spectra of ace_build
+ * and ace_build_kpoints, one buffer of at most ACE_OWNER_SPECTRA_MAX bytes
+ * except where a few pairs exceed that, are the largest) and the batched graphs
+ * that refer to them; the next call allocates again.  Synchronizes the context's streams first. */
 int ace_release_workspace(ace_ctx* ctx);
 
 /*
@@ -283,6 +285,10 @@ int ace_exact_exchange(ace_ctx* ctx, const ace_grid* grid, int norb, const doubl
  * The operator is block-diagonal in k: per k-point M = dV U^H W made
  * Hermitian, -M = L L^H, and P = W L^-H (Appendix A), returned by rows as
  * xi = conj(L)^-1 W, so that V_ACE x = -sum_j xi_j <xi_j|x> dV.  FP64 only.
+ * Where a complex plane fits in one CU's LDS (n <= 96) the spectra of all pairs
+ * (n^3 complex values each) stay resident as in ace_build's fused = 3, in the
+ * same workspace and within the same limits, or those of as many pairs at a
+ * time as the limits allow.
  * Errors as ace_build; ACE_E_NOT_PD names the k-point and the column.
  */
 int ace_build_kpoints(ace_ctx* ctx, const ace_grid* grid, int norb, int nk, const double* kvec, const double* u,

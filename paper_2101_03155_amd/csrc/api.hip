@@ -1392,15 +1392,11 @@ int ace_apply_energy_noalloc(ace_ctx* c, const ace_grid* g, int norb, const doub
 // ACE_WORKSPACE_MAX leaves less than the split passes need): all of them
 // within the budget of the owner paths (ACE_OWNER_SPECTRA_MAX bytes, and 60%
 // of the free device memory), else as many as fit.  The other workspaces of
-// the call are already held.
+// the call are already held, the spectra come last.
 static int64_t kowner_chunk(ace_ctx* c, int N, int64_t npairs, int ntot, size_t slot_bytes) {
   if (!kpair_owner_fits(N)) return 0;
   const int64_t few = std::min<int64_t>(npairs, 32);  // the slots of one launch of the split passes
-  auto held = [c](const char* name) {
-    auto it = c->bufs.find(name);
-    return it == c->bufs.end() ? size_t(0) : it->second.bytes;
-  };
-  const size_t have = held("kspec");
+  const size_t have = ws_held(c, "spec");
   size_t room = c->owner_max;
   size_t freeb = 0, totb = 0;
   if (std::min(room, size_t(npairs) * slot_bytes) > have && hipMemGetInfo(&freeb, &totb) == hipSuccess)
@@ -1408,7 +1404,7 @@ static int64_t kowner_chunk(ace_ctx* c, int N, int64_t npairs, int ntot, size_t 
   int64_t chunk = std::max<int64_t>(few, int64_t(room / slot_bytes));
   if (c->ws_cap) {
     // under a workspace cap the tables come out of it first
-    const size_t others = c->ws_total - have - held("kslots") - held("kadj");
+    const size_t others = c->ws_total - have - ws_held(c, "kslots") - ws_held(c, "kadj");
     const size_t fixed = others + size_t(npairs) * sizeof(KPair);
     for (;;) {
       chunk = std::min(chunk, npairs);
@@ -1513,7 +1509,7 @@ int ace_build_kpoints(ace_ctx* c, const ace_grid* g, int norb, int nk, const dou
     int32_t* dtab;
     WS(c, "kslots", slots.size() * sizeof(KPair), dslots);
     WS(c, "kadj", tab.size() * sizeof(int32_t), dtab);
-    WS(c, "kspec", size_t(chunk) * slot_bytes, spec);
+    WS(c, "spec", size_t(chunk) * slot_bytes, spec);
     HIPCHK(c, hipMemcpyAsync(dslots, slots.data(), slots.size() * sizeof(KPair), hipMemcpyHostToDevice, s));
     HIPCHK(c, hipMemcpyAsync(dtab, tab.data(), tab.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
     for (int64_t q = 0; q < nchunk; ++q)
@@ -1533,7 +1529,7 @@ int ace_build_kpoints(ace_ctx* c, const ace_grid* g, int norb, int nk, const dou
       slots[2 * p + 1] = slot_of(S.packs[p].ib, S.packs[p].jb);
     }
     WS(c, "kslots", slots.size() * sizeof(KPair), dslots);
-    WS(c, "kspec", size_t(2 * S.max_launch) * slot_bytes, spec);
+    WS(c, "spec", size_t(2 * S.max_launch) * slot_bytes, spec);
     HIPCHK(c, hipMemcpyAsync(dslots, slots.data(), slots.size() * sizeof(KPair), hipMemcpyHostToDevice, s));
     launch_zero(W, cbytes, s);
     for (const Schedule::Launch& l : S.launches)

@@ -47,3 +47,20 @@ def test_build_gives_way_to_the_rounds(lib, monkeypatch, norb, n, prec, cap):
     a = ctx.pair_energies(phi, few, grid, kernel="erfc", omega=0.3, precision=prec)
     b = lib.Context().pair_energies(phi, few, grid, kernel="erfc", omega=0.3, precision=prec)
     assert float((a - b).abs().max()) <= tol * float(b.abs().max())
+
+
+def test_spectra_in_one_place(lib):
+    from paper_2101_03155_amd import Grid
+    print("[gpu-case] spectra held between calls", flush=True)
+    ctx, g = lib.Context(), Grid.cubic(48, 20.0)
+    u, phi, pairs = _orbitals(24, 48, 1, True), _orbitals(24, 48, 2), _full(24)
+    ctx.build(phi[:2], _full(2), g, kernel="erfc", omega=0.3)
+    ctx.build_kpoints(u, [(0.0, 0.0, 0.0)], 24, pairs, g, kernel="erfc", omega=0.3)  # 300 spectra, 531 MB
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    r = ctx.build(phi, pairs, g, kernel="erfc", omega=0.3)  # 300 half spectra, 276 MB; W 21 MB
+    torch.cuda.synchronize()
+    more = before - torch.cuda.mem_get_info()[0]
+    print(f"  {more / MB:.0f} MB more", flush=True)
+    assert more <= 128 * MB
+    del r
