@@ -1403,14 +1403,15 @@ static int64_t kowner_chunk(ace_ctx* c, int N, int64_t npairs, int ntot, size_t 
     room = std::min(room, size_t(0.6 * double(freeb + have)));
   int64_t chunk = std::max<int64_t>(few, int64_t(room / slot_bytes));
   if (c->ws_cap) {
-    // under a workspace cap the tables come out of it first
-    const size_t others = c->ws_total - have - ws_held(c, "kslots") - ws_held(c, "kadj");
-    const size_t fixed = others + size_t(npairs) * sizeof(KPair);
+    // under a workspace cap the tables come out of it first (a workspace never
+    // shrinks, the spectra held are freed where they are in the way)
+    const size_t ks = ws_held(c, "kslots"), ka = ws_held(c, "kadj");
+    const size_t fixed = c->ws_total - have - ks - ka + std::max(ks, size_t(npairs) * sizeof(KPair));
     for (;;) {
       chunk = std::min(chunk, npairs);
       const int64_t nchunk = (npairs + chunk - 1) / chunk;
       const size_t tab = (size_t(nchunk) * (size_t(ntot) + 1) + 4 * size_t(npairs) + size_t(ntot)) * sizeof(int32_t);
-      if (fixed + tab + size_t(chunk) * slot_bytes <= c->ws_cap) break;
+      if (fixed + std::max(ka, tab) + size_t(chunk) * slot_bytes <= c->ws_cap) break;
       if (chunk <= few) return 0;
       chunk = std::max(few, chunk / 2);
     }

@@ -64,3 +64,30 @@ def test_spectra_in_one_place(lib):
     print(f"  {more / MB:.0f} MB more", flush=True)
     assert more <= 128 * MB
     del r
+
+
+def test_held_spectra_give_way(lib, monkeypatch):
+    from paper_2101_03155_amd import Grid
+    print("[gpu-case] capped context, spectra of an earlier call", flush=True)
+    # 8 Bloch orbitals on 48^3: 36 spectra of 1.8 MB = 64 MB, fields 35 MB; then 512
+    # on 12^3, whose tables and partial sums need some 20 MB more, and a real build
+    ctx = _ctx(lib, monkeypatch, 104 * MB)
+    u = _orbitals(8, 48, 1, True)
+    kv = [(0.0, 0.0, 0.0), (0.5, 0.0, 0.0), (0.0, 0.5, 0.0), (0.0, 0.0, 0.5)]
+    ctx.build_kpoints(u, kv[:2], 4, _full(8), Grid.cubic(48, 20.0), kernel="erfc", omega=0.3)
+    u, pairs = _orbitals(512, 12, 2, True), _full(512)
+    g = Grid.cubic(12, 6.0)
+    r = ctx.build_kpoints(u, kv, 128, pairs, g, kernel="erfc", omega=0.3, want_W=True)
+    ref = lib.Context().build_kpoints(u, kv, 128, pairs, g, kernel="erfc", omega=0.3, want_W=True)
+    for k in ("W", "M"):
+        assert float((r[k] - ref[k]).abs().max()) <= 1e-12 * float(ref[k].abs().max()), k
+    # 10 on 48^3: beside the tables held by now 32 spectra no longer fit
+    u, g = _orbitals(10, 48, 4, True), Grid.cubic(48, 20.0)
+    r = ctx.build_kpoints(u, kv[:2], 5, _full(10), g, kernel="erfc", omega=0.3, want_W=True)
+    ref = lib.Context().build_kpoints(u, kv[:2], 5, _full(10), g, kernel="erfc", omega=0.3, want_W=True)
+    assert float((r["W"] - ref["W"]).abs().max()) <= 1e-12 * float(ref["W"].abs().max())
+    phi, few = _orbitals(40, 32, 3), _full(40)
+    g = Grid.cubic(32, 9.0)
+    r = ctx.build(phi, few, g, kernel="erfc", omega=0.3, want_W=True)
+    ref = lib.Context().build(phi, few, g, kernel="erfc", omega=0.3, want_W=True)
+    assert float((r["W"] - ref["W"]).abs().max()) <= 1e-12 * float(ref["W"].abs().max())
