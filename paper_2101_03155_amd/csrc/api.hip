@@ -213,6 +213,16 @@ static int ws_get(ace_ctx* c, const char* name, size_t bytes, void** out) {
     if (rc__ != ACE_OK) return rc__;                                \
   } while (0)
 
+// Split count that the partial sums of an M x Nn x K gemm_nt have room for, and
+// *cap, what the product is told of it (0: its own choice).  FP64 products of small
+// grids take chunks of K down to 64, up to four times the partial sums of chunks
+// of 256; under ACE_WORKSPACE_MAX they keep to the latter's number.
+static int64_t split_room(const ace_ctx* c, int M, int Nn, int64_t K, int64_t* cap) {
+  int64_t kchunk;
+  *cap = c->ws_cap ? gemm_nt_nsplit(M, Nn, K, &kchunk, true, 0, 1) : 0;
+  return *cap ? *cap : gemm_nt_nsplit(M, Nn, K, &kchunk);
+}
+
 static int check_grid(ace_ctx* c, const ace_grid* g, int norb) {
   if (!g) return fail(c, ACE_E_ARG, "grid is NULL");
   if (norb < 1 || norb > 512) return fail(c, ACE_E_ARG, "norb=%d outside [1, 512]", norb);
@@ -976,12 +986,12 @@ static int pairlist_core(ace_ctx* c, const ace_grid* g, int norb, const double* 
   rec_begin(c->R(), ST_PAIRLIST, s);
   double *part, *O;
   int64_t* cnt;
-  int64_t kchunk;
-  const int64_t nsplit = gemm_nt_nsplit(norb, norb, ng, &kchunk);
+  int64_t cap;
+  const int64_t nsplit = split_room(c, norb, norb, ng, &cap);
   WS(c, "mpart", size_t(nsplit) * norb * norb * sizeof(double), part);
   WS(c, "O", size_t(norb) * norb * sizeof(double), O);
   WS(c, "cnt", 64, cnt);
-  HIPCHK(c, gemm_nt(0, 1, phi, ng, phi, ng, norb, norb, ng, grid_dv(g), part, O, s, c->R(), true));
+  HIPCHK(c, gemm_nt(0, 1, phi, ng, phi, ng, norb, norb, ng, grid_dv(g), part, O, s, c->R(), true, cap));
   launch_compact_pairs(O, norb, rho_cut, capacity, pairs, overlap, cnt, s);
   int64_t h = 0;
   HIPCHK(c, hipMemcpyAsync(&h, cnt, sizeof(int64_t), hipMemcpyDeviceToHost, s));
@@ -1007,11 +1017,11 @@ int ace_pairlist_device(ace_ctx* c, const ace_grid* g, int norb, const double* p
   const int64_t ng = grid_size(g);
   hipStream_t s = c->stream;
   double *part, *O;
-  int64_t kchunk;
-  const int64_t nsplit = gemm_nt_nsplit(norb, norb, ng, &kchunk);
+  int64_t cap;
+  const int64_t nsplit = split_room(c, norb, norb, ng, &cap);
   WS(c, "mpart", size_t(nsplit) * norb * norb * sizeof(double), part);
   WS(c, "O", size_t(norb) * norb * sizeof(double), O);
-  HIPCHK(c, gemm_nt(0, 1, phi, ng, phi, ng, norb, norb, ng, grid_dv(g), part, O, s, nullptr, true));
+  HIPCHK(c, gemm_nt(0, 1, phi, ng, phi, ng, norb, norb, ng, grid_dv(g), part, O, s, nullptr, true, cap));
   launch_compact_pairs(O, norb, rho_cut, capacity, pairs, overlap, npairs_dev, s);
   HIPCHK(c, hipGetLastError());
   return ACE_OK;
@@ -1123,8 +1133,8 @@ static int build_impl(ace_ctx* c, const ace_grid* g, int norb, const double* phi
   // projectors follow (exact exchange)
   if (xi || (Wout && prec == 1)) WS(c, "W", size_t(norb) * ng * es, W);
   else W = Wout;
-  int64_t kchunk;
-  const int64_t nsplit = gemm_nt_nsplit(norb, norb, ng, &kchunk);
+  int64_t cap;
+  const int64_t nsplit = split_room(c, norb, norb, ng, &cap);
   WS(c, "mpart", size_t(nsplit) * norb * norb * sizeof(double), part);
   WS(c, "Mraw", size_t(norb) * norb * sizeof(double), Mraw);
   WS(c, "Lc", size_t(norb) * norb * sizeof(double), Lb);
@@ -1240,7 +1250,7 @@ static int build_impl(ace_ctx* c, const ace_grid* g, int norb, const double* phi
 
   // (d) M = dV Phi W^T, symmetrize, -M = L L^T
   rec_begin(R, ST_TAIL, s);
-  HIPCHK(c, gemm_nt(prec, 0, phiw, ng, W, ng, norb, norb, ng, dV, part, Mraw, s, R));
+  HIPCHK(c, gemm_nt(prec, 0, phiw, ng, W, ng, norb, norb, ng, dV, part, Mraw, s, R, false, cap));
   launch_symmetrize(Mraw, norb, Mout, Lb, ex ? ex : scal, scal + 1, s);
   if (!xi) {  // exact exchange: W, M and E_x only
     rec_end(R, ST_TAIL, s);
@@ -1301,11 +1311,11 @@ static int apply_impl(ace_ctx* c, const ace_grid* g, int norb, const double* xi,
   const int64_t ng = grid_size(g);
   hipStream_t s = c->stream;
   double *part, *cb;
-  int64_t kchunk;
-  const int64_t nsplit = gemm_nt_nsplit(norb, nvec, ng, &kchunk);
+  int64_t cap;
+  const int64_t nsplit = split_room(c, norb, nvec, ng, &cap);
   WS(c, "apart", size_t(nsplit) * norb * nvec * sizeof(double), part);
   WS(c, "coef", size_t(norb) * nvec * sizeof(double), cb);
-  HIPCHK(c, gemm_nt(0, 0, xi, ng, x, ng, norb, nvec, ng, grid_dv(g), part, cb, s, c->R()));
+  HIPCHK(c, gemm_nt(0, 0, xi, ng, x, ng, norb, nvec, ng, grid_dv(g), part, cb, s, c->R(), false, cap));
   HIPCHK(c, gemm_ls(0, true, false, cb, nvec, xi, ng, y, ng, nvec, norb, ng, -1.0, s, c->R()));
   if (ex) launch_neg_sumsq(cb, int64_t(norb) * nvec, ex, s);
   HIPCHK(c, hipGetLastError());
@@ -1453,8 +1463,8 @@ int ace_build_kpoints(ace_ctx* c, const ace_grid* g, int norb, int nk, const dou
   KPair* dslots;
   double *spec, *W, *Wm, *Mre, *Mim, *part, *negM, *Lr, *Li, *X2;
   int* info;
-  int64_t kchunk;
-  const int64_t nsplit = gemm_nt_nsplit(norb, norb, 2 * ng, &kchunk);
+  int64_t cap;
+  const int64_t nsplit = split_room(c, norb, norb, 2 * ng, &cap);
   if (Wout) W = Wout; else WS(c, "kW", cbytes, W);
   WS(c, "kWm", cbytes, Wm);
   WS(c, "kMre", size_t(nk) * norb * norb * sizeof(double), Mre);
@@ -1541,8 +1551,10 @@ int ace_build_kpoints(ace_ctx* c, const ace_grid* g, int norb, int nk, const dou
   for (int q = 0; q < nk; ++q) {
     const size_t ro = size_t(q) * norb * ng * 2;
     const size_t mo = size_t(q) * norb * norb;
-    HIPCHK(c, gemm_nt(0, 0, u + ro, 2 * ng, W + ro, 2 * ng, norb, norb, 2 * ng, dV, part, Mre + mo, s, nullptr));
-    HIPCHK(c, gemm_nt(0, 0, u + ro, 2 * ng, Wm + ro, 2 * ng, norb, norb, 2 * ng, dV, part, Mim + mo, s, nullptr));
+    HIPCHK(c, gemm_nt(0, 0, u + ro, 2 * ng, W + ro, 2 * ng, norb, norb, 2 * ng, dV, part, Mre + mo, s, nullptr,
+                      false, cap));
+    HIPCHK(c, gemm_nt(0, 0, u + ro, 2 * ng, Wm + ro, 2 * ng, norb, norb, 2 * ng, dV, part, Mim + mo, s, nullptr,
+                      false, cap));
   }
   launch_hermitize(Mre, Mim, norb, nk, Mout, negM, s);
   if (ex) launch_trace_avg(Mre, norb, nk, ex, s);
@@ -1798,6 +1810,7 @@ int ace_build_batched(ace_ctx* c, int nsys, ace_system* sys, int prec, int mode)
   std::vector<int64_t> w_off(nsys), m_off(nsys);
   int max_norb = 0;
   int64_t max_nsplit = 1;
+  std::vector<int64_t> split_cap(static_cast<size_t>(nsys));
   for (int q = 0; q < nsys; ++q) {
     const int64_t ng = grid_size(&sys[q].grid);
     w_off[q] = w_total;
@@ -1805,8 +1818,7 @@ int ace_build_batched(ace_ctx* c, int nsys, ace_system* sys, int prec, int mode)
     m_off[q] = m_total;
     m_total += int64_t(sys[q].norb) * sys[q].norb;
     max_norb = std::max(max_norb, sys[q].norb);
-    int64_t kc;
-    max_nsplit = std::max(max_nsplit, gemm_nt_nsplit(sys[q].norb, sys[q].norb, ng, &kc));
+    max_nsplit = std::max(max_nsplit, split_room(c, sys[q].norb, sys[q].norb, ng, &split_cap[size_t(q)]));
   }
   char *bW, *bphi = nullptr, *bspec;
   double *part, *Mraw, *Lb, *Li, *exs;
@@ -1950,7 +1962,8 @@ int ace_build_batched(ace_ctx* c, int nsys, ace_system* sys, int prec, int mode)
       const int64_t ng = grid_size(&y.grid);
       const void* W = bW + size_t(w_off[q]) * es;
       const void* ph = prec == 0 ? (const void*)y.phi : (const void*)(bphi + size_t(w_off[q]) * es);
-      hipError_t e = gemm_nt(prec, 0, ph, ng, W, ng, n, n, ng, grid_dv(&y.grid), bpart, bM, sb, nullptr);
+      hipError_t e = gemm_nt(prec, 0, ph, ng, W, ng, n, n, ng, grid_dv(&y.grid), bpart, bM, sb, nullptr, false,
+                             split_cap[size_t(q)]);
       if (e != hipSuccess) return fail(c, ACE_E_HIP, "batched M launch failed: %s", hipGetErrorString(e));
       launch_symmetrize(bM, n, y.M, bL, y.ex ? y.ex : exs + 2 * q, exs + 2 * q + 1, sb);
       launch_chol_inv(bL, n, infos + q, bLi, sb);
@@ -2025,8 +2038,8 @@ static int features_impl(ace_ctx* c, const ace_grid* g, int norb, const double* 
   double* sub = nullptr;
   if (stride > 1) WS(c, "f_sub", size_t(norb) * ngs * sizeof(double), sub);
   const double* phis = sub ? sub : phi;
-  int64_t kchunk;
-  const int64_t nsplit = gemm_nt_nsplit(norb, norb, ngs, &kchunk);
+  int64_t cap;
+  const int64_t nsplit = split_room(c, norb, norb, ngs, &cap);
   WS(c, "f_pz", size_t(norb) * n * sizeof(double), pz);
   WS(c, "f_py", size_t(norb) * n * n * sizeof(double), py);
   WS(c, "f_px", size_t(norb) * n * n * sizeof(double), px);
@@ -2037,8 +2050,8 @@ static int features_impl(ace_ctx* c, const ace_grid* g, int norb, const double* 
   WS(c, "mpart", size_t(nsplit) * norb * norb * sizeof(double), part);
   launch_marginals(phi, norb, n, stride, pz, py, px, sub, s);
   launch_centroids(pz, py, px, norb, n, g->L[0], grid_dv(g), cen, spr, s);
-  HIPCHK(c, gemm_nt(0, 1, phis, ngs, phis, ngs, norb, norb, ngs, dVs, part, O, s, nullptr, true));
-  HIPCHK(c, gemm_nt(0, 2, phis, ngs, phis, ngs, norb, norb, ngs, dVs, part, P, s, nullptr, true));
+  HIPCHK(c, gemm_nt(0, 1, phis, ngs, phis, ngs, norb, norb, ngs, dVs, part, O, s, nullptr, true, cap));
+  HIPCHK(c, gemm_nt(0, 2, phis, ngs, phis, ngs, norb, norb, ngs, dVs, part, P, s, nullptr, true, cap));
   (void)ng;
   launch_pair_features(pairs, np, norb, cen, spr, O, P, g->L[0], feats, s);
   HIPCHK(c, hipGetLastError());

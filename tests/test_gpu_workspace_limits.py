@@ -91,3 +91,19 @@ def test_held_spectra_give_way(lib, monkeypatch):
     r = ctx.build(phi, few, g, kernel="erfc", omega=0.3, want_W=True)
     ref = lib.Context().build(phi, few, g, kernel="erfc", omega=0.3, want_W=True)
     assert float((r["W"] - ref["W"]).abs().max()) <= 1e-12 * float(ref["W"].abs().max())
+
+
+def test_partial_sums_give_way(lib, monkeypatch):
+    from paper_2101_03155_amd import Grid
+    print("[gpu-case] capped products on a small grid", flush=True)
+    # 256 orbitals on 24^3: 54 partial products of 0.5 MB fit in the cap, 108 do not
+    phi, g = _orbitals(256, 24, 5), Grid.cubic(24, 9.0)
+    ctx = _ctx(lib, monkeypatch, 40 * MB)
+    pairs, o = ctx.pairlist(phi, g, 0.0)
+    want_p, want_o = lib.Context().pairlist(phi, g, 0.0)
+    assert torch.equal(pairs, want_p)
+    assert float((o - want_o).abs().max()) <= 1e-13 * float(want_o.abs().max())
+    y, ex = _ctx(lib, monkeypatch, 40 * MB).apply_energy(phi, phi, g)
+    want_y, want_ex = lib.Context().apply_energy(phi, phi, g)
+    assert float((y - want_y).abs().max()) <= 1e-12 * float(want_y.abs().max())
+    assert np.isclose(float(ex), float(want_ex), rtol=1e-12)
