@@ -15,6 +15,7 @@
 
 #include "../../include/ace.h"
 #include "ace_internal.h"
+#include "kpoint_tables.h"
 
 namespace ace {
 
@@ -1498,25 +1499,9 @@ int ace_build_kpoints(ace_ctx* c, const ace_grid* g, int norb, int nk, const dou
     for (int64_t p = 0; p < npairs; ++p) slots[size_t(p)] = slot_of(pr[size_t(2 * p)], pr[size_t(2 * p + 1)]);
     const int64_t nchunk = (npairs + chunk - 1) / chunk;
     const size_t np1 = size_t(ntot) + 1;
-    std::vector<int32_t> tab;  // per chunk its offsets (ntot + 1), then every chunk's entries, then the order
-    std::vector<int32_t> ent;
-    tab.reserve(size_t(nchunk) * np1 + S.adj.size() + size_t(ntot));
-    for (int64_t q = 0; q < nchunk; ++q) {
-      for (int k = 0; k < ntot; ++k) {
-        tab.push_back(int32_t(ent.size() / 2));
-        for (int a = S.adj_ptr[size_t(k)]; a < S.adj_ptr[size_t(k) + 1]; ++a) {
-          const int64_t p = S.adj[size_t(2 * a)] - q * chunk;
-          if (p < 0 || p >= chunk) continue;
-          ent.push_back(int32_t(p));
-          ent.push_back(S.adj[size_t(2 * a + 1)]);
-        }
-      }
-      tab.push_back(int32_t(ent.size() / 2));
-    }
-    const size_t ent_off = tab.size();
-    tab.insert(tab.end(), ent.begin(), ent.end());
-    const size_t perm_off = tab.size();
-    tab.insert(tab.end(), S.operm.begin(), S.operm.end());
+    std::vector<int32_t> tab;
+    size_t ent_off, perm_off;
+    make_kowner_tables(S.adj_ptr, S.adj, S.operm, chunk, nchunk, ntot, tab, &ent_off, &perm_off);
     int32_t* dtab;
     WS(c, "kslots", slots.size() * sizeof(KPair), dslots);
     WS(c, "kadj", tab.size() * sizeof(int32_t), dtab);
