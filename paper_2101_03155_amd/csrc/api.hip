@@ -1399,36 +1399,38 @@ int ace_apply_energy_noalloc(ace_ctx* c, const ace_grid* g, int norb, const doub
 
 // ------------------------------------------------------------------ complex orbitals, k-points
 // Pairs whose spectra the owner-computes form of the k-point build keeps
-// resident at a time, or 0 where it does not apply (the plane exceeds LDS, or
-// ACE_WORKSPACE_MAX leaves less than the split passes need): all of them
-// within the budget of the owner paths (ACE_OWNER_SPECTRA_MAX bytes, and 60%
-// of the free device memory), else as many as fit.  The other workspaces of
-// the call are already held, the spectra come last.
+// resident at a time, or 0 where the split passes run instead: all of them
+// within the budget of the owner paths (ACE_OWNER_SPECTRA_MAX bytes, 60% of the
+// free device memory, and what ACE_WORKSPACE_MAX leaves), else as many as fit.
+// Every chunk reads and writes the rows of W that its pairs touch and visits
+// every owner, so a chunk needs about a pair per orbital, more on small grids,
+// where the launches weigh most: the split passes are met at 4 pairs per orbital
+// on 12^3 (512 orbitals: 85.7 ms; 2048 pairs at a time 87.5, 32 at a time 494),
+// 1.4 on 24^3 (512: 150), 1 on 48^3 (128: 44.3; 128 pairs at a time 43.4, 64 50.1)
+// and below on 96^3.  The other workspaces of the call are already held, the
+// spectra come last.
 static int64_t kowner_chunk(ace_ctx* c, int N, int64_t npairs, int ntot, size_t slot_bytes) {
   if (!kpair_owner_fits(N)) return 0;
-  const int64_t few = std::min<int64_t>(npairs, 32);  // the slots of one launch of the split passes
+  const int64_t least = std::min<int64_t>(npairs, std::max<int64_t>(ntot, int64_t(ntot) * 60 / N));
   const size_t have = ws_held(c, "spec");
   size_t room = c->owner_max;
   size_t freeb = 0, totb = 0;
   if (std::min(room, size_t(npairs) * slot_bytes) > have && hipMemGetInfo(&freeb, &totb) == hipSuccess)
     room = std::min(room, size_t(0.6 * double(freeb + have)));
-  int64_t chunk = std::max<int64_t>(few, int64_t(room / slot_bytes));
+  // (the launch grids are 32-bit)
+  int64_t chunk = std::min<int64_t>(std::min(npairs, int64_t(1) << 22), int64_t(room / slot_bytes));
   if (c->ws_cap) {
     // under a workspace cap the tables come out of it first (a workspace never
     // shrinks, the spectra held are freed where they are in the way)
     const size_t ks = ws_held(c, "kslots"), ka = ws_held(c, "kadj");
     const size_t fixed = c->ws_total - have - ks - ka + std::max(ks, size_t(npairs) * sizeof(KPair));
-    for (;;) {
-      chunk = std::min(chunk, npairs);
+    for (; chunk >= least; chunk /= 2) {
       const int64_t nchunk = (npairs + chunk - 1) / chunk;
       const size_t tab = (size_t(nchunk) * (size_t(ntot) + 1) + 4 * size_t(npairs) + size_t(ntot)) * sizeof(int32_t);
       if (fixed + std::max(ka, tab) + size_t(chunk) * slot_bytes <= c->ws_cap) break;
-      if (chunk <= few) return 0;
-      chunk = std::max(few, chunk / 2);
     }
   }
-  // the launch grids are 32-bit
-  return std::min<int64_t>(std::min(chunk, npairs), int64_t(1) << 22);
+  return chunk >= least ? chunk : 0;
 }
 
 int ace_build_kpoints(ace_ctx* c, const ace_grid* g, int norb, int nk, const double* kvec, const double* u,
