@@ -136,8 +136,11 @@ hipError_t refresh_bounds(const double* Q, int ldq, const double* Psi, int64_t l
                           double* res, hipStream_t s);
 void launch_symmetrize(const double* M, int n, double* out, double* negM, double* ex, double* asym, hipStream_t s);
 void launch_neg_sumsq(const double* c, int64_t n, double* out, hipStream_t s);
-// Cholesky of the lower triangle of A (n <= 512) in place; info must be zero on
-// entry; X is n x n doubles of scratch where n > 128.
+// Cholesky A = L L^T of the lower triangle of A (n <= 512); info must be zero on
+// entry.  Up to 128 columns A becomes L.  Beyond, only the diagonal blocks of 128
+// become L's (zeros above the diagonal); the blocks of L below them and the
+// inverses of the diagonal blocks are left in X (n x n doubles, not used up to
+// 128), and A holds residuals in their place.  L's diagonal is always A's.
 void launch_cholesky(double* A, int n, int* info, double* X, hipStream_t s);
 // X = L^-1 of A = L L^T (zeros above the diagonal); info zero on entry, set as by
 // launch_cholesky.  A is overwritten.

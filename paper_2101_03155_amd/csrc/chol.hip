@@ -101,8 +101,9 @@ __global__ __launch_bounds__(CNT) void k_chol_block(double* __restrict__ A, int 
         const double d = row_lane<k>(v[k]);
         if (bad == 0 && !isfinite(d)) bad = -(col0 + k0 + k + 1);
         if (bad == 0 && !(d > 0.0)) bad = col0 + k0 + k + 1;
-        // 1 / sqrt(d): the hardware's approximation (about 26 bits) and one
-        // third-order step; sqrt(d) from it with a Newton correction
+        // 1 / sqrt(d): the hardware's approximation y (about 26 bits) times the
+        // binomial series of (1 - e)^(-1/2) = 1 + e / 2 + 3 e^2 / 8 + ..., e = 1 -
+        // d y^2, to second order; sqrt(d) from it with a Newton correction
         double y = __builtin_amdgcn_rsq(d);
         const double e = fma(-(d * y), y, 1.0);
         y = fma(y * e, fma(0.375, e, 0.5), y);
@@ -243,8 +244,8 @@ __global__ __launch_bounds__(256) void k_chol_tile(const double* __restrict__ S,
 // ---------------------------------------------------------------- launchers
 static dim3 tiles(int M, int R) { return dim3(unsigned((R + 15) / 16), unsigned((M + 15) / 16)); }
 
-// L in A; X (n x n scratch where n > 128) receives the inverses of the diagonal
-// blocks and the blocks of L below them.
+// L in A for n <= 128.  Else A receives the diagonal blocks of L, X (n x n) their
+// inverses and the blocks of L below them; A's blocks there end as residuals.
 void launch_cholesky(double* A, int n, int* info, double* X, hipStream_t s) {
   if (n <= CBN) {
     hipLaunchKernelGGL(k_chol_block, dim3(1), dim3(CNT), 0, s, A, n, n, 0, info, (double*)nullptr, n, 0);
