@@ -1224,8 +1224,9 @@ static int build_impl(ace_ctx* c, const ace_grid* g, int norb, const double* phi
   rec_begin(R, ST_PAIRS, s);
   if (owner) {
     HIPCHK(c, launch_vtable(prec, N, kp, vtab, s));
-    HIPCHK(c, pair_owner(prec, N, phiw, spec, dpk, int(onpk), int(npairs), dadjp, dadj, c->owner_order ? doperm : nullptr,
-                         norb, int64_t(S.adj.size() / 2), W, epart, tw, kp, vtab, 1 << 30, s, R));
+    HIPCHK(c, pair_owner(prec, N, phiw, spec, dpk, int(onpk), int(npairs), dadjp, dadj,
+                         c->owner_order ? doperm : nullptr, norb, int64_t(S.adj.size() / 2), W, epart, tw, kp, vtab,
+                         1 << 30, s, R));
     if (pair_energy) launch_pair_energy(epart, int(onpk), nblk, dpk, dpidx, dV, pair_energy, s);
   } else {
     for (const auto& L : S.launches) {

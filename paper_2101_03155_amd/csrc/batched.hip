@@ -381,10 +381,9 @@ __device__ __forceinline__ P* uniform_ptr(P* p) {
 // offsets.  Adjacency entries (slot, partner) index the slots of the
 // segment's spectra.
 template <typename T, int N, int V>
-__global__ __launch_bounds__(BNTR, (own_inv_waves<T, N>())) void k_batched_owner_r(int nown, const BOwner* __restrict__ own,
-                                                          const BSys* __restrict__ sys,
-                                                          const int32_t* __restrict__ adj,
-                                                          const cplx<T>* __restrict__ spec) {
+__global__ __launch_bounds__(BNTR, (own_inv_waves<T, N>())) void k_batched_owner_r(
+    int nown, const BOwner* __restrict__ own, const BSys* __restrict__ sys, const int32_t* __restrict__ adj,
+    const cplx<T>* __restrict__ spec) {
   constexpr size_t NG = size_t(N) * N * N;
   __shared__ cplx<T> buf[N * r2c_xs<N>()];
   __shared__ cplx<T> tw[N];

@@ -257,12 +257,13 @@ void launch_cholesky(double* A, int n, int* info, double* X, hipStream_t s) {
     hipLaunchKernelGGL(k_chol_block, dim3(1), dim3(CNT), 0, s, A + d, n, b, k0, info, X + d, n, rest);
     if (rest == 0) break;
     // L21 = A21 X11^T, then A21 -= L21 L11^T and L21 += A21 X11^T: one correction
-    hipLaunchKernelGGL((k_chol_tile<true, false>), tiles(rest, b), dim3(256), 0, s, A + below, X + d, X + below, n, rest,
-                       b, b, 1.0, 0.0, info);
-    hipLaunchKernelGGL((k_chol_tile<true, false>), tiles(rest, b), dim3(256), 0, s, X + below, A + d, A + below, n, rest,
-                       b, b, -1.0, 1.0, info);
-    hipLaunchKernelGGL((k_chol_tile<true, false>), tiles(rest, b), dim3(256), 0, s, A + below, X + d, X + below, n, rest,
-                       b, b, 1.0, 1.0, info);
+    const auto product = [&](const double* S, const double* B, double* C, double alpha, double beta) {
+      hipLaunchKernelGGL((k_chol_tile<true, false>), tiles(rest, b), dim3(256), 0, s, S, B, C, n, rest, b, b, alpha,
+                         beta, info);
+    };
+    product(A + below, X + d, X + below, 1.0, 0.0);
+    product(X + below, A + d, A + below, -1.0, 1.0);
+    product(A + below, X + d, X + below, 1.0, 1.0);
     hipLaunchKernelGGL((k_chol_tile<true, true>), tiles(rest, rest), dim3(256), 0, s, X + below, X + below,
                        A + below + b, n, rest, b, rest, -1.0, 1.0, info);
   }

@@ -421,8 +421,8 @@ __device__ __forceinline__ void fft_lines_ls(cplx<T>* buf, TW tw, int tid, L loa
   }
 }
 
-// The same, with the first pass reading its inputs through load(l, p) (an
-// element-wise step fused into the transform's first LDS read).
+// Full transform in LDS (fft_lines) with the first pass reading its inputs
+// through load(l, p): an element-wise step fused into the first LDS read.
 template <typename T, int N, int LINES, int LS, int PS, int NT, int S, bool JFAST, int V, typename TW, typename L>
 __device__ __forceinline__ void fft_lines_load(cplx<T>* buf, TW tw, int tid, L load) {
   static_assert(smooth235(N), "FFT length must be 2^a 3^b 5^c");

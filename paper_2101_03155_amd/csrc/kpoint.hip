@@ -203,8 +203,9 @@ __global__ __launch_bounds__(NT) void k_kfwd_xy(const double2* __restrict__ u, d
 // for each run of equal shifts (lists sorted by (a, b) hold one run per
 // k-point of b).
 template <int N, int TX, int NT, int SPW>
-__global__ __launch_bounds__(NT, N >= 80 ? 3 : 4) void k_kconv_own(double2* __restrict__ spec, const KPair* __restrict__ slots,
-                                                  int64_t nslots, const double2* __restrict__ twg, KernelParams kp) {
+__global__ __launch_bounds__(NT, N >= 80 ? 3 : 4) void k_kconv_own(
+    double2* __restrict__ spec, const KPair* __restrict__ slots, int64_t nslots, const double2* __restrict__ twg,
+    KernelParams kp) {
   constexpr size_t NG = size_t(N) * N * N;
   constexpr int NTILE = N * N / TX;
   __shared__ double2 buf[N * TX];

@@ -231,8 +231,8 @@ __global__ __launch_bounds__(NT) void k_conv_z_r(cplx<T>* __restrict__ spec, con
     double* es = epart ? epart + 2 * (size_t(slot >> 1) * gridDim.x + blockIdx.x) + (slot & 1) : nullptr;
     // (each body's first barrier orders the previous body's reads of buf,
     // tw and red before its writes)
-    body_conv_z_r_v<T, N, TX, NT, 0, PP>(spec + size_t(slot) * N * PP, blockIdx.x * TX, kp, buf, tw, threadIdx.x, true, es,
-                                  red, vt != nullptr, vv);
+    body_conv_z_r_v<T, N, TX, NT, 0, PP>(spec + size_t(slot) * N * PP, blockIdx.x * TX, kp, buf, tw, threadIdx.x,
+                                         true, es, red, vt != nullptr, vv);
   }
 }
 
@@ -269,11 +269,10 @@ __global__ __launch_bounds__(NT) void k_conv_z_c(cplx<T>* __restrict__ spec, con
 // planes and spectra they read in that XCD's L2 (3-6% faster at 32 waters).
 // YC > 1: the z index runs over (plane, row class).
 template <typename T, int N, int NT, bool XCD = false, int YC = 1>
-__global__ __launch_bounds__(NT, (own_inv_waves<T, N>())) void k_inv_owner_r(const T* __restrict__ phi, const cplx<T>* __restrict__ spec,
-                                                    const int32_t* __restrict__ adj_ptr,
-                                                    const int32_t* __restrict__ adj,
-                                                    const int32_t* __restrict__ operm, T* __restrict__ W,
-                                                    const cplx<T>* __restrict__ twg) {
+__global__ __launch_bounds__(NT, (own_inv_waves<T, N>())) void k_inv_owner_r(
+    const T* __restrict__ phi, const cplx<T>* __restrict__ spec, const int32_t* __restrict__ adj_ptr,
+    const int32_t* __restrict__ adj, const int32_t* __restrict__ operm, T* __restrict__ W,
+    const cplx<T>* __restrict__ twg) {
   constexpr size_t NG = size_t(N) * N * N;
   __shared__ cplx<T> buf[cls_elems<N, YC>()];
   __shared__ cplx<T> tw[N];
@@ -291,8 +290,9 @@ __global__ __launch_bounds__(NT, (own_inv_waves<T, N>())) void k_inv_owner_r(con
   for (int t = threadIdx.x; t < N; t += NT) tw[t] = twg[t];
   const int cls = z % YC;
   const size_t zo = size_t(z / YC) * N * N;
-  body_inv_owner_r<T, N, NT, own_inv_plan<T, N>(), YC, cls_pitch<T, N, YC>()>(phi, spec, adj, adj_ptr[k], adj_ptr[k + 1], zo,
-                                    W + size_t(k) * NG + zo + size_t(cls) * N, buf, tw, threadIdx.x, cls);
+  body_inv_owner_r<T, N, NT, own_inv_plan<T, N>(), YC, cls_pitch<T, N, YC>()>(
+      phi, spec, adj, adj_ptr[k], adj_ptr[k + 1], zo, W + size_t(k) * NG + zo + size_t(cls) * N, buf, tw, threadIdx.x,
+      cls);
 }
 
 template <typename T, int N, int NT, bool EN>
@@ -420,51 +420,49 @@ static hipError_t pair_owner_t(const void* phi_, void* spec_, const Pack* packs,
                                int64_t nadj, void* W_,
                                double* epart, const void* tw_, const KernelParams& kp, const void* vt_, int chunk,
                                hipStream_t s, EventRecorder* rec) {
-  {
-    using C = cplx<T>;
-    const T* phi = static_cast<const T*>(phi_);
-    T* W = static_cast<T*>(W_);
-    C* spec = static_cast<C*>(spec_);
-    const C* tw = static_cast<const C*>(tw_);
-    using Cfg = OwnCfg<T, N>;
-    constexpr int YC = Cfg::YC, NTR = Cfg::NTO, NTZ = Cfg::NTZ, SPW = Cfg::SPW, NTILE = own_tiles<T, N>();
-    constexpr int PP = cls_pitch<T, N, YC>();
-    constexpr size_t SLOT = size_t(N) * YC * PP;  // complex values per pair slot
-    const double u3 = double(N) * N * N * sizeof(T);
-    // forward and z pass in launches of at most `chunk` packs (grid y = 2 *
-    // packs <= 65534); one launch each over all pairs measured fastest
-    const int CH = chunk < 1 ? 1 : (chunk > 32767 ? 32767 : chunk);
-    for (int c0 = 0; c0 < npacks; c0 += CH) {
-      const int nc = (npacks - c0 < CH) ? npacks - c0 : CH;
-      const int pc = (2 * c0 + 2 * nc <= npairs) ? 2 * nc : npairs - 2 * c0;  // pairs in this chunk
-      rec_begin(rec, KC_FWD_XY, s);
-      hipLaunchKernelGGL((k_fwd_xy_r<T, N, Cfg::NTF, false, YC, PP>), dim3(2 * nc, N * YC), dim3(Cfg::NTF), 0, s, phi,
-                         spec + 2 * size_t(c0) * SLOT, packs + c0, tw);
-      rec_end(rec, KC_FWD_XY, s, 3 * u3 * pc);
-      rec_begin(rec, KC_CONV_Z, s);
-      const dim3 gz(NTILE, (2 * nc + SPW - 1) / SPW);
-      C* spz = spec + 2 * size_t(c0) * SLOT;
-      double* ep = epart ? epart + 2 * size_t(c0) * NTILE : nullptr;
-      if constexpr (YC > 1)
-        hipLaunchKernelGGL((k_conv_z_c<T, N, Cfg::TX, YC, NTZ, SPW>), gz, dim3(NTZ), 0, s, spz, packs + c0, 2 * nc, tw,
-                           ep, static_cast<const T*>(vt_));
-      else
-        hipLaunchKernelGGL((k_conv_z_r<T, N, Cfg::TX, NTZ, SPW, PP>), gz, dim3(NTZ), 0, s, spz, packs + c0, 2 * nc, tw, kp,
-                           ep, static_cast<const T*>(vt_));
-      rec_end(rec, KC_CONV_Z, s, 2 * u3 * pc);
-    }
-    if (W) {
-      rec_begin(rec, KC_INV_XY, s);
-      if (N * YC % 8 == 0)
-        hipLaunchKernelGGL((k_inv_owner_r<T, N, NTR, true, YC>), dim3(N * YC * norb), dim3(NTR), 0, s, phi, spec, adj_ptr, adj,
-                           operm, W, tw);
-      else
-        hipLaunchKernelGGL((k_inv_owner_r<T, N, NTR, false, YC>), dim3(N * YC, norb), dim3(NTR), 0, s, phi, spec, adj_ptr, adj, operm,
-                           W, tw);
-      rec_end(rec, KC_INV_XY, s, double(nadj) * (2.0 * SLOT * sizeof(T) + u3) + double(norb) * u3);
-    }
-    return hipGetLastError();
+  using C = cplx<T>;
+  const T* phi = static_cast<const T*>(phi_);
+  T* W = static_cast<T*>(W_);
+  C* spec = static_cast<C*>(spec_);
+  const C* tw = static_cast<const C*>(tw_);
+  using Cfg = OwnCfg<T, N>;
+  constexpr int YC = Cfg::YC, NTR = Cfg::NTO, NTZ = Cfg::NTZ, SPW = Cfg::SPW, NTILE = own_tiles<T, N>();
+  constexpr int PP = cls_pitch<T, N, YC>();
+  constexpr size_t SLOT = size_t(N) * YC * PP;  // complex values per pair slot
+  const double u3 = double(N) * N * N * sizeof(T);
+  // forward and z pass in launches of at most `chunk` packs (grid y = 2 *
+  // packs <= 65534); one launch each over all pairs measured fastest
+  const int CH = chunk < 1 ? 1 : (chunk > 32767 ? 32767 : chunk);
+  for (int c0 = 0; c0 < npacks; c0 += CH) {
+    const int nc = (npacks - c0 < CH) ? npacks - c0 : CH;
+    const int pc = (2 * c0 + 2 * nc <= npairs) ? 2 * nc : npairs - 2 * c0;  // pairs in this chunk
+    rec_begin(rec, KC_FWD_XY, s);
+    hipLaunchKernelGGL((k_fwd_xy_r<T, N, Cfg::NTF, false, YC, PP>), dim3(2 * nc, N * YC), dim3(Cfg::NTF), 0, s, phi,
+                       spec + 2 * size_t(c0) * SLOT, packs + c0, tw);
+    rec_end(rec, KC_FWD_XY, s, 3 * u3 * pc);
+    rec_begin(rec, KC_CONV_Z, s);
+    const dim3 gz(NTILE, (2 * nc + SPW - 1) / SPW);
+    C* spz = spec + 2 * size_t(c0) * SLOT;
+    double* ep = epart ? epart + 2 * size_t(c0) * NTILE : nullptr;
+    if constexpr (YC > 1)
+      hipLaunchKernelGGL((k_conv_z_c<T, N, Cfg::TX, YC, NTZ, SPW>), gz, dim3(NTZ), 0, s, spz, packs + c0, 2 * nc, tw,
+                         ep, static_cast<const T*>(vt_));
+    else
+      hipLaunchKernelGGL((k_conv_z_r<T, N, Cfg::TX, NTZ, SPW, PP>), gz, dim3(NTZ), 0, s, spz, packs + c0, 2 * nc, tw,
+                         kp, ep, static_cast<const T*>(vt_));
+    rec_end(rec, KC_CONV_Z, s, 2 * u3 * pc);
   }
+  if (W) {
+    rec_begin(rec, KC_INV_XY, s);
+    if (N * YC % 8 == 0)
+      hipLaunchKernelGGL((k_inv_owner_r<T, N, NTR, true, YC>), dim3(N * YC * norb), dim3(NTR), 0, s, phi, spec,
+                         adj_ptr, adj, operm, W, tw);
+    else
+      hipLaunchKernelGGL((k_inv_owner_r<T, N, NTR, false, YC>), dim3(N * YC, norb), dim3(NTR), 0, s, phi, spec,
+                         adj_ptr, adj, operm, W, tw);
+    rec_end(rec, KC_INV_XY, s, double(nadj) * (2.0 * SLOT * sizeof(T) + u3) + double(norb) * u3);
+  }
+  return hipGetLastError();
 }
 
 #define ACE_PAIR_SIZES(X) X(8) X(12) X(16) X(24) X(32) X(48) X(64) X(80) X(96) X(100) X(108) X(120) X(160)
@@ -581,9 +579,9 @@ bool pair_fused_fits(int prec, int N) {
   }
 }
 
-// The owner-computes path (real-to-complex transforms) is the default wherever
-// its half-spectrum plane fits in LDS: measured faster than the split passes
-// even at one workgroup per CU (120^3 FP64, 160^3 FP32).
+// The owner-computes path (real-to-complex transforms) is the default at every
+// size: measured faster than the split passes with planes that fit once per CU
+// (160^3 FP32) and with FP64 planes taken as classes of rows (100^3 and up).
 PairShape pair_default_shape(int prec, int N) {
   PairShape sh;
   sh.fused_xy = 3;

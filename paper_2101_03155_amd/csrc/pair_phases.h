@@ -492,7 +492,8 @@ __device__ __forceinline__ void body_conv_z_c(cplx<T>* spec_p, int f0, cplx<T>* 
     for (int q = 0; q < YC; ++q) {
       const T v = vv[s * YC + q];
       if (eslot)
-        es += double((kx == 0 || kx == N / 2) ? 1 : 2) * double(v) * (double(t[q].x) * t[q].x + double(t[q].y) * t[q].y);
+        es += double((kx == 0 || kx == N / 2) ? 1 : 2) * double(v) *
+              (double(t[q].x) * t[q].x + double(t[q].y) * t[q].y);
       t[q].x *= v;
       t[q].y *= v;
     }
@@ -681,10 +682,14 @@ template <typename T, int N, int YC> __host__ __device__ constexpr bool own_fuse
 }
 // Waves per SIMD of the owner pass: six keep three workgroups per CU for FP32
 // at 96^3 (81 registers had left two).
-template <typename T, int N> __host__ __device__ constexpr int own_inv_waves() { return sizeof(T) == 4 && N == 96 ? 6 : 4; }
+template <typename T, int N> __host__ __device__ constexpr int own_inv_waves() {
+  return sizeof(T) == 4 && N == 96 ? 6 : 4;
+}
 // Plan order of the owner pass: reversed for FP64 at 160^3, where a last radix
 // of 16 would need more registers than there are.
-template <typename T, int N> __host__ __device__ constexpr int own_inv_plan() { return sizeof(T) == 8 && N == 160 ? 1 : 0; }
+template <typename T, int N> __host__ __device__ constexpr int own_inv_plan() {
+  return sizeof(T) == 8 && N == 160 ? 1 : 0;
+}
 
 template <typename T, int N, int NT, int V = 0, int YC = 1, int PP = N / YC * r2c_xs<N>()>
 __device__ __forceinline__ void body_inv_owner_r(const T* __restrict__ phi, const cplx<T>* __restrict__ spec,

@@ -783,8 +783,8 @@ void launch_mlp_reduce(const float* gpart, const float* lpart, int nb, float* gr
 }
 void launch_mlp_adam(const float* gpart, const float* lpart, int nb, float* m, float* mom, float* vel, int step,
                      float lr, float b1, float b2, float eps, float* loss_acc, hipStream_t s) {
-  hipLaunchKernelGGL(k_mlp_adam, dim3(gridn(NPAR, RPB)), dim3(RG * RPB), 0, s, gpart, lpart, nb, m, mom, vel, step, lr, b1,
-                     b2, eps, loss_acc);
+  hipLaunchKernelGGL(k_mlp_adam, dim3(gridn(NPAR, RPB)), dim3(RG * RPB), 0, s, gpart, lpart, nb, m, mom, vel, step, lr,
+                     b1, b2, eps, loss_acc);
 }
 void launch_select(const float* pred, const float* feats, int64_t np, int norb, const float* model, double budget,
                    const double* O, double rho_cut, float ood_tol, int* ood, double* tau, uint8_t* keep, int64_t cap,
