@@ -151,25 +151,25 @@ __global__ __launch_bounds__(256) void k_row_abs(const double* __restrict__ G, i
 }
 
 // Y = 1.5 X - 0.5 X G.  With rows (the first iteration) X and G stand for the
-// scaled X / sqrt(s) and its G / s, s the largest of the n row sums.
+// scaled X / sqrt(s) and its G / s, s the largest of the n row sums; both are
+// scaled before they are multiplied, so that only squares need be in range.
 __global__ __launch_bounds__(256) void k_ns_step(const double* __restrict__ X, const double* __restrict__ G,
                                                  const double* __restrict__ rows, int n, double* __restrict__ Y) {
-  const int m0 = blockIdx.y * 16, r0 = blockIdx.x * 16, lane = threadIdx.x;
-  const tiny_d4 z = tiny_tile<double, false>(X, n, G, n, m0, r0, n, n, n, n);
-  if (lane >= 64) return;
-  double fx = 1.5, fz = 0.5;
+  const int m0 = blockIdx.y * 16, r0 = blockIdx.x * 16, lane = threadIdx.x & 63;
+  double inv = 1.0, invs = 1.0;
   if (rows) {
     double s = 0.0;
     for (int j = lane; j < n; j += 64) s = fmax(s, rows[j]);
     for (int off = 32; off > 0; off >>= 1) s = fmax(s, __shfl_xor(s, off, 64));
-    const double inv = 1.0 / sqrt(s);
-    fx = 1.5 * inv;
-    fz = 0.5 * inv / s;
+    inv = 1.0 / sqrt(s);
+    invs = 1.0 / s;
   }
+  const tiny_d4 z = tiny_tile<double, false>(X, n, G, n, m0, r0, n, n, n, n, inv, invs);
+  if (threadIdx.x >= 64) return;
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const int i = m0 + lane / 16 + 4 * q, j = r0 + lane % 16;
-    if (i < n && j < n) Y[int64_t(i) * n + j] = fx * X[int64_t(i) * n + j] - fz * z[q];
+    if (i < n && j < n) Y[int64_t(i) * n + j] = 1.5 * (inv * X[int64_t(i) * n + j]) - 0.5 * z[q];
   }
 }
 
