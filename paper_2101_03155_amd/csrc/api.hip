@@ -1127,6 +1127,23 @@ static int build_impl(ace_ctx* c, const ace_grid* g, int norb, const double* phi
   rc = schedule_for(c, pr, npairs, norb, mp, false, &Sp);
   if (rc) return rc;
   const size_t es = prec == 0 ? sizeof(double) : sizeof(float);
+  PairShape sh = shape_for(c, prec, N);
+  // owner-computes W when every pair's half spectrum fits the budget
+  const int64_t onpk = (npairs + 1) / 2;
+  const size_t spec_bytes = size_t(2 * onpk) * pair_owner_slot_elems(prec, N) * 2 * es;
+  bool owner = sh.fused_xy == 3 && spec_bytes <= c->owner_max;
+  if (const size_t have = ws_held(c, "spec"); owner && spec_bytes > have) {
+    // ... and when the spectra, beyond what the workspace already holds, take
+    // at most 60% of the free device memory (a fuller device slows down), with
+    // room for W and the FP32 orbitals in the rest
+    const size_t wb = xi || (Wout && prec == 1) ? size_t(norb) * ng * es : 0;
+    const size_t pb = prec == 1 ? size_t(norb) * ng * es : 0;
+    const size_t more = wb - std::min(wb, ws_held(c, "W")) + pb - std::min(pb, ws_held(c, "phi32"));
+    size_t freeb = 0, totb = 0;
+    if (hipMemGetInfo(&freeb, &totb) == hipSuccess)
+      owner = double(spec_bytes) <= 0.6 * double(freeb + have) &&
+              double(spec_bytes + more) <= 0.95 * double(freeb + have);
+  }
   void *W, *spec, *phiw;
   double *epart = nullptr, *part, *Mraw, *Lb, *Li, *scal;
   int* info;
@@ -1145,24 +1162,12 @@ static int build_impl(ace_ctx* c, const ace_grid* g, int norb, const double* phi
   if (prec == 1) WS(c, "phi32", size_t(norb) * ng * sizeof(float), phiw);
   else phiw = (void*)phi;
 
-  PairShape sh = shape_for(c, prec, N);
-  // owner-computes W when every pair's half spectrum fits the budget
-  const int64_t onpk = (npairs + 1) / 2;
   const int otile = pair_owner_ntile(prec, N);
-  const size_t spec_bytes = size_t(2 * onpk) * pair_owner_slot_elems(prec, N) * 2 * es;
   const size_t otab_bytes = Sp->table.size(), oep_bytes = pair_energy ? size_t(onpk) * otile * 2 * sizeof(double) : 0;
   const size_t vtab_bytes = size_t(N / 2 + 1) * (N / 2 + 1) * (N / 2 + 1) * es;
-  bool owner = sh.fused_xy == 3 && spec_bytes <= c->owner_max;
-  const size_t have = ws_held(c, "spec");
-  if (owner && spec_bytes > have) {
-    // ... and when the spectra, beyond what the workspace already holds, take
-    // at most 60% of the free device memory (a fuller device slows down)
-    size_t freeb = 0, totb = 0;
-    if (hipMemGetInfo(&freeb, &totb) == hipSuccess) owner = double(spec_bytes) <= 0.6 * double(freeb + have);
-  }
   if (owner && c->ws_cap) {
     // ... and ACE_WORKSPACE_MAX holds them and their tables beside the rest
-    size_t need = c->ws_total - have + spec_bytes;
+    size_t need = c->ws_total - ws_held(c, "spec") + spec_bytes;
     for (auto& t : {std::make_pair("otab", otab_bytes), std::make_pair("epart", oep_bytes),
                     std::make_pair("vtab", vtab_bytes)})
       need += std::max(ws_held(c, t.first), t.second) - ws_held(c, t.first);
